@@ -294,12 +294,34 @@ int launch_from_canonical(DevVolume v, const float* F, const uint16_t* W, const 
 int launch_extract(DevVolume v, uint32_t* counts, unsigned long long* offsets, long long* total, float* V,
                    float* N, int32_t* G, long long cap, void* stream);
 int launch_fill_u64(unsigned long long* p, int n, unsigned long long value, void* stream);
-int launch_placement_clear(unsigned long long* table, int table_size, void* stream);
-int launch_placement_count(const float* depth, int depth_pitch, int width, int height,
-                           float fx, float fy, float cx, float cy, const float* T,
-                           float o0, float o1, float o2, float cell,
-                           unsigned long long* table, int table_size, int* overflow,
-                           const int32_t* boxes, int n_boxes, float voxel, void* stream);
+
+// Placement counting of one frame on the lattice of side `cell` (metres):
+// endpoints inside one of the boxes (h_t[3], dims[3], global voxels) are left
+// out.  The pose and the boxes travel in the launch's arguments.
+constexpr int kPlaceTable = 8192;     // hash slots, a power of two
+constexpr int kMaxPlaceBoxes = 64;
+struct PlacementCount {
+    const float* depth;
+    int32_t depth_pitch, width, height;
+    float fx, fy, cx, cy;
+    float T[12];
+    float o[3];                // grid origin
+    float cell, voxel;
+    unsigned long long* table; // 2 * table_size words, empty before the count and after the collection
+    int32_t table_size;
+    int32_t n_boxes;
+    int* overflow;             // bit 0: table full, bit 1: a cell or voxel index out of range
+    int32_t boxes[6 * kMaxPlaceBoxes];
+};
+// What a count found (pinned host memory).
+struct PlacementCells {
+    int32_t n, overflow;
+    unsigned long long key[kPlaceTable];
+    unsigned long long count[kPlaceTable];
+};
+int launch_placement_clear(unsigned long long* table, int table_size, int* overflow, void* stream);
+// The count and its collection into *out (pinned), which also empties the table.
+int launch_placement_count(const PlacementCount& P, PlacementCells* out, void* stream);
 
 // Camera tracking (mvf_track.hip).  The pose estimate and the statistics of
 // every Gauss-Newton step live in device memory.

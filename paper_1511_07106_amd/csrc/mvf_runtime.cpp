@@ -252,10 +252,8 @@ struct mvf_ctx {
     std::map<int, std::map<std::vector<int>, int>> placed;
     unsigned long long* place_table = nullptr;
     int* place_overflow = nullptr;
-    float* place_T = nullptr;
-    int32_t* place_boxes = nullptr;  // kMaxPlaceBoxes x (h_t, dims)
-    static constexpr int kMaxPlaceBoxes = 64;
-    static constexpr int kPlaceTable = 8192;
+    PlacementCells* place_cells = nullptr;  // pinned: what the last count found
+    bool place_clean = false;               // the table is empty (every finished count leaves it so)
     double* diff_partials = nullptr;
     int diff_partials_n = 0;
     // brick-layout mirror of the caller's dense volume (differentiable
@@ -1527,8 +1525,7 @@ mvf_status mvf_destroy(mvf_ctx* c)
     if (c->counters) (void)hipFree(c->counters);
     if (c->place_table) (void)hipFree(c->place_table);
     if (c->place_overflow) (void)hipFree(c->place_overflow);
-    if (c->place_T) (void)hipFree(c->place_T);
-    if (c->place_boxes) (void)hipFree(c->place_boxes);
+    if (c->place_cells) (void)hipHostFree(c->place_cells);
     if (c->diff_partials) (void)hipFree(c->diff_partials);
     if (c->extract_buf) (void)hipFree(c->extract_buf);
     if (c->track.dev) (void)hipFree(c->track.dev);
@@ -2353,40 +2350,40 @@ static mvf_status placement_count_impl(mvf_ctx* c, const mvf_frame* f, const flo
                                        const Grid& g, int d_v, const std::vector<int32_t>& boxes,
                                        std::vector<std::pair<std::vector<int>, int>>* out, hipStream_t s)
 {
-    if (!c->place_table) {
-        CHECK_HIP(hipMalloc((void**)&c->place_table, sizeof(unsigned long long) * 2 * mvf_ctx::kPlaceTable));
-        CHECK_HIP(hipMalloc((void**)&c->place_overflow, 256));
-        CHECK_HIP(hipMalloc((void**)&c->place_T, 256));
-        CHECK_HIP(hipMalloc((void**)&c->place_boxes, sizeof(int32_t) * 6 * mvf_ctx::kMaxPlaceBoxes));
-    }
     const int n_boxes = (int)boxes.size() / 6;
-    if (n_boxes > mvf_ctx::kMaxPlaceBoxes) return set_error(MVF_ERR_INVALID_ARG, "too many placement boxes");
-    const float cell = g.d.voxel_size * (float)(d_v - 2);
-    CHECK_HIP(hipMemcpyAsync(c->place_T, T, sizeof(float) * 12, hipMemcpyHostToDevice, s));
-    if (n_boxes)
-        CHECK_HIP(hipMemcpyAsync(c->place_boxes, boxes.data(), sizeof(int32_t) * boxes.size(), hipMemcpyHostToDevice,
-                                 s));
-    CHECK_LAUNCH(launch_placement_clear(c->place_table, mvf_ctx::kPlaceTable, s));
-    CHECK_HIP(hipMemsetAsync(c->place_overflow, 0, sizeof(int), s));
-    CHECK_LAUNCH(launch_placement_count(f->depth, f->depth_pitch ? f->depth_pitch : f->width, f->width, f->height,
-                                        K->fx, K->fy, K->cx, K->cy, c->place_T, g.d.origin[0], g.d.origin[1],
-                                        g.d.origin[2], cell, c->place_table, mvf_ctx::kPlaceTable,
-                                        c->place_overflow, c->place_boxes, n_boxes, g.d.voxel_size, s));
-    std::vector<unsigned long long> tab(2 * mvf_ctx::kPlaceTable);
-    int ovf = 0;
-    CHECK_HIP(hipMemcpyAsync(tab.data(), c->place_table, tab.size() * 8, hipMemcpyDeviceToHost, s));
-    CHECK_HIP(hipMemcpyAsync(&ovf, c->place_overflow, sizeof(int), hipMemcpyDeviceToHost, s));
+    if (n_boxes > kMaxPlaceBoxes) return set_error(MVF_ERR_INVALID_ARG, "too many placement boxes");
+    if (!c->place_table) CHECK_HIP(hipMalloc((void**)&c->place_table, sizeof(unsigned long long) * 2 * kPlaceTable));
+    if (!c->place_overflow) CHECK_HIP(hipMalloc((void**)&c->place_overflow, 256));
+    if (!c->place_cells) CHECK_HIP(hipHostMalloc((void**)&c->place_cells, sizeof(PlacementCells), hipHostMallocDefault));
+    if (!c->place_clean) CHECK_LAUNCH(launch_placement_clear(c->place_table, kPlaceTable, c->place_overflow, s));
+    c->place_clean = false;
+    PlacementCount P{};
+    P.depth = f->depth;
+    P.depth_pitch = f->depth_pitch ? f->depth_pitch : f->width;
+    P.width = f->width;
+    P.height = f->height;
+    P.fx = K->fx; P.fy = K->fy; P.cx = K->cx; P.cy = K->cy;
+    memcpy(P.T, T, sizeof(P.T));
+    memcpy(P.o, g.d.origin, sizeof(P.o));
+    P.cell = g.d.voxel_size * (float)(d_v - 2);
+    P.voxel = g.d.voxel_size;
+    P.table = c->place_table;
+    P.table_size = kPlaceTable;
+    P.n_boxes = n_boxes;
+    P.overflow = c->place_overflow;
+    if (n_boxes) memcpy(P.boxes, boxes.data(), sizeof(int32_t) * boxes.size());
+    CHECK_LAUNCH(launch_placement_count(P, c->place_cells, s));
     CHECK_HIP(hipStreamSynchronize(s));
-    if (ovf & 1) return set_error(MVF_ERR_STATE, "more than %d distinct placement cells", mvf_ctx::kPlaceTable);
-    if (ovf & 2) return set_error(MVF_ERR_INVALID_ARG, "placement cell index out of range");
+    c->place_clean = true;
+    const PlacementCells& found = *c->place_cells;
+    if (found.overflow & 1) return set_error(MVF_ERR_STATE, "more than %d distinct placement cells", kPlaceTable);
+    if (found.overflow & 2) return set_error(MVF_ERR_INVALID_ARG, "placement cell index out of range");
     out->clear();
-    for (int i = 0; i < mvf_ctx::kPlaceTable; ++i) {
-        const unsigned long long key = tab[2 * i];
-        if (key == ~0ull) continue;
-        const long long nrays = (long long)tab[2 * i + 1];
+    for (int i = 0; i < found.n; ++i) {
+        const unsigned long long key = found.key[i];
         std::vector<int> k = { (int)((key >> 42) & 0x1FFFFF) - (1 << 20), (int)((key >> 21) & 0x1FFFFF) - (1 << 20),
                                (int)(key & 0x1FFFFF) - (1 << 20) };
-        out->push_back({k, (int)nrays});
+        out->push_back({k, (int)found.count[i]});
     }
     std::sort(out->begin(), out->end());
     return MVF_OK;
