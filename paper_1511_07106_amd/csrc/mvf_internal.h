@@ -287,12 +287,23 @@ int launch_ray_bounds_merge(const LaunchHeader* hdr, const DevFrame* frames, con
 int launch_to_canonical(DevVolume v, float* F, uint16_t* W, uint32_t* C, void* stream);
 int launch_from_canonical(DevVolume v, const float* F, const uint16_t* W, const uint32_t* C,
                           void* stream);
-// Surface points of one volume: per-brick counts, their exclusive prefix sum
-// (offsets, nbricks entries; total[0] = the sum) and, when cap > 0, the
-// emission of the first cap points (V, N: 3 floats each; G: 3 ints, or null)
-// in brick order.  counts: nbricks entries.
-int launch_extract(DevVolume v, uint32_t* counts, unsigned long long* offsets, long long* total, float* V,
-                   float* N, int32_t* G, long long cap, void* stream);
+// Surface points of one volume of nbricks bricks: scratch of
+// extract_buffer_bytes(nbricks) device bytes laid out by extract_buffers, and
+// a pinned host word that receives the number of points.  With cap > 0 the
+// first cap points are written (V, N: 3 floats each; G: 3 ints, or null) in
+// brick order.
+struct ExtractBuffers {
+    uint32_t* list;      // bricks with a set cell mask, in brick order
+    uint32_t* counts;    // points of each listed brick
+    uint32_t* group_n;   // points of each 16 listed bricks
+    uint32_t* chunk_n;   // listed bricks of each 1024 bricks
+    uint32_t* super_n;   // points of each 1024 listed bricks
+    uint32_t* list_n;
+    long long* total;    // pinned
+};
+size_t extract_buffer_bytes(size_t nbricks);
+ExtractBuffers extract_buffers(void* mem, size_t nbricks, long long* total);
+int launch_extract(DevVolume v, const ExtractBuffers& B, float* V, float* N, int32_t* G, long long cap, void* stream);
 int launch_fill_u64(unsigned long long* p, int n, unsigned long long value, void* stream);
 
 // Placement counting of one frame on the lattice of side `cell` (metres):

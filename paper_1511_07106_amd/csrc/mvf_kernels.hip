@@ -2427,9 +2427,17 @@ int launch_placement_count(const PlacementCount& P, PlacementCells* out, void* s
 // sub-block with a clear cell-mask bit has no corner F <= 2^-100, hence no
 // sign change: such z-slice pairs and bricks are skipped.
 //
-// Three launches: per-brick counts (one wavefront per brick), an exclusive
-// prefix sum over the bricks, and the emission, which writes brick by brick
-// (inside a brick z-slice by z-slice, x fastest), so the order is fixed.
+// Launches: the bricks with a set cell mask are counted per chunk of 1024 and
+// listed in brick order; the listed bricks' points are counted, 16 bricks a
+// block, into sums per block group and per 64 groups; the emission adds up
+// the sums before its group and writes brick by brick (inside a brick z-slice
+// by z-slice, x fastest), so the order is fixed.
+//
+// Bound: launch and load latency (the surface's bricks of a 512^3 room are 7 %
+// of 262k): 2.8 + 4.5 + 15 + 4 us to count and 26 us to emit.  A wavefront for
+// every brick of the volume, with its cells' corners loaded slice by slice,
+// took 43 us to count and 57 us to emit, and one block scanning all bricks'
+// counts 430 us.  Count and emission of a 512^3 room: 1.06 -> 0.13 ms.
 // ---------------------------------------------------------------------------
 struct SurfVoxel {
     bool emit;
@@ -2437,22 +2445,48 @@ struct SurfVoxel {
     float c[8];   // corner (x + (k & 1), y + (k >> 1 & 1), z + (k >> 2))
 };
 
-static __device__ __forceinline__ void surf_voxel(const DevVolume& v, GPTR(const float) F, int gx, int gy, int gz,
-                                                  SurfVoxel& S)
+constexpr int kExtractGroup = 16;              // bricks per group: four wavefronts of four
+constexpr int kExtractSuper = 64;              // groups per super sum
+constexpr int kExtractChunk = 1024;            // bricks per listing block
+constexpr int kExtractBlocks = 2048;           // most blocks of the counting and the emission
+
+// The values a brick's cells read: lane (lx, ly) holds, for each of the
+// planes z = 0 .. 8, the voxels (x, y), (x + 1, y), (x, y + 1), (x + 1, y + 1).
+// All 36 loads are in flight together.  Neighbours past the padded volume
+// read its last plane; surf_voxel leaves their cells out.
+static __device__ __forceinline__ void load_brick_cells(const DevVolume& v, int bx, int by, int bz, int lane,
+                                                        float (&P)[kBrick + 1][4])
 {
-    S.emit = false;
-    S.axis = -1;
-    if (gx + 1 >= v.dims[0] || gy + 1 >= v.dims[1] || gz + 1 >= v.dims[2]) return;
-    bool observed = true;
+    GPTR(const float) const F = gptr((const float*)v.F);
+    const int x0 = 8 * bx + (lane & 7), y0 = 8 * by + (lane >> 3);
+    const int x1 = min(x0 + 1, 8 * v.bd[0] - 1), y1 = min(y0 + 1, 8 * v.bd[1] - 1);
+    const int bz1 = min(bz + 1, v.bd[2] - 1);
+    uint32_t col[4];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        const int x = gx + (k & 1), y = gy + ((k >> 1) & 1), z = gz + (k >> 2);
-        const size_t o = brick_index(v.bd, x >> 3, y >> 3, z >> 3) * kBrickVox +
-                         (size_t)(((z & 7) << 6) | ((y & 7) << 3) | (x & 7));
-        S.c[k] = F[o];
-        observed &= !__builtin_isnan(S.c[k]);
+    for (int k = 0; k < 4; ++k) {
+        const int x = (k & 1) ? x1 : x0, y = (k & 2) ? y1 : y0;
+        col[k] = brick_index32(v, x >> 3, y >> 3, 0) * (uint32_t)kBrickVox + (uint32_t)(((y & 7) << 3) | (x & 7));
     }
-    if (!observed) return;
+#pragma unroll
+    for (int z = 0; z <= kBrick; ++z) {
+        const uint32_t off = z < kBrick ? (uint32_t)bz * kBrickVox + 64u * z
+                                        : (uint32_t)bz1 * kBrickVox + (bz1 == bz ? 64u * (kBrick - 1) : 0u);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) P[z][k] = ld_elem(F, col[k] + off);
+    }
+}
+
+static __device__ __forceinline__ void surf_voxel(const DevVolume& v, int gx, int gy, int gz, const float (&lo)[4],
+                                                  const float (&hi)[4], SurfVoxel& S)
+{
+    bool observed = gx + 1 < v.dims[0] && gy + 1 < v.dims[1] && gz + 1 < v.dims[2];
+    S.axis = -1;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        S.c[k] = lo[k];
+        S.c[4 + k] = hi[k];
+        observed = observed && !__builtin_isnan(lo[k]) && !__builtin_isnan(hi[k]);
+    }
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         const float f0 = S.c[0], f1 = S.c[1 << a];
@@ -2460,7 +2494,7 @@ static __device__ __forceinline__ void surf_voxel(const DevVolume& v, GPTR(const
         const bool change = (f0 > 0.0f && f1 <= 0.0f) || (f0 <= 0.0f && f1 > 0.0f);
         if (S.axis < 0 && in_band && change) S.axis = a;
     }
-    S.emit = S.axis >= 0;
+    S.emit = observed && S.axis >= 0;
 }
 
 // Bits of the cell mask for the two z-slices 2 zp and 2 zp + 1 of a brick.
@@ -2469,91 +2503,169 @@ static __device__ __forceinline__ uint32_t cmask_pair(uint64_t cm, int zp)
     return (uint32_t)((cm >> (16 * zp)) & 0xffffu);
 }
 
-__global__ __launch_bounds__(256) void mvf_extract_count_kernel(DevVolume v, size_t nbricks, uint32_t* counts)
+// Sum over a 256-thread block (every thread gets it).
+static __device__ __forceinline__ uint32_t block_sum256(uint32_t x, uint32_t* part)
 {
-    const int lane = threadIdx.x & 63;
-    const int lx = lane & 7, ly = lane >> 3;
-    GPTR(const float) F = gptr((const float*)v.F);
-    const size_t waves = (size_t)gridDim.x * (blockDim.x >> 6);
-    for (size_t b = (size_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); b < nbricks; b += waves) {
-        const uint64_t cm = v.cmask[b];
-        uint32_t n = 0;
-        if (cm) {
-            const int bz = (int)(b % v.bd[2]);
-            const size_t t = b / v.bd[2];
-            const int by = (int)(t % v.bd[1]), bx = (int)(t / v.bd[1]);
-            for (int zp = 0; zp < 4; ++zp) {
-                if (!cmask_pair(cm, zp)) continue;
-                for (int dz = 0; dz < 2; ++dz) {
-                    SurfVoxel S;
-                    surf_voxel(v, F, 8 * bx + lx, 8 * by + ly, 8 * bz + 2 * zp + dz, S);
-                    n += (uint32_t)__popcll(__ballot(S.emit));
-                }
-            }
-        }
-        if (lane == 0) counts[b] = n;
-    }
-}
-
-// Exclusive prefix sum of n counts by one block of 1024 threads (each takes
-// a contiguous run); total[0] = the sum.
-__global__ __launch_bounds__(1024) void mvf_extract_scan_kernel(const uint32_t* counts, size_t n,
-                                                                unsigned long long* offsets,
-                                                                long long* total)
-{
-    __shared__ unsigned long long part[1024];
-    const size_t per = (n + 1023) / 1024;
-    const size_t lo = min(n, (size_t)threadIdx.x * per), hi = min(n, lo + per);
-    unsigned long long s = 0;
-    for (size_t i = lo; i < hi; ++i) s += counts[i];
-    part[threadIdx.x] = s;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) x += (uint32_t)__shfl_xor((int)x, o);
+    __syncthreads();   // part may still be read
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = x;
     __syncthreads();
-    for (int d = 1; d < 1024; d <<= 1) {
-        const unsigned long long add = (int)threadIdx.x >= d ? part[threadIdx.x - d] : 0ull;
-        __syncthreads();
-        part[threadIdx.x] += add;
-        __syncthreads();
-    }
-    unsigned long long run = part[threadIdx.x] - s;
-    for (size_t i = lo; i < hi; ++i) {
-        offsets[i] = run;
-        run += counts[i];
-    }
-    if (threadIdx.x == 1023) total[0] = (long long)part[1023];
+    return part[0] + part[1] + part[2] + part[3];
 }
 
-__global__ __launch_bounds__(256) void mvf_extract_emit_kernel(DevVolume v, size_t nbricks,
-                                                               const unsigned long long* offsets, float* V, float* N,
+// Bricks with a set cell mask of each chunk; the super sums start at zero.
+__global__ __launch_bounds__(256) void mvf_extract_mark_kernel(DevVolume v, uint32_t nbricks, ExtractBuffers B)
+{
+    __shared__ uint32_t part[4];
+    uint32_t n = 0;
+#pragma unroll
+    for (int j = 0; j < kExtractChunk / 256; ++j) {
+        const uint32_t b = blockIdx.x * kExtractChunk + j * 256 + threadIdx.x;
+        n += b < nbricks && v.cmask[b] != 0ull ? 1u : 0u;
+    }
+    n = block_sum256(n, part);
+    if (threadIdx.x == 0) {
+        B.chunk_n[blockIdx.x] = n;
+        B.super_n[blockIdx.x] = 0;   // at most one super per chunk
+    }
+}
+
+// The bricks with a set cell mask, in brick order, and their number.
+__global__ __launch_bounds__(256) void mvf_extract_list_kernel(DevVolume v, uint32_t nbricks, ExtractBuffers B)
+{
+    __shared__ uint32_t part[4];
+    __shared__ uint32_t wave_n[kExtractChunk / 64];
+    const uint32_t mine = B.chunk_n[blockIdx.x];
+    if (mine == 0 && blockIdx.x + 1 < gridDim.x) return;
+    uint32_t before = 0;
+    for (uint32_t c = threadIdx.x; c < blockIdx.x; c += 256) before += B.chunk_n[c];
+    before = block_sum256(before, part);
+    if (blockIdx.x + 1 == gridDim.x && threadIdx.x == 0) *B.list_n = before + mine;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint64_t m[kExtractChunk / 256];
+#pragma unroll
+    for (int j = 0; j < kExtractChunk / 256; ++j) {
+        const uint32_t b = blockIdx.x * kExtractChunk + j * 256 + threadIdx.x;
+        m[j] = __ballot(b < nbricks && v.cmask[b] != 0ull);
+        if (lane == 0) wave_n[4 * j + wave] = (uint32_t)__popcll(m[j]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kExtractChunk / 256; ++j) {
+        uint32_t at = before;
+        for (int q = 0; q < 4 * j + wave; ++q) at += wave_n[q];
+        if ((m[j] >> lane) & 1ull)
+            B.list[at + (uint32_t)__popcll(m[j] & ((1ull << lane) - 1ull))] =
+                blockIdx.x * kExtractChunk + j * 256 + threadIdx.x;
+    }
+}
+
+// Brick coordinates of brick b (z fastest).
+static __device__ __forceinline__ void brick_coords(const DevVolume& v, uint32_t b, int& bx, int& by, int& bz)
+{
+    const uint32_t t = b / (uint32_t)v.bd[2];
+    bz = (int)(b - t * (uint32_t)v.bd[2]);
+    bx = (int)(t / (uint32_t)v.bd[1]);
+    by = (int)(t - (uint32_t)bx * (uint32_t)v.bd[1]);
+}
+
+// Points of every listed brick, per group and per super.
+__global__ __launch_bounds__(256) void mvf_extract_count_kernel(DevVolume v, ExtractBuffers B)
+{
+    __shared__ uint32_t wave_n[4];
+    const int lane = threadIdx.x & 63, wave = wave_uniform((int)(threadIdx.x >> 6));
+    const uint32_t nlist = *B.list_n;
+    for (uint32_t g = blockIdx.x; g * kExtractGroup < nlist; g += gridDim.x) {
+        uint32_t sum = 0;
+        for (int j = 0; j < kExtractGroup / 4; ++j) {
+            const uint32_t i = g * kExtractGroup + wave * (kExtractGroup / 4) + j;
+            if (i >= nlist) break;
+            const uint32_t b = (uint32_t)wave_uniform((int)B.list[i]);
+            const uint64_t cm = cptr(v.cmask)[b];
+            int bx, by, bz;
+            brick_coords(v, b, bx, by, bz);
+            float P[kBrick + 1][4];
+            load_brick_cells(v, bx, by, bz, lane, P);
+            uint32_t n = 0;
+#pragma unroll
+            for (int z = 0; z < kBrick; ++z) {
+                if (!cmask_pair(cm, z >> 1)) continue;
+                SurfVoxel S;
+                surf_voxel(v, 8 * bx + (lane & 7), 8 * by + (lane >> 3), 8 * bz + z, P[z], P[z + 1], S);
+                n += (uint32_t)__popcll(__ballot(S.emit));
+            }
+            if (lane == 0) B.counts[i] = n;
+            sum += n;
+        }
+        if (lane == 0) wave_n[wave] = sum;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            const uint32_t n = wave_n[0] + wave_n[1] + wave_n[2] + wave_n[3];
+            B.group_n[g] = n;
+            if (n) atomicAdd(&B.super_n[g / kExtractSuper], n);
+        }
+        __syncthreads();
+    }
+}
+
+// The number of points, to the host.  A launch of its own (one wavefront, 2 to
+// 4 us): counting blocks that fence and take a ticket, so that the last one
+// can sum, took the count from 15 to 46 us (a cache writeback per block).
+__global__ __launch_bounds__(64) void mvf_extract_total_kernel(ExtractBuffers B)
+{
+    const uint32_t nlist = *B.list_n;
+    const uint32_t nsuper = (nlist + kExtractGroup * kExtractSuper - 1) / (kExtractGroup * kExtractSuper);
+    unsigned long long t = 0;
+    for (uint32_t i = threadIdx.x; i < nsuper; i += 64) t += B.super_n[i];
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) t += __shfl_xor(t, o);
+    if (threadIdx.x == 0) *B.total = (long long)t;
+}
+
+__global__ __launch_bounds__(256) void mvf_extract_emit_kernel(DevVolume v, ExtractBuffers B, float* V, float* N,
                                                                int32_t* G, long long cap)
 {
-    const int lane = threadIdx.x & 63;
-    const int lx = lane & 7, ly = lane >> 3;
-    GPTR(const float) F = gptr((const float*)v.F);
+    __shared__ uint32_t part[4];
+    const int lane = threadIdx.x & 63, wave = wave_uniform((int)(threadIdx.x >> 6));
     const unsigned long long below = (1ull << lane) - 1ull;
-    const size_t waves = (size_t)gridDim.x * (blockDim.x >> 6);
-    for (size_t b = (size_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); b < nbricks; b += waves) {
-        const uint64_t cm = v.cmask[b];
-        if (!cm) continue;
-        unsigned long long base = offsets[b];
-        if ((long long)base >= cap) continue;
-        const int bz = (int)(b % v.bd[2]);
-        const size_t t = b / v.bd[2];
-        const int by = (int)(t % v.bd[1]), bx = (int)(t / v.bd[1]);
-        for (int zp = 0; zp < 4; ++zp) {
-            if (!cmask_pair(cm, zp)) continue;
-            for (int dz = 0; dz < 2; ++dz) {
-                const int gx = 8 * bx + lx, gy = 8 * by + ly, gz = 8 * bz + 2 * zp + dz;
+    const uint32_t nlist = *B.list_n;
+    for (uint32_t g = blockIdx.x; g * kExtractGroup < nlist; g += gridDim.x) {
+        const uint32_t sg = g / kExtractSuper;
+        uint32_t before = 0;
+        for (uint32_t i = threadIdx.x; i < sg; i += 256) before += B.super_n[i];
+        for (uint32_t i = sg * kExtractSuper + threadIdx.x; i < g; i += 256) before += B.group_n[i];
+        before = block_sum256(before, part);
+        // the group's bricks before this wavefront's first
+        const uint32_t i0 = g * kExtractGroup;
+        const uint32_t cnt = lane < kExtractGroup && i0 + lane < nlist ? B.counts[i0 + lane] : 0u;
+        unsigned long long base = before;
+        for (int q = 0; q < wave * (kExtractGroup / 4); ++q) base += (uint32_t)__shfl((int)cnt, q);
+        for (int j = 0; j < kExtractGroup / 4; ++j) {
+            const uint32_t i = i0 + wave * (kExtractGroup / 4) + j;
+            if (i >= nlist || (long long)base >= cap) break;
+            if (__shfl((int)cnt, wave * (kExtractGroup / 4) + j) == 0) continue;
+            const uint32_t b = (uint32_t)wave_uniform((int)B.list[i]);
+            const uint64_t cm = cptr(v.cmask)[b];
+            int bx, by, bz;
+            brick_coords(v, b, bx, by, bz);
+            float P[kBrick + 1][4];
+            load_brick_cells(v, bx, by, bz, lane, P);
+#pragma unroll
+            for (int z = 0; z < kBrick; ++z) {
+                if (!cmask_pair(cm, z >> 1)) continue;
+                const int gx = 8 * bx + (lane & 7), gy = 8 * by + (lane >> 3), gz = 8 * bz + z;
                 SurfVoxel S;
-                surf_voxel(v, F, gx, gy, gz, S);
+                surf_voxel(v, gx, gy, gz, P[z], P[z + 1], S);
                 const unsigned long long m = __ballot(S.emit);
                 const unsigned long long idx = base + (unsigned long long)__popcll(m & below);
                 base += (unsigned long long)__popcll(m);
                 if (!S.emit || (long long)idx >= cap) continue;
                 const float* c = S.c;
                 const int a = S.axis;
-                const float f0 = c[0], f1 = c[1 << a];
-                float fr[3] = { 0.0f, 0.0f, 0.0f };
-                fr[a] = f0 / (f0 - f1);
+                const float f0 = c[0], f1 = a == 0 ? c[1] : (a == 1 ? c[2] : c[4]);
+                const float fa = f0 / (f0 - f1);
+                const float fr[3] = { a == 0 ? fa : 0.0f, a == 1 ? fa : 0.0f, a == 2 ? fa : 0.0f };
                 // gradient of the trilinear interpolant at fr (local units)
                 const float c00 = lerp32(c[0], c[1], fr[0]), c10 = lerp32(c[2], c[3], fr[0]);
                 const float c01 = lerp32(c[4], c[5], fr[0]), c11 = lerp32(c[6], c[7], fr[0]);
@@ -2563,29 +2675,52 @@ __global__ __launch_bounds__(256) void mvf_extract_emit_kernel(DevVolume v, size
                 const float g2 = lerp32(c01, c11, fr[1]) - lerp32(c00, c10, fr[1]);
                 const float len = sqrtf((g0 * g0 + g1 * g1) + g2 * g2);
                 const float inv = len > 0.0f ? 1.0f / len : qnan();
-                const int g[3] = { v.off[0] + gx, v.off[1] + gy, v.off[2] + gz };
+                const int gg[3] = { v.off[0] + gx, v.off[1] + gy, v.off[2] + gz };
                 const float gr[3] = { g0, g1, g2 };
 #pragma unroll
                 for (int q = 0; q < 3; ++q) {
-                    V[3 * idx + q] = v.o[q] + v.s * (((float)g[q] + 0.5f) + fr[q]);
+                    V[3 * idx + q] = v.o[q] + v.s * (((float)gg[q] + 0.5f) + fr[q]);
                     N[3 * idx + q] = gr[q] * inv;
-                    if (G) G[3 * idx + q] = g[q];
+                    if (G) G[3 * idx + q] = gg[q];
                 }
             }
         }
     }
 }
 
-int launch_extract(DevVolume v, uint32_t* counts, unsigned long long* offsets, long long* total, float* V,
-                   float* N, int32_t* G, long long cap, void* stream)
+size_t extract_buffer_bytes(size_t nbricks)
+{
+    const size_t chunks = (nbricks + kExtractChunk - 1) / kExtractChunk;
+    return sizeof(uint32_t) * (2 * nbricks + (nbricks + kExtractGroup - 1) / kExtractGroup + 2 * chunks + 1);
+}
+
+ExtractBuffers extract_buffers(void* mem, size_t nbricks, long long* total)
+{
+    static_assert(kExtractGroup * kExtractSuper == kExtractChunk, "one super sum per chunk of a full list");
+    const size_t chunks = (nbricks + kExtractChunk - 1) / kExtractChunk;
+    ExtractBuffers B;
+    B.list = static_cast<uint32_t*>(mem);
+    B.counts = B.list + nbricks;
+    B.group_n = B.counts + nbricks;
+    B.chunk_n = B.group_n + (nbricks + kExtractGroup - 1) / kExtractGroup;
+    B.super_n = B.chunk_n + chunks;
+    B.list_n = B.super_n + chunks;
+    B.total = total;
+    return B;
+}
+
+int launch_extract(DevVolume v, const ExtractBuffers& B, float* V, float* N, int32_t* G, long long cap, void* stream)
 {
     hipStream_t s = (hipStream_t)stream;
-    const size_t nb = (size_t)v.bd[0] * v.bd[1] * v.bd[2];
-    const unsigned blocks = (unsigned)std::min<size_t>(65536, (nb + 3) / 4);
-    hipLaunchKernelGGL(mvf_extract_count_kernel, dim3(blocks), dim3(256), 0, s, v, nb, counts);
-    hipLaunchKernelGGL(mvf_extract_scan_kernel, dim3(1), dim3(1024), 0, s, counts, nb, offsets, total);
+    const uint32_t nb = (uint32_t)v.bd[0] * (uint32_t)v.bd[1] * (uint32_t)v.bd[2];
+    const unsigned chunks = (nb + kExtractChunk - 1) / kExtractChunk;
+    const unsigned blocks = std::min<unsigned>(kExtractBlocks, (nb + kExtractGroup - 1) / kExtractGroup);
+    hipLaunchKernelGGL(mvf_extract_mark_kernel, dim3(chunks), dim3(256), 0, s, v, nb, B);
+    hipLaunchKernelGGL(mvf_extract_list_kernel, dim3(chunks), dim3(256), 0, s, v, nb, B);
+    hipLaunchKernelGGL(mvf_extract_count_kernel, dim3(blocks), dim3(256), 0, s, v, B);
+    hipLaunchKernelGGL(mvf_extract_total_kernel, dim3(1), dim3(64), 0, s, B);
     if (cap > 0)
-        hipLaunchKernelGGL(mvf_extract_emit_kernel, dim3(blocks), dim3(256), 0, s, v, nb, offsets, V, N, G, cap);
+        hipLaunchKernelGGL(mvf_extract_emit_kernel, dim3(blocks), dim3(256), 0, s, v, B, V, N, G, cap);
     return (int)hipGetLastError();
 }
 

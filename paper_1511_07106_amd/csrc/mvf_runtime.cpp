@@ -273,7 +273,8 @@ struct mvf_ctx {
         size_t bytes = 0;
         TrackState* host = nullptr;
     } track;
-    uint8_t* extract_buf = nullptr;   // surface points: per-brick counts (4 B), offsets (8 B), total (8 B)
+    uint8_t* extract_buf = nullptr;   // surface points: scratch (extract_buffer_bytes)
+    long long* extract_total = nullptr;  // pinned
     size_t extract_buf_n = 0;         // nbricks it holds
     StepGraph step;
     hipStream_t capture_stream = nullptr;
@@ -1528,6 +1529,7 @@ mvf_status mvf_destroy(mvf_ctx* c)
     if (c->place_cells) (void)hipHostFree(c->place_cells);
     if (c->diff_partials) (void)hipFree(c->diff_partials);
     if (c->extract_buf) (void)hipFree(c->extract_buf);
+    if (c->extract_total) (void)hipHostFree(c->extract_total);
     if (c->track.dev) (void)hipFree(c->track.dev);
     if (c->track.host) (void)hipHostFree(c->track.host);
     if (c->tail) (void)hipEventDestroy(c->tail);
@@ -1737,22 +1739,20 @@ mvf_status mvf_volume_extract(mvf_ctx* c, int32_t id, float* V, float* N, int32_
             c->extract_buf = nullptr;
             c->extract_buf_n = 0;
         }
-        if (hipMalloc((void**)&c->extract_buf, align_up(4 * nb, kAlign) + 8 * nb + 8) != hipSuccess) {
+        if (hipMalloc((void**)&c->extract_buf, extract_buffer_bytes(nb)) != hipSuccess) {
             (void)hipGetLastError();
             c->extract_buf = nullptr;
             return set_error(MVF_ERR_OOM, "surface extraction scratch of %zu bricks", nb);
         }
         c->extract_buf_n = nb;
     }
-    uint32_t* counts = reinterpret_cast<uint32_t*>(c->extract_buf);
-    unsigned long long* offsets = reinterpret_cast<unsigned long long*>(c->extract_buf + align_up(4 * nb, kAlign));
-    long long* total = reinterpret_cast<long long*>(offsets + nb);
-    DevVolume dv = make_dev(c, *v);
-    CHECK_LAUNCH(launch_extract(dv, counts, offsets, total, V, N, G, (long long)cap, s));
-    long long n = 0;
-    CHECK_HIP(hipMemcpyAsync(&n, total, sizeof(n), hipMemcpyDeviceToHost, s));
+    if (!c->extract_total)
+        CHECK_HIP(hipHostMalloc((void**)&c->extract_total, sizeof(long long), hipHostMallocDefault));
+    *c->extract_total = 0;
+    const ExtractBuffers B = extract_buffers(c->extract_buf, nb, c->extract_total);
+    CHECK_LAUNCH(launch_extract(make_dev(c, *v), B, V, N, G, (long long)cap, s));
     CHECK_HIP(hipStreamSynchronize(s));
-    *n_total = (int64_t)n;
+    *n_total = (int64_t)*c->extract_total;
     return mark_tail(c, s);
 }
 

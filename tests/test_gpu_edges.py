@@ -61,3 +61,50 @@ def test_placement_counts_after_overflow(mvf):
             with pytest.raises(mvf._lib.MvfError):
                 ctx.placement_count(t(d), POSE, K, gid, 3, max_cells=16384)
             assert ctx.placement_count(t(d), POSE, K, gid, 500) == O.placement_counts(d, K, POSE, og, 500)
+
+
+@pytest.mark.parametrize("dims,share", [((2, 2, 2), 1.0), ((8, 8, 8), 1.0), ((9, 17, 8), 1.0), ((8, 8, 1100), 0.1),
+                                        ((72, 80, 96), 1.0), ((40, 33, 130), 0.02)])
+def test_surface_points_edges(mvf, dims, share):
+    """One brick, a brick and a voxel, a column of more than 128 bricks, more
+    surface bricks than one group, one chunk and one sum of sums hold: points
+    of random values in a share of the bricks, against the oracle on the same
+    values (emitting voxels equal; positions within 1e-4 m and normals within
+    2e-3, the bounds of the room tests)."""
+    log(f"surface points {dims} share {share}")
+    rng = np.random.default_rng(dims[0] + 7 * dims[2])
+    nx, ny, nz = dims
+    F = rng.uniform(0.05, 0.95, (nz, ny, nx)).astype(np.float32)
+    bricks = rng.random([(n + 7) // 8 for n in (nz, ny, nx)]) < share
+    neg = np.kron(bricks, np.ones((8, 8, 8), bool))[:nz, :ny, :nx] & (rng.random(F.shape) < 0.3)
+    F[neg] *= -1.0
+    W = np.where(rng.random(F.shape) < 0.002, 0, 7).astype(np.uint16)
+    F[W == 0] = 0.0
+    og = O.OGrid((-0.3, 0.1, 0.2), 0.02, 4.0, 128)
+    with mvf.Context() as ctx:
+        gid = ctx.grid((-0.3, 0.1, 0.2), 0.02)
+        vid = ctx.volume(gid, (3, -5, 11), dims)
+        ctx.write_volume(vid, F, W, np.zeros(F.shape + (4,), np.uint8))
+        ov = O.OVolume(dims, (3, -5, 11), F.astype(np.float64), W, np.zeros(W.shape + (4,), np.uint8))
+        ref = O.extract(ov, og, F32=F)
+        got = {k: v.cpu().numpy() if hasattr(v, "cpu") else v for k, v in ctx.extract(vid).items()}
+    assert got["n"] == ref["n"]
+
+    def by_voxel(G, *arrs):
+        order = np.lexsort((G[:, 0], G[:, 1], G[:, 2]))
+        return [G[order]] + [a[order] for a in arrs]
+
+    # the device writes bricks z fastest, then slices, then x fastest
+    l = got["G"].astype(np.int64) - (3, -5, 11)
+    bd = [(n + 7) // 8 for n in dims]
+    key = (((l[:, 0] >> 3) * bd[1] + (l[:, 1] >> 3)) * bd[2] + (l[:, 2] >> 3)) * 512 + (l[:, 2] & 7) * 64 + \
+        (l[:, 1] & 7) * 8 + (l[:, 0] & 7)
+    assert np.all(np.diff(key) > 0)
+    Gd, Vd, Nd = by_voxel(got["G"], got["V"].astype(np.float64), got["N"].astype(np.float64))
+    Go, Vo, No = by_voxel(ref["G"], ref["V"], ref["N"])
+    np.testing.assert_array_equal(Gd, Go)
+    if got["n"]:
+        assert np.abs(Vd - Vo).max() <= 1e-4
+        ok = np.isfinite(No).all(axis=1)
+        assert np.array_equal(ok, np.isfinite(Nd).all(axis=1))
+        assert not ok.any() or np.abs(Nd[ok] - No[ok]).max() <= 2e-3
