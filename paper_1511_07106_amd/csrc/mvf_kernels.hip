@@ -2449,6 +2449,11 @@ constexpr int kExtractGroup = 16;              // bricks per group: four wavefro
 constexpr int kExtractSuper = 64;              // groups per super sum
 constexpr int kExtractChunk = 1024;            // bricks per listing block
 constexpr int kExtractBlocks = 2048;           // most blocks of the counting and the emission
+// Volumes of at most this many bricks take every brick as listed: the two
+// listing launches cost more than the skipped bricks' masks.  Count and
+// emission with / without the listing, cubes of 343, 3375, 15625, 21952, 32768
+// and 64000 bricks: 119/88, 122/101, 126/114, 125/121, 128/127, 129/151 us.
+constexpr uint32_t kExtractDirect = 24576;
 
 // The values a brick's cells read: lane (lx, ly) holds, for each of the
 // planes z = 0 .. 8, the voxels (x, y), (x + 1, y), (x, y + 1), (x + 1, y + 1).
@@ -2570,19 +2575,25 @@ static __device__ __forceinline__ void brick_coords(const DevVolume& v, uint32_t
     by = (int)(t - (uint32_t)bx * (uint32_t)v.bd[1]);
 }
 
-// Points of every listed brick, per group and per super.
-__global__ __launch_bounds__(256) void mvf_extract_count_kernel(DevVolume v, ExtractBuffers B)
+// Points of every listed brick, per group and per super.  Direct: every brick
+// is listed, and there are no super sums.
+template <bool Direct>
+__global__ __launch_bounds__(256) void mvf_extract_count_kernel(DevVolume v, ExtractBuffers B, uint32_t nbricks)
 {
     __shared__ uint32_t wave_n[4];
     const int lane = threadIdx.x & 63, wave = wave_uniform((int)(threadIdx.x >> 6));
-    const uint32_t nlist = *B.list_n;
+    const uint32_t nlist = Direct ? nbricks : *B.list_n;
     for (uint32_t g = blockIdx.x; g * kExtractGroup < nlist; g += gridDim.x) {
         uint32_t sum = 0;
         for (int j = 0; j < kExtractGroup / 4; ++j) {
             const uint32_t i = g * kExtractGroup + wave * (kExtractGroup / 4) + j;
             if (i >= nlist) break;
-            const uint32_t b = (uint32_t)wave_uniform((int)B.list[i]);
+            const uint32_t b = Direct ? i : (uint32_t)wave_uniform((int)B.list[i]);
             const uint64_t cm = cptr(v.cmask)[b];
+            if (Direct && cm == 0ull) {
+                if (lane == 0) B.counts[i] = 0;
+                continue;
+            }
             int bx, by, bz;
             brick_coords(v, b, bx, by, bz);
             float P[kBrick + 1][4];
@@ -2603,7 +2614,7 @@ __global__ __launch_bounds__(256) void mvf_extract_count_kernel(DevVolume v, Ext
         if (threadIdx.x == 0) {
             const uint32_t n = wave_n[0] + wave_n[1] + wave_n[2] + wave_n[3];
             B.group_n[g] = n;
-            if (n) atomicAdd(&B.super_n[g / kExtractSuper], n);
+            if (!Direct && n) atomicAdd(&B.super_n[g / kExtractSuper], n);
         }
         __syncthreads();
     }
@@ -2612,26 +2623,29 @@ __global__ __launch_bounds__(256) void mvf_extract_count_kernel(DevVolume v, Ext
 // The number of points, to the host.  A launch of its own (one wavefront, 2 to
 // 4 us): counting blocks that fence and take a ticket, so that the last one
 // can sum, took the count from 15 to 46 us (a cache writeback per block).
-__global__ __launch_bounds__(64) void mvf_extract_total_kernel(ExtractBuffers B)
+template <bool Direct>
+__global__ __launch_bounds__(64) void mvf_extract_total_kernel(ExtractBuffers B, uint32_t nbricks)
 {
-    const uint32_t nlist = *B.list_n;
-    const uint32_t nsuper = (nlist + kExtractGroup * kExtractSuper - 1) / (kExtractGroup * kExtractSuper);
+    const uint32_t per = Direct ? kExtractGroup : kExtractGroup * kExtractSuper;
+    const uint32_t n = ((Direct ? nbricks : *B.list_n) + per - 1) / per;
+    const uint32_t* sums = Direct ? B.group_n : B.super_n;
     unsigned long long t = 0;
-    for (uint32_t i = threadIdx.x; i < nsuper; i += 64) t += B.super_n[i];
+    for (uint32_t i = threadIdx.x; i < n; i += 64) t += sums[i];
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) t += __shfl_xor(t, o);
     if (threadIdx.x == 0) *B.total = (long long)t;
 }
 
-__global__ __launch_bounds__(256) void mvf_extract_emit_kernel(DevVolume v, ExtractBuffers B, float* V, float* N,
-                                                               int32_t* G, long long cap)
+template <bool Direct>
+__global__ __launch_bounds__(256) void mvf_extract_emit_kernel(DevVolume v, ExtractBuffers B, uint32_t nbricks, float* V,
+                                                               float* N, int32_t* G, long long cap)
 {
     __shared__ uint32_t part[4];
     const int lane = threadIdx.x & 63, wave = wave_uniform((int)(threadIdx.x >> 6));
     const unsigned long long below = (1ull << lane) - 1ull;
-    const uint32_t nlist = *B.list_n;
+    const uint32_t nlist = Direct ? nbricks : *B.list_n;
     for (uint32_t g = blockIdx.x; g * kExtractGroup < nlist; g += gridDim.x) {
-        const uint32_t sg = g / kExtractSuper;
+        const uint32_t sg = Direct ? 0 : g / kExtractSuper;
         uint32_t before = 0;
         for (uint32_t i = threadIdx.x; i < sg; i += 256) before += B.super_n[i];
         for (uint32_t i = sg * kExtractSuper + threadIdx.x; i < g; i += 256) before += B.group_n[i];
@@ -2645,7 +2659,7 @@ __global__ __launch_bounds__(256) void mvf_extract_emit_kernel(DevVolume v, Extr
             const uint32_t i = i0 + wave * (kExtractGroup / 4) + j;
             if (i >= nlist || (long long)base >= cap) break;
             if (__shfl((int)cnt, wave * (kExtractGroup / 4) + j) == 0) continue;
-            const uint32_t b = (uint32_t)wave_uniform((int)B.list[i]);
+            const uint32_t b = Direct ? i : (uint32_t)wave_uniform((int)B.list[i]);
             const uint64_t cm = cptr(v.cmask)[b];
             int bx, by, bz;
             brick_coords(v, b, bx, by, bz);
@@ -2709,18 +2723,29 @@ ExtractBuffers extract_buffers(void* mem, size_t nbricks, long long* total)
     return B;
 }
 
+template <bool Direct>
+static void launch_extract_points(DevVolume v, const ExtractBuffers& B, uint32_t nb, float* V, float* N, int32_t* G,
+                                  long long cap, hipStream_t s)
+{
+    const unsigned blocks = std::min<unsigned>(kExtractBlocks, (nb + kExtractGroup - 1) / kExtractGroup);
+    hipLaunchKernelGGL(mvf_extract_count_kernel<Direct>, dim3(blocks), dim3(256), 0, s, v, B, nb);
+    hipLaunchKernelGGL(mvf_extract_total_kernel<Direct>, dim3(1), dim3(64), 0, s, B, nb);
+    if (cap > 0)
+        hipLaunchKernelGGL(mvf_extract_emit_kernel<Direct>, dim3(blocks), dim3(256), 0, s, v, B, nb, V, N, G, cap);
+}
+
 int launch_extract(DevVolume v, const ExtractBuffers& B, float* V, float* N, int32_t* G, long long cap, void* stream)
 {
     hipStream_t s = (hipStream_t)stream;
     const uint32_t nb = (uint32_t)v.bd[0] * (uint32_t)v.bd[1] * (uint32_t)v.bd[2];
-    const unsigned chunks = (nb + kExtractChunk - 1) / kExtractChunk;
-    const unsigned blocks = std::min<unsigned>(kExtractBlocks, (nb + kExtractGroup - 1) / kExtractGroup);
-    hipLaunchKernelGGL(mvf_extract_mark_kernel, dim3(chunks), dim3(256), 0, s, v, nb, B);
-    hipLaunchKernelGGL(mvf_extract_list_kernel, dim3(chunks), dim3(256), 0, s, v, nb, B);
-    hipLaunchKernelGGL(mvf_extract_count_kernel, dim3(blocks), dim3(256), 0, s, v, B);
-    hipLaunchKernelGGL(mvf_extract_total_kernel, dim3(1), dim3(64), 0, s, B);
-    if (cap > 0)
-        hipLaunchKernelGGL(mvf_extract_emit_kernel, dim3(blocks), dim3(256), 0, s, v, B, V, N, G, cap);
+    if (nb <= kExtractDirect) {
+        launch_extract_points<true>(v, B, nb, V, N, G, cap, s);
+    } else {
+        const unsigned chunks = (nb + kExtractChunk - 1) / kExtractChunk;
+        hipLaunchKernelGGL(mvf_extract_mark_kernel, dim3(chunks), dim3(256), 0, s, v, nb, B);
+        hipLaunchKernelGGL(mvf_extract_list_kernel, dim3(chunks), dim3(256), 0, s, v, nb, B);
+        launch_extract_points<false>(v, B, nb, V, N, G, cap, s);
+    }
     return (int)hipGetLastError();
 }
 
