@@ -345,6 +345,7 @@ struct TrackState {
     double T[12];        // estimate, camera-to-world, row-major 3x4
     float T32[12];       // its binary32 rounding (the association reads it)
     int32_t steps;
+    uint32_t ticket;     // blocks of the running step that have finished
     int32_t pairs[kTrackMaxSteps];
     double sq_err[kTrackMaxSteps];
 };
@@ -360,18 +361,38 @@ struct TrackLaunch {
     float eps_d, cos_theta;
     TrackState* state;
     double* partials;    // track_blocks(w, h) x kTrackSums
-    uint8_t* inlier;     // per current pixel, or null
+};
+
+// The maps of one pyramid level: depth in, vertex and normal maps out; for
+// levels >= 1 also the subsampled model maps out.
+struct TrackMapLevel {
+    const float* D;
+    int32_t pitch, w, h;
+    float fx, fy, cx, cy;
+    float* V;
+    float* N;
+    float* Vm;
+    float* Nm;
+};
+constexpr int kTrackMapsMax = 5;
+struct TrackMaps {
+    TrackMapLevel level[3];
+    int32_t levels;
+    int32_t first[kTrackMapsMax];  // first block of each map (set by launch_track_maps)
+    const float* Vm;     // full-size model maps, or null (no model)
+    const float* Nm;
+    TrackState* state;   // set up for a call that starts from T, or null
+    double T[12];
 };
 
 // Edge-preserving smoothing of a depth map (out: w x h, pitch w).
 int launch_track_smooth(const float* D, int pitch, int w, int h, float delta, float* out, void* stream);
 int launch_track_down(const float* D, int pitch, int w, int h, float tau, float* D2, void* stream);
-int launch_track_vn(const float* D, int pitch, int w, int h, const float K[4], float* V, float* N, void* stream);
-int launch_track_model_down(const float* V, const float* N, int w, int h, float* V2, float* N2, void* stream);
+int launch_track_maps(TrackMaps M, void* stream);
 int track_blocks(int w, int h);
-// Association + reduction, then the solve and update of step `step`.
-int launch_icp_step(const TrackLaunch& L, TrackState* state, int step, void* stream);
-int launch_track_init(TrackState* state, void* stream);
+// Step `step`: association, reduction, solve and update; with `out` (pinned
+// host memory) also the call's result.
+int launch_icp_step(const TrackLaunch& L, int step, TrackState* out, void* stream);
 
 struct DiffVolume {
     const float* F;

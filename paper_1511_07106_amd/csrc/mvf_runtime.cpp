@@ -141,7 +141,7 @@ struct Arena {
     static constexpr int kSlots = 32;
     static constexpr int kBatch = 4;
     static constexpr size_t kSlotBytes = 1 << 20;
-    uint8_t* host = nullptr;
+    uint8_t* host = nullptr;           // kSlots slots, then the mailbox
     uint8_t* dev = nullptr;
     hipEvent_t ev[kSlots] = {};
     hipEvent_t wait_ev[kSlots] = {};   // the event a pending slot waits on before reuse
@@ -150,6 +150,14 @@ struct Arena {
     int open[kBatch] = {};             // step slots released since the last record
     int n_open = 0;
     hipStream_t open_stream = nullptr;
+};
+
+// Pinned memory behind the arena's slots in which the synchronising calls'
+// last kernels leave their results.
+struct Mailbox {
+    long long points;       // surface points
+    TrackState track;
+    PlacementCells cells;
 };
 
 struct Writer {
@@ -227,6 +235,7 @@ struct mvf_ctx {
     int fault_slab_allocs = 0;
     mvf_stats stats{};
     Arena arena;
+    Mailbox* mail = nullptr;       // in the arena's pinned memory
     std::vector<TimedPair> timed;
     std::vector<hipEvent_t> event_pool;
     hipEvent_t tail = nullptr;     // recorded by mark_tail
@@ -252,7 +261,6 @@ struct mvf_ctx {
     std::map<int, std::map<std::vector<int>, int>> placed;
     unsigned long long* place_table = nullptr;
     int* place_overflow = nullptr;
-    PlacementCells* place_cells = nullptr;  // pinned: what the last count found
     bool place_clean = false;               // the table is empty (every finished count leaves it so)
     double* diff_partials = nullptr;
     int diff_partials_n = 0;
@@ -266,15 +274,12 @@ struct mvf_ctx {
         float o[3] = {0, 0, 0}, s = 0.0f;
         uint64_t generation = 0;
     } diff_mirror;
-    // camera tracking: pyramid maps, partials and the device state, plus a
-    // pinned copy of the state for the result
+    // camera tracking: pyramid maps, partials and the device state
     struct TrackScratch {
         uint8_t* dev = nullptr;
         size_t bytes = 0;
-        TrackState* host = nullptr;
     } track;
     uint8_t* extract_buf = nullptr;   // surface points: scratch (extract_buffer_bytes)
-    long long* extract_total = nullptr;  // pinned
     size_t extract_buf_n = 0;         // nbricks it holds
     StepGraph step;
     hipStream_t capture_stream = nullptr;
@@ -1457,10 +1462,12 @@ mvf_status mvf_create(mvf_ctx** out, const mvf_config* cfg)
         (e = hipStreamCreateWithFlags(&c->capture_stream, hipStreamNonBlocking)) != hipSuccess ||
         (e = hipMalloc((void**)&c->counters, sizeof(unsigned long long) * kCntNum * kCntSlots)) != hipSuccess ||
         (e = hipMemset(c->counters, 0, sizeof(unsigned long long) * kCntNum * kCntSlots)) != hipSuccess ||
-        (e = hipHostMalloc((void**)&c->arena.host, Arena::kSlots * Arena::kSlotBytes, hipHostMallocDefault)) != hipSuccess ||
+        (e = hipHostMalloc((void**)&c->arena.host, Arena::kSlots * Arena::kSlotBytes + sizeof(Mailbox),
+                            hipHostMallocDefault)) != hipSuccess ||
         (e = hipMalloc((void**)&c->arena.dev, Arena::kSlots * Arena::kSlotBytes)) != hipSuccess ||
         (e = hipEventCreateWithFlags(&c->tail, hipEventDisableTiming | hipEventDisableSystemFence)) != hipSuccess)
         return fail(set_error(MVF_ERR_HIP, "context setup: %s", hipGetErrorString(e)));
+    c->mail = reinterpret_cast<Mailbox*>(c->arena.host + Arena::kSlots * Arena::kSlotBytes);
     for (int i = 0; i < Arena::kSlots; ++i)
         // the host waits on these before rewriting a slot the device has read
         if ((e = hipEventCreateWithFlags(&c->arena.ev[i], hipEventDisableTiming | hipEventDisableSystemFence)) !=
@@ -1526,12 +1533,9 @@ mvf_status mvf_destroy(mvf_ctx* c)
     if (c->counters) (void)hipFree(c->counters);
     if (c->place_table) (void)hipFree(c->place_table);
     if (c->place_overflow) (void)hipFree(c->place_overflow);
-    if (c->place_cells) (void)hipHostFree(c->place_cells);
     if (c->diff_partials) (void)hipFree(c->diff_partials);
     if (c->extract_buf) (void)hipFree(c->extract_buf);
-    if (c->extract_total) (void)hipHostFree(c->extract_total);
     if (c->track.dev) (void)hipFree(c->track.dev);
-    if (c->track.host) (void)hipHostFree(c->track.host);
     if (c->tail) (void)hipEventDestroy(c->tail);
     if (c->d2h_stream) (void)hipStreamDestroy(c->d2h_stream);
     if (c->h2d_stream) (void)hipStreamDestroy(c->h2d_stream);
@@ -1746,13 +1750,11 @@ mvf_status mvf_volume_extract(mvf_ctx* c, int32_t id, float* V, float* N, int32_
         }
         c->extract_buf_n = nb;
     }
-    if (!c->extract_total)
-        CHECK_HIP(hipHostMalloc((void**)&c->extract_total, sizeof(long long), hipHostMallocDefault));
-    *c->extract_total = 0;
-    const ExtractBuffers B = extract_buffers(c->extract_buf, nb, c->extract_total);
+    c->mail->points = 0;
+    const ExtractBuffers B = extract_buffers(c->extract_buf, nb, &c->mail->points);
     CHECK_LAUNCH(launch_extract(make_dev(c, *v), B, V, N, G, (long long)cap, s));
     CHECK_HIP(hipStreamSynchronize(s));
-    *n_total = (int64_t)*c->extract_total;
+    *n_total = (int64_t)c->mail->points;
     return mark_tail(c, s);
 }
 
@@ -2354,7 +2356,6 @@ static mvf_status placement_count_impl(mvf_ctx* c, const mvf_frame* f, const flo
     if (n_boxes > kMaxPlaceBoxes) return set_error(MVF_ERR_INVALID_ARG, "too many placement boxes");
     if (!c->place_table) CHECK_HIP(hipMalloc((void**)&c->place_table, sizeof(unsigned long long) * 2 * kPlaceTable));
     if (!c->place_overflow) CHECK_HIP(hipMalloc((void**)&c->place_overflow, 256));
-    if (!c->place_cells) CHECK_HIP(hipHostMalloc((void**)&c->place_cells, sizeof(PlacementCells), hipHostMallocDefault));
     if (!c->place_clean) CHECK_LAUNCH(launch_placement_clear(c->place_table, kPlaceTable, c->place_overflow, s));
     c->place_clean = false;
     PlacementCount P{};
@@ -2372,10 +2373,10 @@ static mvf_status placement_count_impl(mvf_ctx* c, const mvf_frame* f, const flo
     P.n_boxes = n_boxes;
     P.overflow = c->place_overflow;
     if (n_boxes) memcpy(P.boxes, boxes.data(), sizeof(int32_t) * boxes.size());
-    CHECK_LAUNCH(launch_placement_count(P, c->place_cells, s));
+    CHECK_LAUNCH(launch_placement_count(P, &c->mail->cells, s));
     CHECK_HIP(hipStreamSynchronize(s));
     c->place_clean = true;
-    const PlacementCells& found = *c->place_cells;
+    const PlacementCells& found = c->mail->cells;
     if (found.overflow & 1) return set_error(MVF_ERR_STATE, "more than %d distinct placement cells", kPlaceTable);
     if (found.overflow & 2) return set_error(MVF_ERR_INVALID_ARG, "placement cell index out of range");
     out->clear();
@@ -2741,8 +2742,11 @@ mvf_status mvf_depth_maps(mvf_ctx* c, const mvf_frame* f, const mvf_intrinsics* 
     }
     if (st == MVF_OK) {
         const float sc = std::ldexp(1.0f, -level);
-        const float Kl[4] = { K->fx * sc, K->fy * sc, (K->cx + 0.5f) * sc - 0.5f, (K->cy + 0.5f) * sc - 0.5f };
-        const int le = launch_track_vn(D, pitch, w, h, Kl, V, N, s);
+        TrackMaps M{};
+        M.levels = 1;
+        M.level[0] = TrackMapLevel{D, pitch, w, h, K->fx * sc, K->fy * sc, (K->cx + 0.5f) * sc - 0.5f,
+                                   (K->cy + 0.5f) * sc - 0.5f, V, N, nullptr, nullptr};
+        const int le = launch_track_maps(M, s);
         if (le) st = set_error(MVF_ERR_HIP, "launch: %s", hipGetErrorString((hipError_t)le));
     }
     if (tmp[0] || tmp[1] || tmp[2]) {
@@ -2823,17 +2827,21 @@ mvf_status mvf_track(mvf_ctx* c, const mvf_frame* f, const mvf_intrinsics* K, co
         }
         tk.bytes = off;
     }
-    if (!tk.host) CHECK_HIP(hipHostMalloc((void**)&tk.host, sizeof(TrackState), hipHostMallocDefault));
     uint8_t* B = tk.dev;
     TrackState* dstate = reinterpret_cast<TrackState*>(B + o_state);
     double* partials = reinterpret_cast<double*>(B + o_part);
-    for (int i = 0; i < 12; ++i) tk.host->T[i] = T_init[i];
-    CHECK_HIP(hipMemcpyAsync(dstate->T, tk.host->T, sizeof(double) * 12, hipMemcpyHostToDevice, s));
-    CHECK_LAUNCH(launch_track_init(dstate, s));
+    // a call without steps returns the estimate it was given
+    for (int i = 0; i < 12; ++i) c->mail->track.T[i] = T_init[i];
+    c->mail->track.steps = 0;
+    TrackMaps M{};
+    M.levels = p->levels;
+    M.Vm = m->vertex;
+    M.Nm = m->normal;
+    M.state = dstate;
+    for (int i = 0; i < 12; ++i) M.T[i] = T_init[i];
     // pyramid and maps
     const float* D[3];
     int pitch[3];
-    float Kl[3][4];
     D[0] = f->depth;
     pitch[0] = f->depth_pitch ? f->depth_pitch : f->width;
     if (p->smooth > 0.0f) {
@@ -2851,57 +2859,46 @@ mvf_status mvf_track(mvf_ctx* c, const mvf_frame* f, const mvf_intrinsics* K, co
         }
         // f / 2^l and (c + 1/2) / 2^l - 1/2 in binary32
         const float sc = std::ldexp(1.0f, -l);
-        Kl[l][0] = K->fx * sc;
-        Kl[l][1] = K->fy * sc;
-        Kl[l][2] = (K->cx + 0.5f) * sc - 0.5f;
-        Kl[l][3] = (K->cy + 0.5f) * sc - 0.5f;
-        CHECK_LAUNCH(launch_track_vn(D[l], pitch[l], w[l], h[l], Kl[l], reinterpret_cast<float*>(B + o_v[l]),
-                                     reinterpret_cast<float*>(B + o_n[l]), s));
+        float* vm = l ? reinterpret_cast<float*>(B + o_vm[l]) : nullptr;
+        float* nm = l ? reinterpret_cast<float*>(B + o_nm[l]) : nullptr;
+        M.level[l] = TrackMapLevel{D[l], pitch[l], w[l], h[l], K->fx * sc, K->fy * sc, (K->cx + 0.5f) * sc - 0.5f,
+                                   (K->cy + 0.5f) * sc - 0.5f, reinterpret_cast<float*>(B + o_v[l]),
+                                   reinterpret_cast<float*>(B + o_n[l]), vm, nm};
     }
-    const float* Vm[3];
-    const float* Nm[3];
-    Vm[0] = m->vertex;
-    Nm[0] = m->normal;
-    for (int l = 1; l < p->levels; ++l) {
-        float* v2 = reinterpret_cast<float*>(B + o_vm[l]);
-        float* n2 = reinterpret_cast<float*>(B + o_nm[l]);
-        CHECK_LAUNCH(launch_track_model_down(Vm[l - 1], Nm[l - 1], w[l - 1], h[l - 1], v2, n2, s));
-        Vm[l] = v2;
-        Nm[l] = n2;
-    }
+    CHECK_LAUNCH(launch_track_maps(M, s));
     // coarse to fine
     int step = 0;
     for (int l = p->levels - 1; l >= 0; --l) {
         for (int it = 0; it < p->iters[l]; ++it) {
             TrackLaunch L{};
-            L.V = reinterpret_cast<const float*>(B + o_v[l]);
-            L.N = reinterpret_cast<const float*>(B + o_n[l]);
+            L.V = M.level[l].V;
+            L.N = M.level[l].N;
             L.w = w[l];
             L.h = h[l];
-            L.Vm = Vm[l];
-            L.Nm = Nm[l];
-            L.fx = Kl[l][0];
-            L.fy = Kl[l][1];
-            L.cx = Kl[l][2];
-            L.cy = Kl[l][3];
+            L.Vm = l ? M.level[l].Vm : m->vertex;
+            L.Nm = l ? M.level[l].Nm : m->normal;
+            L.fx = M.level[l].fx;
+            L.fy = M.level[l].fy;
+            L.cx = M.level[l].cx;
+            L.cy = M.level[l].cy;
             for (int i = 0; i < 12; ++i) L.Tm[i] = m->T_wc[i];
             L.eps_d = p->eps_d;
             L.cos_theta = p->cos_theta;
             L.state = dstate;
             L.partials = partials;
-            L.inlier = nullptr;
-            CHECK_LAUNCH(launch_icp_step(L, dstate, step++, s));
+            // the last step writes the result to the pinned copy
+            CHECK_LAUNCH(launch_icp_step(L, step, step + 1 == nsteps ? &c->mail->track : nullptr, s));
+            ++step;
         }
     }
-    CHECK_HIP(hipMemcpyAsync(tk.host, dstate, sizeof(TrackState), hipMemcpyDeviceToHost, s));
     CHECK_HIP(hipStreamSynchronize(s));
-    for (int i = 0; i < 12; ++i) T_out[i] = tk.host->T[i];
+    for (int i = 0; i < 12; ++i) T_out[i] = c->mail->track.T[i];
     if (st) {
         memset(st, 0, sizeof(*st));
-        st->steps = tk.host->steps;
-        for (int i = 0; i < tk.host->steps && i < kTrackMaxSteps; ++i) {
-            st->pairs[i] = tk.host->pairs[i];
-            st->sq_err[i] = tk.host->sq_err[i];
+        st->steps = c->mail->track.steps;
+        for (int i = 0; i < c->mail->track.steps && i < kTrackMaxSteps; ++i) {
+            st->pairs[i] = c->mail->track.pairs[i];
+            st->sq_err[i] = c->mail->track.sq_err[i];
         }
     }
     return mark_tail(c, s);

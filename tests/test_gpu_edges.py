@@ -64,10 +64,12 @@ def test_placement_counts_after_overflow(mvf):
 
 
 @pytest.mark.parametrize("dims,share", [((2, 2, 2), 1.0), ((8, 8, 8), 1.0), ((9, 17, 8), 1.0), ((8, 8, 1100), 0.1),
-                                        ((72, 80, 96), 1.0), ((40, 33, 130), 0.02)])
+                                        ((72, 80, 96), 1.0), ((40, 33, 130), 0.02), ((208, 200, 204), 0.15),
+                                        ((200, 207, 211), 0.0003)])
 def test_surface_points_edges(mvf, dims, share):
     """One brick, a brick and a voxel, a column of more than 128 bricks, more
-    surface bricks than one group, one chunk and one sum of sums hold: points
+    surface bricks than one group, one chunk and one sum of sums hold, volumes
+    below and above the size at which surface bricks are listed first: points
     of random values in a share of the bricks, against the oracle on the same
     values (emitting voxels equal; positions within 1e-4 m and normals within
     2e-3, the bounds of the room tests)."""
@@ -108,3 +110,39 @@ def test_surface_points_edges(mvf, dims, share):
         ok = np.isfinite(No).all(axis=1)
         assert np.array_equal(ok, np.isfinite(Nd).all(axis=1))
         assert not ok.any() or np.abs(Nd[ok] - No[ok]).max() <= 2e-3
+
+
+@pytest.mark.parametrize("w,h,iters", [(17, 13, (2,)), (64, 48, (2, 2)), (333, 251, (2, 1, 2)), (1100, 500, (2, 2, 1))])
+def test_track_edges(mvf, w, h, iters):
+    """Images of less than a block, of partial blocks and of more blocks than
+    the last block sums in one go; one to three levels.  Every step pairs the
+    oracle's pixels; squared errors within 1e-9 (sums in another order) and
+    the pose within 1e-6, the bounds of the room tests."""
+    log(f"track {w}x{h} {iters}")
+    import torch
+    f = 0.9 * w
+    K = np.array([f, f, w / 2 - 0.4, h / 2 + 0.3], np.float32)
+    u, v = np.meshgrid(np.arange(w), np.arange(h))
+    x, y = (u - w / 2) / f, (v - h / 2) / f
+
+    def surface(dz):
+        z = 2.0 + dz + 0.25 * np.sin(5 * x + 0.3) * np.cos(4 * y) + 0.3 * x - 0.2 * y
+        rng = np.random.default_rng(w)
+        z[rng.random(z.shape) < 0.01] = 0.0
+        return z.astype(np.float32)
+
+    Tm = POSE
+    Vc, Nc = O.vertex_normal(surface(0.0), K)
+    Vm = (Vc.astype(np.float64) @ Tm[:, :3].T + Tm[:, 3]).astype(np.float32)
+    Nm = (Nc.astype(np.float64) @ Tm[:, :3].T).astype(np.float32)
+    d = surface(0.012)
+    T32 = Tm.astype(np.float32).astype(np.float64)
+    model = {"vertex": t(Vm), "normal": t(Nm)}
+    with mvf.Context() as ctx:
+        for _ in range(3):   # the state starts afresh with every call
+            T, st = ctx.track(t(d), K, model, Tm, T32, iters=iters)
+    T_ora, steps = O.icp_track(d, K, Vm, Nm, T32, T32, iters=iters)
+    assert [s[1] for s in steps] == st["pairs"]
+    for (_, _, e), e_dev in zip(steps, st["sq_err"]):
+        assert abs(e - e_dev) <= 1e-9 * max(e, 1e-12)
+    assert np.abs(T - T_ora).max() <= 1e-6
