@@ -267,7 +267,8 @@ int launch_raycast(const RaycastLaunch& L, int blocks, void* stream, void* ev_st
 // Launch order of the ray_groups(n) groups of n raycast tiles from their
 // last durations, longest first (a slow tile started late bounds the launch).
 int launch_tile_order(const uint32_t* cost, int32_t* order, int n, void* stream);
-int launch_brick_summary(DevVolume v, void* stream);
+// Column flag words from the brick flags.
+int launch_column_flags(DevVolume v, void* stream);
 // Brick distance transform of every volume in the table (3 passes).
 // brick_base: nvol + 1 prefix sums of the volumes' brick counts (each a
 // multiple of 64).  With frames and rb.entries set, the last pass also
@@ -285,8 +286,9 @@ int launch_ray_bounds_merge(const LaunchHeader* hdr, const DevFrame* frames, con
                             const int32_t* list_base, const int32_t* brick_base, RayBounds rb, int nstreams,
                             int max_cells_x, int max_cells_y, void* stream);
 int launch_to_canonical(DevVolume v, float* F, uint16_t* W, uint32_t* C, void* stream);
-int launch_from_canonical(DevVolume v, const float* F, const uint16_t* W, const uint32_t* C,
-                          void* stream);
+// Canonical planes (null: empty) into the volume's bricks, with the brick
+// flags and sub-block masks; full: weights and colours too, else only F.
+int launch_import(DevVolume v, const float* F, const uint16_t* W, const uint32_t* C, bool full, void* stream);
 // Surface points of one volume of nbricks bricks: scratch of
 // extract_buffer_bytes(nbricks) device bytes laid out by extract_buffers, and
 // a pinned host word that receives the number of points.  With cap > 0 the

@@ -1153,13 +1153,12 @@ mvf_status raycast_plain(mvf_ctx* c, int sid, const float* T, const mvf_intrinsi
     return MVF_OK;
 }
 
-// Exact recompute of a resident volume's brick summaries (flags, sub-block
-// masks, column words, distances and cell masks) after its planes were
-// overwritten, on `stream`.
+// The summaries that follow from a resident volume's flags and sub-block masks
+// (column words, distances and cell masks) after an import, on `stream`.
 mvf_status recompute_summaries(mvf_ctx* c, const Volume& v, hipStream_t stream)
 {
     const DevVolume dv = make_dev(c, v);
-    CHECK_LAUNCH(launch_brick_summary(dv, stream));
+    CHECK_LAUNCH(launch_column_flags(dv, stream));
     int slot;
     Writer w;
     CHECK_ST(arena_acquire(c, &slot, &w));
@@ -1873,8 +1872,7 @@ mvf_status mvf_volume_write(mvf_ctx* c, int32_t id, const float* F, const uint16
     if (st == MVF_OK && rgba && (e = hipMemcpy(dC, rgba, n * 4, hipMemcpyHostToDevice)) != hipSuccess) st = MVF_ERR_HIP;
     if (st == MVF_OK) {
         DevVolume dv = make_dev(c, *v);
-        int le = launch_volume_init(dv, nullptr);
-        if (!le) le = launch_from_canonical(dv, dF, dW, dC, nullptr);
+        const int le = launch_import(dv, dF, dW, dC, true, nullptr);
         if (le) { st = MVF_ERR_HIP; e = (hipError_t)le; }
         else {
             const mvf_status sst = recompute_summaries(c, *v, nullptr);
@@ -2970,7 +2968,9 @@ static mvf_status build_diff_mirror(mvf_ctx* c, const mvf_dense_tsdf* v, hipStre
     for (int a = 0; a < 3; ++a) mv.d.offset[a] = v->offset[a];
     m.F = nullptr;  // invalid until the import below is enqueued
     CHECK_ST(ensure_resident(c, std::vector<int>{m.vol}, s));
-    CHECK_LAUNCH(launch_from_canonical(make_dev(c, mv), v->F, v->W, nullptr, s));
+    // (the mirror's weights and colours stay as the slab's initialisation left
+    // them: a raycast reads F, its NaN and the summaries alone)
+    CHECK_LAUNCH(launch_import(make_dev(c, mv), v->F, v->W, nullptr, false, s));
     CHECK_ST(recompute_summaries(c, mv, s));
     m.F = v->F;
     m.W = v->W;

@@ -146,3 +146,75 @@ def test_track_edges(mvf, w, h, iters):
     for (_, _, e), e_dev in zip(steps, st["sq_err"]):
         assert abs(e - e_dev) <= 1e-9 * max(e, 1e-12)
     assert np.abs(T - T_ora).max() <= 1e-6
+
+
+@pytest.mark.parametrize("dims", [(2, 2, 2), (8, 8, 8), (9, 15, 17), (32, 8, 8), (36, 33, 40), (100, 24, 530), (64, 65, 66)])
+def test_write_read_summary_edges(mvf, dims):
+    """Import of canonical planes: a part of a brick, rows that are and are not
+    a multiple of four voxels (wide and narrow loads), columns of more than 64
+    bricks; NULL planes.  The planes come back equal and the brick flags equal
+    those of the values."""
+    log(f"write / read {dims}")
+    rng = np.random.default_rng(sum(dims))
+    nx, ny, nz = dims
+    F = rng.uniform(-1.0, 1.0, (nz, ny, nx)).astype(np.float32)
+    F[rng.random(F.shape) < 0.5] = 1.0
+    hole = np.kron(rng.random([(n + 7) // 8 for n in (nz, ny, nx)]) < 0.6, np.ones((8, 8, 8), bool))[:nz, :ny, :nx]
+    F[hole] = np.abs(F[hole]) + 0.01
+    W = rng.integers(0, 4, F.shape).astype(np.uint16)
+    C = rng.integers(0, 256, F.shape + (4,)).astype(np.uint8)
+    want = np.where(W > 0, F, 0.0).astype(np.float32)
+    bd = [(n + 7) // 8 for n in dims]
+    neg = np.zeros([8 * b for b in bd[::-1]], bool)
+    neg[:nz, :ny, :nx] = (W > 0) & (F <= 0)
+    flag = neg.reshape(bd[2], 8, bd[1], 8, bd[0], 8).any(axis=(1, 3, 5)).transpose(2, 1, 0)
+    with mvf.Context() as ctx:
+        gid = ctx.grid((0.0, 0.0, 0.0), 0.01)
+        vid = ctx.volume(gid, (0, 0, 0), dims)
+        for _ in range(2):   # a fresh slab, then one that holds other values
+            ctx.write_volume(vid, F, W, C)
+            f, w, c = ctx.read_volume(vid)
+            np.testing.assert_array_equal(w, W)
+            np.testing.assert_array_equal(c, C)
+            np.testing.assert_array_equal(f, want)
+            np.testing.assert_array_equal(ctx.brick_summary(vid)[0], flag.astype(np.uint8))
+            ctx.write_volume(vid, None, W, None)
+            f, w, c = ctx.read_volume(vid)
+            np.testing.assert_array_equal(w, W)
+            assert not f.any() and not c.any()
+            ctx.write_volume(vid, F, None, C)
+            f, w, c = ctx.read_volume(vid)
+            assert not f.any() and not w.any()
+            np.testing.assert_array_equal(c, C)
+            assert not ctx.brick_summary(vid)[0].any()
+
+
+@pytest.mark.parametrize("dims,shift", [((64, 40, 48), 0), ((64, 40, 48), 1), ((64, 40, 48), 2), ((45, 52, 61), 0),
+                                        ((45, 52, 61), 3)])
+def test_diffray_forward_import_alignment(mvf, dims, shift):
+    """The forward's copy of a dense volume whose planes start at any element:
+    its depths are those of a plain raycast of a volume written from the same
+    values, bit for bit."""
+    import torch
+    log(f"diffray import {dims} shift {shift}")
+    nx, ny, nz = dims
+    s = 0.05
+    z, y, x = np.meshgrid(np.arange(nz), np.arange(ny), np.arange(nx), indexing="ij")
+    r = np.sqrt((x - nx / 2) ** 2 + (y - ny / 2) ** 2 + (z - nz / 2) ** 2)
+    F = np.clip((r - 14.0) / 4.0, -1.0, 1.0).astype(np.float32)
+    W = np.where(F > -1.0, 3, 0).astype(np.uint16)
+    T = np.array([[1.0, 0, 0, s * nx / 2], [0, 1.0, 0, s * ny / 2], [0, 0, 1.0, -0.7]])
+    K = np.array([80.0, 80.0, 47.5, 35.5], np.float32)
+    buf = torch.zeros(F.size + 8, device="cuda")
+    wbuf = torch.zeros(F.size + 8, dtype=torch.int16, device="cuda")
+    Fd, Wd = buf[shift:shift + F.size].view(nz, ny, nx), wbuf[shift:shift + F.size].view(nz, ny, nx)
+    Fd.copy_(t(F))
+    Wd.copy_(t(W.view(np.int16)))
+    with mvf.Context() as ctx:
+        depth, record = ctx.diffray_forward(Fd, Wd, (0.0, 0.0, 0.0), s, T, K, 96, 72)
+        gid = ctx.grid((0.0, 0.0, 0.0), s)
+        vid = ctx.volume(gid, (0, 0, 0), dims)
+        ctx.write_volume(vid, F, W)
+        plain = ctx.raycast(T, K, 96, 72)["depth"]
+    assert int((record > 0).sum()) > 500
+    assert torch.equal(depth, plain)
