@@ -218,3 +218,41 @@ def test_diffray_forward_import_alignment(mvf, dims, shift):
         plain = ctx.raycast(T, K, 96, 72)["depth"]
     assert int((record > 0).sum()) > 500
     assert torch.equal(depth, plain)
+
+
+@pytest.mark.parametrize("w,h,f,add", [(33, 17, 30.0, 0.0), (16, 16, 9000.0, 0.0), (160, 120, 60.0, 0.25),
+                                       (257, 31, 400.0, -1.5)])
+def test_diffray_backward_edges(mvf, w, h, f, add):
+    """Voxel gradients gathered per block: pixels whose voxels are all
+    different (more than a block's table holds), pixels that all share a few
+    voxels, partial blocks, and a gradient buffer that already holds values.
+    Against the binary64 oracle, within the contract's 1e-3 of the largest
+    entry and 1e-3 relative for the pose."""
+    import torch
+    log(f"diffray backward {w}x{h} f {f}")
+    n, s = 96, 0.02
+    z, y, x = np.meshgrid(np.arange(n), np.arange(n), np.arange(n), indexing="ij")
+    r = np.sqrt((x - 47.3) ** 2 + (y - 48.1) ** 2 + (z - 50.2) ** 2)
+    F = np.clip((r - 36.0) / 4.0, -1.0, 1.0).astype(np.float32)
+    W = np.where(F > -1.0, 3, 0).astype(np.uint16)
+    og = O.OGrid((0.0, 0.0, 0.0), s, 4.0, 128)
+    ov = O.OVolume((n, n, n), (0, 0, 0), F.astype(np.float64), W, np.zeros(W.shape + (4,), np.uint8))
+    T = np.array([[1.0, 0, 0, 0.95], [0, 1.0, 0, 0.97], [0, 0, 1.0, -0.4]]).astype(np.float32).astype(np.float64)
+    K = np.array([f, f, w / 2 - 0.3, h / 2 + 0.2], np.float32)
+    rc = O.raycast([ov], og, K, T, w, h)
+    rng = np.random.default_rng(w)
+    gd = (rng.uniform(0.5, 1.5, (h, w)) * (rc["hit"] >= 0)).astype(np.float32)
+    assert (rc["hit"] >= 0).sum() > 100
+    g_ref, gF_ref = O.depth_grad(ov, og, K, T, w, h, O.structure(rc), gd.astype(np.float64))
+    Fd, Wd = t(F), t(W.view(np.int16))
+    with mvf.Context() as ctx:
+        _, record = ctx.diffray_forward(Fd, Wd, og.origin, s, T, K, w, h)
+        np.testing.assert_array_equal(record.cpu().numpy(), rc["k"])
+        for noalloc in (False, True):
+            grad_F = torch.full_like(Fd, add)
+            gxi = ctx.diffray_backward(Fd, Wd, og.origin, s, T, K, t(gd), record, grad_F, noalloc=noalloc)
+            err = np.abs(grad_F.cpu().numpy().astype(np.float64) - add - gF_ref).max()
+            assert err <= 1e-3 * np.abs(gF_ref).max()
+            assert np.linalg.norm(gxi.cpu().numpy() - g_ref) <= 1e-3 * np.linalg.norm(g_ref)
+        alone = ctx.diffray_backward(Fd, Wd, og.origin, s, T, K, t(gd), record)
+        assert torch.equal(alone, gxi)
