@@ -190,8 +190,8 @@ struct IntegrateLaunch {
     // item may hold a voxel the frame updates (written by the z-table
     // launch), or null (visit all); needs zchunk <= kVisitPerItem
     uint8_t* visit;
-    // optional: block 0 computes a raycast tile order (see launch_tile_order)
-    // from these costs instead of integrating; the grid has one more block
+    // optional: block 0 computes a raycast tile order (see TileOrder) from
+    // these costs instead of integrating; the grid has one more block
     const uint32_t* tile_cost;
     int32_t* tile_order;
     int32_t order_tiles;
@@ -264,9 +264,14 @@ int launch_integrate(const IntegrateLaunch& L, int blocks, void* stream, void* e
 // Raycast kernel over ray_blocks(total tiles) blocks (or fewer: a grid-stride loop).
 int launch_raycast(const RaycastLaunch& L, int blocks, void* stream, void* ev_start = nullptr,
                    void* ev_stop = nullptr);
-// Launch order of the ray_groups(n) groups of n raycast tiles from their
-// last durations, longest first (a slow tile started late bounds the launch).
-int launch_tile_order(const uint32_t* cost, int32_t* order, int n, void* stream);
+// A launch order to compute for the ray_groups(tiles) groups of that many
+// raycast tiles from their last durations, longest first (a slow tile started
+// late bounds the launch); tiles 0: none.
+struct TileOrder {
+    const uint32_t* cost;
+    int32_t* order;
+    int32_t tiles;
+};
 // Column flag words from the brick flags.
 int launch_column_flags(DevVolume v, void* stream);
 // Brick distance transform of every volume in the table (3 passes).
@@ -282,9 +287,10 @@ int launch_ray_bounds_collect(const LaunchHeader* hdr, const DevVolume* vols, co
 // Range bounds of every cell of each stream's frame from the footprints of
 // the stream's volumes (lists / list_base as in RaycastLaunch); clears the
 // other half of rb.counts.  max_cells_x/y: largest cell grid of the frames.
+// One more block computes `order`, if given.
 int launch_ray_bounds_merge(const LaunchHeader* hdr, const DevFrame* frames, const int32_t* lists,
                             const int32_t* list_base, const int32_t* brick_base, RayBounds rb, int nstreams,
-                            int max_cells_x, int max_cells_y, void* stream);
+                            int max_cells_x, int max_cells_y, void* stream, TileOrder order = TileOrder{});
 int launch_to_canonical(DevVolume v, float* F, uint16_t* W, uint32_t* C, void* stream);
 // Canonical planes (null: empty) into the volume's bricks, with the brick
 // flags and sub-block masks; full: weights and colours too, else only F.

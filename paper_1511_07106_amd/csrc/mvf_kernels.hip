@@ -1644,19 +1644,6 @@ __global__ __launch_bounds__(64, 5) void mvf_raycast_kernel(RaycastLaunch L)
     }
 }
 
-__global__ __launch_bounds__(1024) void mvf_tile_order_kernel(const uint32_t* cost, int32_t* order, int ntiles)
-{
-    __shared__ int hist[kOrderBins];
-    tile_order_block(cost, order, ntiles, hist);
-}
-
-int launch_tile_order(const uint32_t* cost, int32_t* order, int n, void* stream)
-{
-    if (n <= 0) return 0;
-    hipLaunchKernelGGL(mvf_tile_order_kernel, dim3(1), dim3(1024), 0, (hipStream_t)stream, cost, order, n);
-    return (int)hipGetLastError();
-}
-
 template <int P>
 static __host__ __device__ void raycast_pixel(const RaycastLaunch& L, const LaunchHeader& H, int s, int u, int v,
                                               int j)
@@ -2053,11 +2040,19 @@ int launch_ray_bounds_collect(const LaunchHeader* hdr, const DevVolume* vols, co
 
 // Block (x, y, s): cells [8x, 8x + 8) x [8y, 8y + 8) of stream s, folded in
 // LDS from every footprint of the stream's volumes.  Block (0, 0, 0) also
-// clears the other half of the counts.
+// clears the other half of the counts.  With a tile order to compute, block
+// (0, 0, order_z) sorts the tile groups beside the others (a launch of its own
+// between the merge and the raycast took 8 us and its gap).
 __global__ __launch_bounds__(1024) void mvf_ray_bounds_merge_kernel(const LaunchHeader* hdr, const DevFrame* frames,
                                                                    const int32_t* lists, const int32_t* list_base,
-                                                                   const int32_t* brick_base, RayBounds rb)
+                                                                   const int32_t* brick_base, RayBounds rb,
+                                                                   TileOrder order, int order_z)
 {
+    if (order.tiles > 0 && (int)blockIdx.z == order_z) {
+        __shared__ int hist[kOrderBins];
+        if (blockIdx.x == 0 && blockIdx.y == 0) tile_order_block(order.cost, order.order, order.tiles, hist);
+        return;
+    }
     const int par = hdr->rb_parity;
     if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0)
         for (int i = threadIdx.x; i < rb.cap; i += blockDim.x) rb.counts[(1 - par) * rb.cap + i] = 0;
@@ -2111,12 +2106,12 @@ __global__ __launch_bounds__(1024) void mvf_ray_bounds_merge_kernel(const Launch
 
 int launch_ray_bounds_merge(const LaunchHeader* hdr, const DevFrame* frames, const int32_t* lists,
                             const int32_t* list_base, const int32_t* brick_base, RayBounds rb, int nstreams,
-                            int max_cells_x, int max_cells_y, void* stream)
+                            int max_cells_x, int max_cells_y, void* stream, TileOrder order)
 {
     if (nstreams <= 0) return 0;
-    const dim3 grid((max_cells_x + 7) / 8, (max_cells_y + 7) / 8, nstreams);
+    const dim3 grid((max_cells_x + 7) / 8, (max_cells_y + 7) / 8, nstreams + (order.tiles > 0 ? 1 : 0));
     hipLaunchKernelGGL(mvf_ray_bounds_merge_kernel, grid, dim3(1024), 0, (hipStream_t)stream, hdr, frames, lists,
-                       list_base, brick_base, rb);
+                       list_base, brick_base, rb, order, nstreams);
     return (int)hipGetLastError();
 }
 

@@ -1069,7 +1069,7 @@ mvf_status raycast_plain(mvf_ctx* c, int sid, const float* T, const mvf_intrinsi
     const int tiles = ((out->width + tw - 1) / tw) * ((out->height + th - 1) / th);
     CHECK_ST(get_tile_buffers(sc, tiles));
     CHECK_ST(get_bound_buffers(sc, out->width, out->height));
-    // an order the integration computed holds for this many tiles only
+    // an order the integration computed holds for this many tiles only (else the merge computes one)
     const bool ordered = sc->order_ready_tiles == tiles && sc->last_tiles == tiles;
     sc->order_ready_tiles = 0;
     sc->last_tiles = tiles;
@@ -1142,8 +1142,8 @@ mvf_status raycast_plain(mvf_ctx* c, int sid, const float* T, const mvf_intrinsi
         CHECK_ST(timing_pair(c, &t0, &t1));
         const RayBounds RB{sc->rb_entries, sc->rb_counts, sc->rb_counts_cap};
         CHECK_LAUNCH(launch_ray_bounds_collect(dh, dvols, dbb, dfr, RB, std::min(1024, (nbr + 255) / 256), stream));
-        CHECK_LAUNCH(launch_ray_bounds_merge(dh, dfr, dlists, dlb, dbb, RB, 1, fr->cells_x, fr->cells_y, stream));
-        if (!(ordered && wi == 0)) CHECK_LAUNCH(launch_tile_order(sc->tile_cost, sc->tile_order, tiles, stream));
+        const TileOrder order = ordered && wi == 0 ? TileOrder{} : TileOrder{sc->tile_cost, sc->tile_order, tiles};
+        CHECK_LAUNCH(launch_ray_bounds_merge(dh, dfr, dlists, dlb, dbb, RB, 1, fr->cells_x, fr->cells_y, stream, order));
         CHECK_LAUNCH(launch_raycast(L, ray_blocks(tiles), stream, t0, t1));
         CHECK_ST(timing_push(c, t0, t1, 1));
         CHECK_ST(arena_release(c, slot, stream));
