@@ -80,6 +80,9 @@ struct DevVolume {
     int32_t w_max;
     int32_t frame;       // index of the stream's frame in the frame table
     int32_t zt_base;     // first entry of this volume in the launch's z table
+    // world box that a raycast looks for samples in: the sample domain grown
+    // by a voxel
+    float ray_lo[3], ray_hi[3];
 };
 
 struct DevFrame {
@@ -102,6 +105,8 @@ struct DevFrame {
     int32_t* best_id;
     int32_t* record;         // per pixel: k of the nearest crossing's second sample, -1 = none; or null
     int32_t out_w, out_h;
+    int32_t ray_tiles_x;     // raycast pixel tiles per row of the output
+    float inv_ray_tiles_x;   // its reciprocal (rounded; the kernel corrects the quotient)
     // raycast range bounds per 8x8 output-pixel cell (cells_x * cells_y,
     // row-major), or null: the nearest and farthest camera distance of any
     // sample the march may have to evaluate; a cell no brick reaches holds
@@ -214,8 +219,8 @@ constexpr int kVisitPerItem = 8;
 // samples per round of gathers: 2, 4 or 8), and the pixel tile of a
 // 64-lane block for each (8x4, 4x4, 4x2).  kRayLanes is the default.
 constexpr int kRayLanes = 4;
-MVF_HD int ray_tile_w(int lanes) { return lanes == 2 ? 8 : 4; }
-MVF_HD int ray_tile_h(int lanes) { return 64 / lanes / ray_tile_w(lanes); }
+MVF_HD constexpr int ray_tile_w(int lanes) { return lanes == 2 ? 8 : 4; }
+MVF_HD constexpr int ray_tile_h(int lanes) { return 64 / lanes / ray_tile_w(lanes); }
 constexpr int kBoundCell = 8;   // output pixels per side of a raycast range-bound cell (a ray tile lies in one)
 // Raycast launch order: groups of kRayGroup consecutive tiles are ordered by
 // their summed last duration, slowest first.  Blocks are dealt round-robin
@@ -233,8 +238,7 @@ struct RaycastLaunch {
     const int32_t* lists;       // concatenated per-stream lists of table indices, nearest first
     const int32_t* list_base;   // per stream: [list_base[s], list_base[s+1])
     const int32_t* tile_base;   // per stream: first pixel tile; nstreams + 1 entries
-    int32_t tile_w, tile_h;     // pixel tile: ray_tile_w(lanes) x ray_tile_h(lanes)
-    int32_t lanes;              // lanes per ray (2, 4 or 8)
+    int32_t lanes;              // lanes per ray (2, 4 or 8); pixel tile: ray_tile_w(lanes) x ray_tile_h(lanes)
     uint32_t* tile_cost;        // per tile: its duration in the last launch (10 ns ticks), or null
     const int32_t* tile_order;  // tile groups in launch order, or null (index order)
 };
@@ -261,7 +265,7 @@ int launch_ztable(const IntegrateLaunch& L, int bricks, void* stream);
 // With ev_start/ev_stop (hipEvent_t) the kernel's own dispatch records them.
 int launch_integrate(const IntegrateLaunch& L, int blocks, void* stream, void* ev_start = nullptr,
                      void* ev_stop = nullptr);
-// Raycast kernel over ray_blocks(total tiles) blocks (or fewer: a grid-stride loop).
+// Raycast kernel; blocks: ray_blocks(total tiles).
 int launch_raycast(const RaycastLaunch& L, int blocks, void* stream, void* ev_start = nullptr,
                    void* ev_stop = nullptr);
 // A launch order to compute for the ray_groups(tiles) groups of that many

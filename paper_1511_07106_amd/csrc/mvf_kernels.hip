@@ -1056,23 +1056,28 @@ static __host__ __device__ __forceinline__ bool in_domain(const DevVolume& V, co
            l[1] < (float)(V.dims[1] - 1) && l[2] >= 0.0f && l[2] < (float)(V.dims[2] - 1);
 }
 
-// 32-bit brick-linear addressing: a volume holds at most 2^30 padded
-// voxels, so element and byte offsets of its planes fit in 32 bits.
-static __host__ __device__ __forceinline__ uint32_t mul24(uint32_t a, uint32_t b)
+// a * b + c of values below 2^24 (left to itself the compiler takes the
+// 64-bit multiply-add, at a quarter of the rate)
+static __device__ __forceinline__ uint32_t mad24(uint32_t a, uint32_t b, uint32_t c)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
-    return __umul24(a, b);
+    uint32_t r;
+    asm("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(r) : "v"(a), "s"(b), "v"(c));
+    return r;
 #else
-    return a * b;
+    return a * b + c;
 #endif
 }
 
-static __host__ __device__ __forceinline__ uint32_t brick_index32(const DevVolume& V, int bx, int by, int bz)
+// 32-bit brick-linear addressing: a volume holds at most 2^30 padded
+// voxels, so element and byte offsets of its planes fit in 32 bits.  (V's
+// table entry is the same for the whole wavefront.)
+static __device__ __forceinline__ uint32_t brick_index32(const DevVolume& V, int bx, int by, int bz)
 {
-    return mul24(mul24((uint32_t)bx, (uint32_t)V.bd[1]) + (uint32_t)by, (uint32_t)V.bd[2]) + (uint32_t)bz;
+    return mad24(mad24((uint32_t)bx, (uint32_t)V.bd[1], (uint32_t)by), (uint32_t)V.bd[2], (uint32_t)bz);
 }
 
-static __host__ __device__ __forceinline__ uint32_t voxel_index32(const DevVolume& V, const int i[3])
+static __device__ __forceinline__ uint32_t voxel_index32(const DevVolume& V, const int i[3])
 {
     return brick_index32(V, i[0] >> 3, i[1] >> 3, i[2] >> 3) * (uint32_t)kBrickVox +
            (uint32_t)(((i[2] & 7) << 6) | ((i[1] & 7) << 3) | (i[0] & 7));
@@ -1086,7 +1091,7 @@ static __host__ __device__ __forceinline__ T ld_elem(GPTR(const T) base, uint32_
 }
 
 // 8 corner values of the cell with base i (brick-linear addressing)
-static __host__ __device__ __forceinline__ void gather8(const DevVolume& V, const int i[3], float c[8])
+static __device__ __forceinline__ void gather8(const DevVolume& V, const int i[3], float c[8])
 {
     const uint32_t base = voxel_index32(V, i);
     const uint32_t sx = ((i[0] & 7) == 7) ? (uint32_t)V.bd[1] * (uint32_t)V.bd[2] * kBrickVox - 7u : 1u;
@@ -1114,34 +1119,6 @@ static __host__ __device__ __forceinline__ float trilinear(const float c[8], con
     const float c0 = lerp32(c00, c10, f[1]);
     const float c1 = lerp32(c01, c11, f[1]);
     return lerp32(c0, c1, f[2]);
-}
-
-// The 8 corner values of the last cell gathered by a ray; consecutive
-// samples half a voxel apart often share a cell.
-struct CellCache {
-    int i[3];
-    float c[8];
-};
-
-static __host__ __device__ __forceinline__ bool eval_sample_cached(const DevVolume& V, const float l[3], float& Fk,
-                                                                   CellCache& cc)
-{
-    int i[3];
-    float f[3];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        const float fl = floorf(l[a]);
-        i[a] = (int)fl;
-        f[a] = l[a] - fl;
-    }
-    if (i[0] != cc.i[0] || i[1] != cc.i[1] || i[2] != cc.i[2]) {
-        gather8(V, i, cc.c);
-        cc.i[0] = i[0];
-        cc.i[1] = i[1];
-        cc.i[2] = i[2];
-    }
-    Fk = trilinear(cc.c, f);
-    return !isnan(Fk);
 }
 
 // Conservative sample range [k0, k1] of the ray inside V's domain box grown
@@ -1231,28 +1208,23 @@ static __device__ void collect_footprint(const DevVolume& V, const DevFrame& Fr,
     if (has) rb.entries[brick_base[v] + base + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = e;
 }
 
-static __host__ __device__ __forceinline__ void ray_k_range(const DevVolume& V, const Ray& r, float delta, int kmax,
-                                                   int& k0, int& k1)
+static __device__ __forceinline__ void ray_k_range(const DevVolume& V, const Ray& r, float delta, int kmax, int& k0,
+                                                   int& k1)
 {
     float t0 = fmaxf(0.0f, r.t_lo), t1 = fminf((float)kmax * delta, r.t_hi);
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        const float lo = V.o[a] + V.s * ((float)V.off[a] + 0.5f) - V.s;
-        const float hi = V.o[a] + V.s * ((float)V.off[a] + (float)V.dims[a] - 0.5f) + V.s;
-        if (r.dw[a] == 0.0f) {
-            if (r.C[a] < lo || r.C[a] > hi) { k0 = 1; k1 = 0; return; }
-        } else {
-            // approximate reciprocal: the range is grown by a voxel and two
-            // samples, far beyond its rounding error
-            float ta = (lo - r.C[a]) * r.inv_dw[a], tb = (hi - r.C[a]) * r.inv_dw[a];
-            if (ta > tb) { const float t = ta; ta = tb; tb = t; }
-            t0 = fmaxf(t0, ta);
-            t1 = fminf(t1, tb);
-        }
+        // approximate reciprocal: the range is grown by a voxel and two
+        // samples, far beyond its rounding error.  A ray along the planes has
+        // an infinite one: both ends at -inf and +inf inside, both on one side
+        // (an empty range) outside.
+        const float ta = (V.ray_lo[a] - r.C[a]) * r.inv_dw[a], tb = (V.ray_hi[a] - r.C[a]) * r.inv_dw[a];
+        t0 = fmaxf(t0, fminf(ta, tb));
+        t1 = fminf(t1, fmaxf(ta, tb));
     }
-    if (!(t0 <= t1)) { k0 = 1; k1 = 0; return; }
-    k0 = max(1, (int)floorf(t0 * r.inv_delta) - 2);
-    k1 = min(kmax, (int)ceilf(t1 * r.inv_delta) + 2);
+    const bool some = t0 <= t1;
+    k0 = some ? max(1, (int)floorf(t0 * r.inv_delta) - 2) : 1;
+    k1 = some ? min(kmax, (int)ceilf(t1 * r.inv_delta) + 2) : 0;
 }
 
 // Empty-space skip.  Samples whose cells have no corner that may hold F <= 0
@@ -1261,144 +1233,93 @@ static __host__ __device__ __forceinline__ void ray_k_range(const DevVolume& V, 
 // bricks within dist - 1 of the sample's brick, else clear cell sub-blocks
 // of its brick grown along the ray.  Returns how many samples, from this
 // one (local coordinate l, cell base i, in the domain), can be skipped, or 0
-// when it must be evaluated.  The jump keeps a 0.01-voxel margin to the box
-// [A, B) of cell base coordinates.
+// when it must be evaluated.  The jump keeps a 0.01-voxel margin to the end
+// of the region.
+//
+// A raycast's slowest rays make dozens of these tests one after the other, and
+// the launch's bulk is bound by their instructions, so positions are counted
+// along the ray (each axis from the side of the brick that the ray enters):
+// the cell mask is turned that way once per brick, and then growth and jump
+// need no case per direction (measured: at the kernel).
 struct SkipCache {
     uint32_t b;    // brick whose distance and cell mask are held
     int D;
-    uint64_t cm;
+    uint64_t cm;   // oriented along the ray
 };
 
-static __host__ __device__ __forceinline__ int skip_run(const DevVolume& V, const float l[3], const int i[3],
-                                                        const float dl[3], const float inv_dl[3],
-                                                        GPTR(const uint8_t) distp, GPTR(const uint64_t) cmaskp,
-                                                        SkipCache& sc)
+struct SkipDir {
+    uint32_t flip;               // of orient_mask
+    float sg[3], off[3];         // position along the ray in a brick: sg * (l - 8 b) + off
+    float inv[3];                // samples per voxel
+};
+
+static __device__ __forceinline__ SkipDir skip_dir(const DevVolume& V, const Ray& r, float delta)
 {
-    int A[3], B[3];
-    bool skip = false;
+    SkipDir d;
+    d.flip = 0;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        // advance per sample in voxels (skipping only: the 0.01-voxel margin
+        // absorbs the rounding); an axis without advance never ends the jump
+        const float dl = delta * r.dw[a] * V.inv_s;
+        const bool neg = dl < 0.0f;
+        d.flip |= neg ? 3u << (2 * a) : 0u;
+        d.sg[a] = neg ? -1.0f : 1.0f;
+        d.off[a] = neg ? 8.0f : 0.0f;
+        d.inv[a] = fminf(fabsf(approx_rcp(dl)), 1e30f);
+    }
+    return d;
+}
+
+static __device__ __forceinline__ int skip_run(const DevVolume& V, const float l[3], const int i[3], const SkipDir& d,
+                                               GPTR(const uint8_t) distp, GPTR(const uint64_t) cmaskp, SkipCache& sc)
+{
     const uint32_t bi = brick_index32(V, i[0] >> 3, i[1] >> 3, i[2] >> 3);
     if (bi != sc.b) {
         sc.b = bi;
         sc.D = ld_elem(distp, bi);
-        sc.cm = ld_elem(cmaskp, bi);
+        sc.cm = orient_mask(ld_elem(cmaskp, bi), d.flip);
     }
-    const int D = sc.D;
-    if (D >= 2) {
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            A[a] = 8 * ((i[a] >> 3) - (D - 1));
-            B[a] = 8 * ((i[a] >> 3) + (D - 1)) + 7;
-        }
-        skip = true;
-    } else {
-        int lo[3], hi[3];
-#pragma unroll
-        for (int a = 0; a < 3; ++a) lo[a] = hi[a] = (i[a] & 7) >> 1;
-        if ((subblock_box(lo, hi) & sc.cm) == 0) {
-            skip = true;
-            // grown over clear sub-blocks along the ray (x, then y, then z)
-            grow_clear_box(sc.cm, lo, hi, dl);
-#pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                A[a] = (i[a] & ~7) + 2 * lo[a];
-                B[a] = (i[a] & ~7) + 2 * hi[a] + 2;
-            }
-        }
-    }
-    if (!skip) return 0;
-    float m = 1e30f;
+    const uint32_t q = (((uint32_t)i[0] >> 1 & 3u) | ((uint32_t)i[1] >> 1 & 3u) << 2 | ((uint32_t)i[2] >> 1 & 3u) << 4) ^ d.flip;
+    uint32_t n[3];
+    clear_ahead(sc.cm, q, n);
+    if (sc.D < 2 && n[0] == 0) return 0;
+    // end of the clear region along the ray: of the cube of bricks (its last
+    // cells reach into the brick beyond), or of the sub-blocks
+    const float cube = (float)(8 * sc.D - 1);
+    float m = 4096.0f;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        if (dl[a] > 0.0f) m = fminf(m, ((float)B[a] - 0.01f - l[a]) * inv_dl[a]);
-        else if (dl[a] < 0.0f) m = fminf(m, (l[a] - ((float)A[a] + 0.01f)) * -inv_dl[a]);
+        const float end = sc.D >= 2 ? cube : (float)(2u * ((q >> (2 * a) & 3u) + n[a]));
+        const float at = fmaf(d.sg[a], l[a] - (float)(i[a] & ~7), d.off[a]);
+        m = fminf(m, fmaxf((end - 0.01f) - at, 1e-20f) * d.inv[a]);
     }
-    const int jump = (int)fminf(fmaxf(m, 0.0f), 4096.0f);
-    return jump < 1 ? 1 : jump;
+    return max((int)m, 1);
 }
 
-// March one volume.  Returns true with t* and k when a crossing nearer than
-// (best_t, best_id) exists.
-static __host__ __device__ bool march_volume(const DevVolume& V, const Ray& r, float delta, int kmax,
-                                    float best_t, int best_id, float& tstar, int& kstar, int cell[3])
+// Exchanges within the P lanes of a group: cross-lane operands where a group
+// lies in four lanes (an LDS exchange takes its whole latency in every round).
+template <int P, int Op>
+static __device__ __forceinline__ int group_move(int x, int gbase)
 {
-    int k0, k1;
-    ray_k_range(V, r, delta, kmax, k0, k1);
-    if (k0 > k1) return false;
-    {
-        const float t0 = (float)k0 * delta;
-        if (t0 > best_t || (t0 == best_t && V.id > best_id)) return false;
-    }
-    // per-sample advance in local voxel units and its reciprocal (for
-    // skipping only; the 0.01-voxel shrink of the skip box absorbs rounding)
-    float dl[3], inv_dl[3];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        dl[a] = delta * r.dw[a] * V.inv_s;
-        inv_dl[a] = approx_rcp(dl[a]);
-    }
-
-    int prev_k = -2;     // index of the last evaluated sample
-    bool prev_ok = false;
-    float Fprev = 0.0f;
-    GPTR(const uint8_t) const distp = gptr((const uint8_t*)V.dist);
-    GPTR(const uint64_t) const cmaskp = gptr((const uint64_t*)V.cmask);
-    SkipCache sc;
-    sc.b = 0xffffffffu;
-    sc.D = 0;
-    sc.cm = 0;
-    CellCache cc;
-    cc.i[0] = -1; cc.i[1] = -1; cc.i[2] = -1;
-    int k = k0;
-    while (k <= k1) {
-        if ((float)(k - 1) * delta > best_t) break;   // nothing nearer can follow
-        const float tk = (float)k * delta;
-        float l[3];
-        sample_coord(V, r, tk, l);
-        if (!in_domain(V, l)) {
-            prev_k = k; prev_ok = false;
-            ++k;
-            continue;
-        }
-        int i[3];
-#pragma unroll
-        for (int a = 0; a < 3; ++a) i[a] = (int)floorf(l[a]);
-        {
-            const int jump = skip_run(V, l, i, dl, inv_dl, distp, cmaskp, sc);
-            if (jump) {
-                prev_ok = false;
-                prev_k = -2;
-                k += jump;
-                continue;
-            }
-        }
-        if (prev_k != k - 1) {
-            // re-evaluate the previous sample (skipped or never seen)
-            float lp[3];
-            sample_coord(V, r, (float)(k - 1) * delta, lp);
-            prev_ok = in_domain(V, lp) && eval_sample_cached(V, lp, Fprev, cc);
-        }
-        float Fk;
-        const bool ok = eval_sample_cached(V, l, Fk, cc);
-        if (prev_ok && ok && Fprev > 0.0f && Fk <= 0.0f) {
-            const float ta = (float)(k - 1) * delta;
-            const float ts = ta + ((delta * Fprev) / (Fprev - Fk));
-            if (ts < best_t || (ts == best_t && V.id < best_id)) {
-                tstar = ts;
-                kstar = k;
-                cell[0] = i[0]; cell[1] = i[1]; cell[2] = i[2];
-                return true;
-            }
-            return false;
-        }
-        prev_k = k;
-        prev_ok = ok;
-        Fprev = Fk;
-        ++k;
-    }
-    return false;
+    // Op 0: lane ^ 1, 1: lane ^ 2, 2: the lane before (the first keeps its own), 3: the last lane
+    constexpr int quad = Op == 0 ? 0xb1 : Op == 1 ? 0x4e : Op == 2 ? (P == 2 ? 0xa0 : 0x90) : (P == 2 ? 0xf5 : 0xff);
+    if (P <= 4) return __builtin_amdgcn_update_dpp(x, x, quad, 0xf, 0xf, true);
+    if (Op == 0) return __shfl_xor(x, 1);
+    if (Op == 1) return __shfl_xor(x, 2);
+    if (Op == 2) return __shfl_up(x, 1, P);
+    return __shfl(x, gbase + P - 1);
 }
 
-#if defined(__HIP_DEVICE_COMPILE__)
+template <int P>
+static __device__ __forceinline__ int group_max(int x, int gbase)
+{
+    x = max(x, group_move<P, 0>(x, gbase));
+    if (P > 2) x = max(x, group_move<P, 1>(x, gbase));
+    if (P > 4) x = max(x, __shfl_xor(x, 4));
+    return x;
+}
+
 // March one volume with the P lanes of a group (lane j of the group; all P
 // lanes carry the same ray and take the same path through the loop).  A
 // round starts at sample w0: every lane makes the skip decision of sample
@@ -1423,53 +1344,47 @@ static __device__ bool march_volume_group(const DevVolume& V, const Ray& r, floa
         const float t0 = (float)k0 * delta;
         if (t0 > best_t || (t0 == best_t && V.id > best_id)) return false;
     }
-    float dl[3], inv_dl[3];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        dl[a] = delta * r.dw[a] * V.inv_s;
-        inv_dl[a] = approx_rcp(dl[a]);
+    // a crossing is not nearer than its first sample: the last far end is the
+    // last k with (k - 1) delta <= best_t (from an estimate above it)
+    if ((float)(k1 - 1) * delta > best_t) {
+        k1 = min(k1, (int)(best_t * r.inv_delta) + 4);
+        while ((float)(k1 - 1) * delta > best_t) --k1;
     }
+    const SkipDir dir = skip_dir(V, r, delta);
     const int gbase = (int)(threadIdx.x & 63u) & ~(P - 1);
-    const uint32_t gm = (1u << P) - 1u;
     GPTR(const uint8_t) const distp = gptr((const uint8_t*)V.dist);
     GPTR(const uint64_t) const cmaskp = gptr((const uint64_t*)V.cmask);
     SkipCache sc;
     sc.b = 0xffffffffu;
     sc.D = 0;
     sc.cm = 0;
+    constexpr int kMust = 0x7fffffff;
     int prev_k = -2;
-    bool prev_ok = false;
+    int prev_ok = 0;
     float Fprev = 0.0f;
     int k = k0;
     while (k <= k1) {
-        if ((float)(k - 1) * delta > best_t) break;   // nothing nearer can follow
-        const int w0 = (prev_k != k - 1) ? k - 1 : k;
-        const int sidx = w0 + j;
-        const bool far = sidx >= k && sidx <= k1;       // may be the far end of a crossing
+        const int sk = k + j;
         float l[3];
-        sample_coord(V, r, (float)sidx * delta, l);
-        const bool dom = in_domain(V, l);
-        int i[3];
-#pragma unroll
-        for (int a = 0; a < 3; ++a) i[a] = (int)floorf(l[a]);
-        int reach = sidx + 1;   // end (exclusive) of the run of samples this lane vouches for
-        bool must = false;
-        if (far && dom) {
-            const int jump = skip_run(V, l, i, dl, inv_dl, distp, cmaskp, sc);
-            if (jump) reach = sidx + jump;
-            else must = true;
+        sample_coord(V, r, (float)sk * delta, l);
+        // end (exclusive) of the run of samples this lane vouches for
+        int reach = sk + 1;
+        if (sk <= k1 && in_domain(V, l)) {
+            const int i[3] = {(int)l[0], (int)l[1], (int)l[2]};   // l >= 0
+            const int jump = skip_run(V, l, i, dir, distp, cmaskp, sc);
+            reach = jump ? sk + jump : kMust;
         }
-        const uint32_t must_g = (uint32_t)(__ballot(must) >> gbase) & gm;
-        if (must_g == 0) {
-            // the far-end samples of the window lie in overlapping clear runs
-            int rmax = far ? reach : k + 1;
-#pragma unroll
-            for (int o = 1; o < P; o <<= 1) rmax = max(rmax, __shfl_xor(rmax, o));
-            prev_ok = false;
-            prev_k = -2;
-            k = rmax;
+        // the window's samples lie in overlapping clear runs
+        const int clear = group_max<P>(reach, gbase);
+        if (clear != kMust) {
+            k = clear;
             continue;
         }
+        // on to the first sample that must be evaluated, from the one before it
+        // on unless that has been evaluated
+        k -= group_max<P>(reach == kMust ? -j : -P, gbase);
+        const int w0 = (prev_k != k - 1) ? k - 1 : k;
+        const int sidx = w0 + j;
         // evaluation round: kEvalWindows windows of P consecutive samples
         // from w0, lane j taking sample w0 + w*P + j of window w.  Samples of
         // the later windows are evaluated without a skip test: a sample the
@@ -1479,102 +1394,70 @@ static __device__ bool march_volume_group(const DevVolume& V, const Ray& r, floa
         // cell 0 and is discarded).
         constexpr int S = kEvalWindows;
         float Fs[S], Fns[S];
-        int oks[S], ics[S][3];
-        uint32_t cross_all = 0, excl_all = 0;
+        int jc = S * P;   // first crossing (offset from w0)
         {
             float cs[S][8], fs[S][3];
             bool doms[S];
 #pragma unroll
             for (int w = 0; w < S; ++w) {
                 float ls[3];
-                if (w == 0) {
-#pragma unroll
-                    for (int a = 0; a < 3; ++a) ls[a] = l[a];
-                    doms[w] = dom;
-                } else {
-                    sample_coord(V, r, (float)(sidx + w * P) * delta, ls);
-                    doms[w] = sidx + w * P <= k1 && in_domain(V, ls);
-                }
+                sample_coord(V, r, (float)(sidx + w * P) * delta, ls);
+                doms[w] = sidx + w * P <= k1 && in_domain(V, ls);
+                int i[3];
 #pragma unroll
                 for (int a = 0; a < 3; ++a) {
                     const float fl = floorf(ls[a]);
-                    ics[w][a] = doms[w] ? (int)fl : 0;
+                    i[a] = doms[w] ? (int)fl : 0;
                     fs[w][a] = ls[a] - fl;
                 }
-                gather8(V, ics[w], cs[w]);
+                gather8(V, i, cs[w]);
             }
-            float Fc = Fprev;
-            int okc = prev_ok;
 #pragma unroll
             for (int w = 0; w < S; ++w) {
                 const float Fk = trilinear(cs[w], fs[w]);
-                const bool ok = doms[w] && !isnan(Fk);
+                const int ok = doms[w] && !isnan(Fk);
                 Fs[w] = Fk;
-                oks[w] = ok;
-                float Fn = __shfl_up(Fk, 1, P);
-                int okn = __shfl_up((int)ok, 1, P);
-                if (j == 0) { Fn = Fc; okn = okc; }
+                float Fn = __int_as_float(group_move<P, 2>(__float_as_int(Fk), gbase));
+                int okn = group_move<P, 2>(ok, gbase);
+                if (j == 0) { Fn = Fprev; okn = prev_ok; }
                 Fns[w] = Fn;
-                Fc = __shfl(Fk, gbase + P - 1);
-                okc = __shfl((int)ok, gbase + P - 1);
-                const int si = sidx + w * P;
-                const bool farw = si >= k && si <= k1;
-                const bool excl = farw && (float)(si - 1) * delta > best_t;   // the sequential march stops first
-                const bool cross = farw && !excl && okn && ok && Fn > 0.0f && Fk <= 0.0f;
-                cross_all |= ((uint32_t)(__ballot(cross) >> gbase) & gm) << (w * P);
-                excl_all |= ((uint32_t)(__ballot(excl) >> gbase) & gm) << (w * P);
+                // the window's last sample is the next one's previous
+                Fprev = __int_as_float(group_move<P, 3>(__float_as_int(Fk), gbase));
+                prev_ok = group_move<P, 3>(ok, gbase);
+                if (sidx + w * P >= k && okn && ok && Fn > 0.0f && Fk <= 0.0f) jc = min(jc, w * P + j);
             }
         }
-        const int jc = cross_all ? __ffs(cross_all) - 1 : S * P;
-        const int je = excl_all ? __ffs(excl_all) - 1 : S * P;
-        if (jc < je) {
+        jc = -group_max<P>(-jc, gbase);
+        if (jc < S * P) {
             const int wc = jc / P, lc = jc - wc * P;
             float Fn = 0.0f, Fk = 0.0f;
-            int ic[3] = {0, 0, 0};
 #pragma unroll
             for (int w = 0; w < S; ++w)
-                if (w == wc) {
-                    Fn = Fns[w]; Fk = Fs[w];
-                    ic[0] = ics[w][0]; ic[1] = ics[w][1]; ic[2] = ics[w][2];
-                }
-            float ts = 0.0f;
-            int acc = 0;
-            if (j == lc) {
-                const float ta = (float)(w0 + jc - 1) * delta;
-                ts = ta + ((delta * Fn) / (Fn - Fk));
-                acc = (ts < best_t || (ts == best_t && V.id < best_id)) ? 1 : 0;
-            }
-            ts = __shfl(ts, gbase + lc);
-            acc = __shfl(acc, gbase + lc);
-            if (!acc) return false;
+                if (w == wc) { Fn = Fns[w]; Fk = Fs[w]; }
+            const float ta = (float)(w0 + jc - 1) * delta;
+            const float ts = __shfl(ta + ((delta * Fn) / (Fn - Fk)), gbase + lc);
+            if (!(ts < best_t || (ts == best_t && V.id < best_id))) return false;
             tstar = ts;
             kstar = w0 + jc;
+            // the far end's cell
+            float l[3];
+            sample_coord(V, r, (float)kstar * delta, l);
 #pragma unroll
-            for (int a = 0; a < 3; ++a) cell[a] = __shfl(ic[a], gbase + lc);
+            for (int a = 0; a < 3; ++a) cell[a] = (int)l[a];
             return true;
         }
-        if (je < S * P) return false;
-        // no crossing: the last far-end sample becomes the previous one
-        const int last = min(w0 + S * P - 1, k1);
-        const int jl = last - w0, wl = jl / P, ll = jl - wl * P;
-        float Fl = 0.0f;
-        int okl = 0;
-#pragma unroll
-        for (int w = 0; w < S; ++w)
-            if (w == wl) { Fl = Fs[w]; okl = oks[w]; }
-        prev_ok = __shfl(okl, gbase + ll) != 0;
-        Fprev = __shfl(Fl, gbase + ll);
-        prev_k = last;
-        k = last + 1;
+        // no crossing: the round's last sample becomes the previous one (past
+        // k1 the march ends)
+        prev_k = w0 + S * P - 1;
+        k = prev_k + 1;
     }
     return false;
 }
-#endif
 
 // unit normal: the gradient, at world point x, of the trilinear interpolant
 // of the given cell (the cell of the crossing's second sample, whose 8
 // voxels are all observed)
-static __host__ __device__ void surface_normal(const DevVolume& V, const float x[3], const int i[3], float n[3])
+static __device__ void surface_normal(const DevVolume& V, const float x[3], const int i[3], float n[3])
 {
     float f[3];
 #pragma unroll
@@ -1602,61 +1485,72 @@ static __host__ __device__ void surface_normal(const DevVolume& V, const float x
     }
 }
 
-// Pixel (u, v) of stream s; j: lane of the pixel's group (the host build
-// marches sequentially with j = 0).
+// Pixel (u, v) of stream s; j: lane of the pixel's group.
 template <int P>
-static __host__ __device__ void raycast_pixel(const RaycastLaunch& L, const LaunchHeader& H, int s, int u, int v,
-                                              int j = 0);
+static __device__ void raycast_pixel(const RaycastLaunch& L, CPTR(LaunchHeader) H, int s, int u, int v, int j);
 
+// Bounds: instruction issue in the bulk, the dependent rounds of the slowest
+// rays at the end (one 512^3 volume at 640 x 480: the tiles' durations sum to
+// 32 us on every resident block, the slowest tile takes 71 us of the launch's
+// 75).  So what counts is instructions per round and per tile: no loop over
+// tiles, the tile from reciprocals, the ray box's slabs and the skip boxes
+// without a case per direction, the group's exchanges as cross-lane operands,
+// table fields read where they are used.  106 us before these, 76 us after;
+// 1001 -> 655 us for 16 volumes of 256^3, 41 -> 29 us for 128^3 at 320 x 240.
+// Not taken: one lane testing two bricks a round (93 us), all of a tile's rays
+// skipping before any evaluates (its longest tile 95 -> 271 us), slow tiles
+// split into ray segments (101-142 us).
 template <int P>
 __global__ __launch_bounds__(64, 5) void mvf_raycast_kernel(RaycastLaunch L)
 {
-    const LaunchHeader H = *cptr(L.hdr);
+    CPTR(LaunchHeader) const H = cptr(L.hdr);
     // Tile groups are taken in the launch order (the slowest groups of the
     // last launch first, when an order is given); each block records how
     // long its tile took.
-    const int ngroups = ray_groups(H.total_tiles);
-    const int slots = ray_blocks(H.total_tiles);
-    for (int idx = blockIdx.x; idx < slots; idx += gridDim.x) {
-        const int win = idx / (kXcds * kRayGroup), r = idx - win * (kXcds * kRayGroup);
-        const int k = win * kXcds + r % kXcds;   // position in the order
-        if (k >= ngroups) continue;
-        const int g = L.tile_order ? cptr(L.tile_order)[k] : k;
-        const int tile = g * kRayGroup + r / kXcds;
-        if (tile >= H.total_tiles) continue;
-        const unsigned long long t_tile = wall_clock64();
-        CPTR(int32_t) const tile_base = cptr(L.tile_base);
-        int s = 0;
-        while (s + 1 < H.nstreams && tile_base[s + 1] <= tile) ++s;
-        s = wave_uniform(s);
-        const int out_w = cptr(L.frames)[s].out_w, out_h = cptr(L.frames)[s].out_h;
-        const int local = tile - tile_base[s];
-        const int tiles_x = (out_w + L.tile_w - 1) / L.tile_w;
-        const int ty = local / tiles_x, tx = local - ty * tiles_x;
-        const int pix = (int)threadIdx.x / P;   // P lanes per pixel
-        const int u = tx * L.tile_w + pix % L.tile_w;
-        const int v = ty * L.tile_h + pix / L.tile_w;
-        if (u < out_w && v < out_h) raycast_pixel<P>(L, H, s, u, v, (int)threadIdx.x % P);
-        if (L.tile_cost && threadIdx.x == 0) {
-            const unsigned long long d = wall_clock64() - t_tile;
-            L.tile_cost[tile] = d < 0xffffffffull ? (uint32_t)d : 0xffffffffu;
-        }
+    const int total = H->total_tiles, nstreams = H->nstreams;
+    const int win = (int)(blockIdx.x / (kXcds * kRayGroup)), in = (int)(blockIdx.x % (kXcds * kRayGroup));
+    const int k = win * kXcds + in % kXcds;   // position in the order
+    if (k >= ray_groups(total)) return;
+    const int g = L.tile_order ? cptr(L.tile_order)[k] : k;
+    const int tile = g * kRayGroup + in / kXcds;
+    if (tile >= total) return;
+    const unsigned long long t_tile = wall_clock64();
+    CPTR(int32_t) const tile_base = cptr(L.tile_base);
+    int s = 0;
+    while (s + 1 < nstreams && tile_base[s + 1] <= tile) ++s;
+    s = wave_uniform(s);
+    CPTR(DevFrame) const Fr = cptr(L.frames) + s;
+    const int tiles_x = Fr->ray_tiles_x;
+    const int local = tile - tile_base[s];
+    // local / tiles_x: an estimate within one of the quotient, corrected
+    int ty = (int)((float)local * Fr->inv_ray_tiles_x);
+    int tx = local - ty * tiles_x;
+    if (tx < 0) { --ty; tx += tiles_x; }
+    if (tx >= tiles_x) { ++ty; tx -= tiles_x; }
+    constexpr int tw = ray_tile_w(P), th = ray_tile_h(P);
+    const int pix = (int)threadIdx.x / P;   // P lanes per pixel
+    const int u = tx * tw + pix % tw, v = ty * th + pix / tw;
+    if (u < Fr->out_w && v < Fr->out_h) raycast_pixel<P>(L, H, s, u, v, (int)threadIdx.x % P);
+    if (L.tile_cost && threadIdx.x == 0) {
+        const unsigned long long d = wall_clock64() - t_tile;
+        L.tile_cost[tile] = d < 0xffffffffull ? (uint32_t)d : 0xffffffffu;
     }
 }
 
 template <int P>
-static __host__ __device__ void raycast_pixel(const RaycastLaunch& L, const LaunchHeader& H, int s, int u, int v,
-                                              int j)
+static __device__ void raycast_pixel(const RaycastLaunch& L, CPTR(LaunchHeader) H, int s, int u, int v, int j)
 {
-    const DevFrame Fr = cptr(L.frames)[s];
-    const size_t p = (size_t)v * Fr.out_w + u;
+    // fields are read where they are used: the output pointers, loaded with the
+    // rest of the frame, would hold scalar registers through the march
+    CPTR(DevFrame) const Fr = cptr(L.frames) + s;
+    const size_t p = (size_t)v * Fr->out_w + u;
 
     // ray (binary32 contract)
     Ray r;
     float dh[3];
     {
-        const float dc0 = ((float)u - Fr.cx) / Fr.fx;
-        const float dc1 = ((float)v - Fr.cy) / Fr.fy;
+        const float dc0 = ((float)u - Fr->cx) / Fr->fx;
+        const float dc1 = ((float)v - Fr->cy) / Fr->fy;
         const float n = sqrtf(((dc0 * dc0) + (dc1 * dc1)) + (1.0f * 1.0f));
         const float inv_n = 1.0f / n;
         dh[0] = dc0 * inv_n;
@@ -1664,18 +1558,18 @@ static __host__ __device__ void raycast_pixel(const RaycastLaunch& L, const Laun
         dh[2] = 1.0f * inv_n;
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-            r.dw[a] = ((Fr.T[4 * a + 0] * dh[0]) + (Fr.T[4 * a + 1] * dh[1])) + (Fr.T[4 * a + 2] * dh[2]);
-            r.C[a] = Fr.T[4 * a + 3];
+            r.dw[a] = ((Fr->T[4 * a + 0] * dh[0]) + (Fr->T[4 * a + 1] * dh[1])) + (Fr->T[4 * a + 2] * dh[2]);
+            r.C[a] = Fr->T[4 * a + 3];
             r.inv_dw[a] = approx_rcp(r.dw[a]);
         }
-        r.inv_delta = approx_rcp(H.rp.delta);
+        r.inv_delta = approx_rcp(H->rp.delta);
         // the range bounds of the pixel's cell and of the whole image
         r.t_lo = 0.0f;
         r.t_hi = pinf();
-        if (Fr.rb_lo) {
-            const int cell = (v / kBoundCell) * Fr.cells_x + u / kBoundCell;
-            r.t_lo = Fr.rb_lo[cell];
-            r.t_hi = Fr.rb_hi[cell];
+        if (Fr->rb_lo) {
+            const int cell = (v / kBoundCell) * Fr->cells_x + u / kBoundCell;
+            r.t_lo = Fr->rb_lo[cell];
+            r.t_hi = Fr->rb_hi[cell];
         }
     }
     float best_t = pinf();
@@ -1683,21 +1577,16 @@ static __host__ __device__ void raycast_pixel(const RaycastLaunch& L, const Laun
     int best_vol = -1;
     int best_k = -1;
     int best_cell[3] = {0, 0, 0};
-    if (!H.first_wave) {
-        const int prev = Fr.best_id[p];
-        if (prev >= 0) { best_t = Fr.best_t[p]; best_id = prev; }
+    if (!H->first_wave) {
+        const int prev = Fr->best_id[p];
+        if (prev >= 0) { best_t = Fr->best_t[p]; best_id = prev; }
     }
     const int l0 = cptr(L.list_base)[s], l1 = cptr(L.list_base)[s + 1];
     for (int li = l0; li < l1; ++li) {
         const DevVolume V = cptr(L.vols)[cptr(L.lists)[li]];
         float ts;
         int ks, cell[3];
-#if defined(__HIP_DEVICE_COMPILE__)
-        const bool found = march_volume_group<P>(V, r, H.rp.delta, H.rp.kmax, best_t, best_id, ts, ks, cell, j);
-#else
-        const bool found = march_volume(V, r, H.rp.delta, H.rp.kmax, best_t, best_id, ts, ks, cell);
-#endif
-        if (found) {
+        if (march_volume_group<P>(V, r, H->rp.delta, H->rp.kmax, best_t, best_id, ts, ks, cell, j)) {
             best_t = ts;
             best_id = V.id;
             best_k = ks;
@@ -1707,25 +1596,32 @@ static __host__ __device__ void raycast_pixel(const RaycastLaunch& L, const Laun
     }
     if (j != 0) return;   // the group's first lane writes the pixel
     if (best_vol >= 0) {
-        const DevVolume V = cptr(L.vols)[best_vol];
         float x[3], n[3];
 #pragma unroll
         for (int a = 0; a < 3; ++a) x[a] = r.C[a] + (best_t * r.dw[a]);
-        surface_normal(V, x, best_cell, n);
-        Fr.depth[p] = best_t * dh[2];
-        if (Fr.vertex) { Fr.vertex[3 * p] = x[0]; Fr.vertex[3 * p + 1] = x[1]; Fr.vertex[3 * p + 2] = x[2]; }
-        if (Fr.normal) { Fr.normal[3 * p] = n[0]; Fr.normal[3 * p + 1] = n[1]; Fr.normal[3 * p + 2] = n[2]; }
-        if (Fr.hit) Fr.hit[p] = V.id;
-        if (Fr.record) Fr.record[p] = best_k;
-        if (Fr.best_t) { Fr.best_t[p] = best_t; Fr.best_id[p] = best_id; }
-    } else if (H.first_wave) {
+        // volume by volume of the wavefront's pixels (most often one), its table
+        // entry in scalar registers
+        for (bool todo = true; todo;) {
+            const int vi = wave_uniform(best_vol);
+            if (best_vol == vi) {
+                surface_normal(cptr(L.vols)[vi], x, best_cell, n);
+                todo = false;
+            }
+        }
+        Fr->depth[p] = best_t * dh[2];
+        if (Fr->vertex) { Fr->vertex[3 * p] = x[0]; Fr->vertex[3 * p + 1] = x[1]; Fr->vertex[3 * p + 2] = x[2]; }
+        if (Fr->normal) { Fr->normal[3 * p] = n[0]; Fr->normal[3 * p + 1] = n[1]; Fr->normal[3 * p + 2] = n[2]; }
+        if (Fr->hit) Fr->hit[p] = best_id;
+        if (Fr->record) Fr->record[p] = best_k;
+        if (Fr->best_t) { Fr->best_t[p] = best_t; Fr->best_id[p] = best_id; }
+    } else if (H->first_wave) {
         const float qn = qnan();
-        Fr.depth[p] = 0.0f;
-        if (Fr.vertex) { Fr.vertex[3 * p] = qn; Fr.vertex[3 * p + 1] = qn; Fr.vertex[3 * p + 2] = qn; }
-        if (Fr.normal) { Fr.normal[3 * p] = qn; Fr.normal[3 * p + 1] = qn; Fr.normal[3 * p + 2] = qn; }
-        if (Fr.hit) Fr.hit[p] = -1;
-        if (Fr.record) Fr.record[p] = -1;
-        if (Fr.best_t) { Fr.best_t[p] = pinf(); Fr.best_id[p] = -1; }
+        Fr->depth[p] = 0.0f;
+        if (Fr->vertex) { Fr->vertex[3 * p] = qn; Fr->vertex[3 * p + 1] = qn; Fr->vertex[3 * p + 2] = qn; }
+        if (Fr->normal) { Fr->normal[3 * p] = qn; Fr->normal[3 * p + 1] = qn; Fr->normal[3 * p + 2] = qn; }
+        if (Fr->hit) Fr->hit[p] = -1;
+        if (Fr->record) Fr->record[p] = -1;
+        if (Fr->best_t) { Fr->best_t[p] = pinf(); Fr->best_id[p] = -1; }
     }
 }
 
@@ -1741,7 +1637,6 @@ static void launch_raycast_p(const RaycastLaunch& L, int blocks, hipStream_t str
 int launch_raycast(const RaycastLaunch& L, int blocks, void* stream, void* ev_start, void* ev_stop)
 {
     if (blocks <= 0) return 0;
-    if (ray_tile_w(L.lanes) != L.tile_w || ray_tile_h(L.lanes) != L.tile_h) return (int)hipErrorInvalidValue;
     hipStream_t s = (hipStream_t)stream;
     hipEvent_t a = (hipEvent_t)ev_start, b = (hipEvent_t)ev_stop;
     switch (L.lanes) {

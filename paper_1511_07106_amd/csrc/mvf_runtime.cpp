@@ -430,6 +430,11 @@ DevVolume make_dev(mvf_ctx* c, const Volume& v)
     d.inv_mu = g.inv_mu;
     d.w_max = g.d.w_max;
     d.frame = 0;
+    for (int a = 0; a < 3; ++a) {
+        const double o = g.d.origin[a], vs = g.d.voxel_size;
+        d.ray_lo[a] = (float)(o + vs * (v.d.offset[a] - 0.5));
+        d.ray_hi[a] = (float)(o + vs * ((double)v.d.offset[a] + v.d.dims[a] + 0.5));
+    }
     return d;
 }
 
@@ -808,8 +813,13 @@ mvf_status get_footprint_buffers(RayBoundEntry** entries, int* entries_cap, uint
     return MVF_OK;
 }
 
-void set_bounds(DevFrame* f, const Scratch* s, int w, int h)
+// The raycast side of a frame: output size, tile grid and range bounds.
+void set_output(DevFrame* f, const Scratch* s, int w, int h, int lanes)
 {
+    f->out_w = w;
+    f->out_h = h;
+    f->ray_tiles_x = (w + ray_tile_w(lanes) - 1) / ray_tile_w(lanes);
+    f->inv_ray_tiles_x = 1.0f / (float)f->ray_tiles_x;
     f->rb_lo = s->rb_lo;
     f->rb_hi = s->rb_hi;
     f->cells_x = (w + kBoundCell - 1) / kBoundCell;
@@ -1103,13 +1113,11 @@ mvf_status raycast_plain(mvf_ctx* c, int sid, const float* T, const mvf_intrinsi
         fr->normal = out->normal;
         fr->hit = out->hit;
         fr->record = record;
-        fr->out_w = out->width;
-        fr->out_h = out->height;
         if (multi) {
             fr->best_t = sc->best_t;
             fr->best_id = sc->best_id;
         }
-        set_bounds(fr, sc, out->width, out->height);
+        set_output(fr, sc, out->width, out->height, kRayLanes);
         // footprint regions: the wave's bricks, 64-aligned per volume
         int32_t* dbb;
         int32_t* bb = w.alloc<int32_t>(wave.size() + 1, &dbb);
@@ -1137,7 +1145,7 @@ mvf_status raycast_plain(mvf_ctx* c, int sid, const float* T, const mvf_intrinsi
         sc->rb_parity ^= 1;
         CHECK_ST(arena_upload(c, w, stream));
         // slowest tiles of the stream's last raycast first
-        RaycastLaunch L{dh, dvols, dfr, dlists, dlb, dtb, tw, th, kRayLanes, sc->tile_cost, sc->tile_order};
+        RaycastLaunch L{dh, dvols, dfr, dlists, dlb, dtb, kRayLanes, sc->tile_cost, sc->tile_order};
         hipEvent_t t0, t1;
         CHECK_ST(timing_pair(c, &t0, &t1));
         const RayBounds RB{sc->rb_entries, sc->rb_counts, sc->rb_counts_cap};
@@ -2122,14 +2130,12 @@ mvf_status mvf_step(mvf_ctx* c, int32_t n, const mvf_stream_frame* frames, const
             p.rmax = sc[i]->rmax;
             p.tmax = sc[i]->tmax;
             fill_frame(&dfr[i], sc[i], fr.frame.width, fr.frame.height, fr.T_wc, fr.K);
-            set_bounds(&dfr[i], sc[i], outs[i].width, outs[i].height);
+            set_output(&dfr[i], sc[i], outs[i].width, outs[i].height, sch.ray_lanes);
             if (!fr.frame.rgb) dfr[i].color = nullptr;
             dfr[i].depth = outs[i].depth;
             dfr[i].vertex = outs[i].vertex;
             dfr[i].normal = outs[i].normal;
             dfr[i].hit = outs[i].hit;
-            dfr[i].out_w = outs[i].width;
-            dfr[i].out_h = outs[i].height;
             if (multi_wave) {
                 dfr[i].best_t = sc[i]->best_t;
                 dfr[i].best_id = sc[i]->best_id;
@@ -2206,7 +2212,7 @@ mvf_status mvf_step(mvf_ctx* c, int32_t n, const mvf_stream_frame* frames, const
             const RayBounds RB{G.rb_entries, G.rb_counts, G.max_vols};
             if (!e2) e2 = launch_brick_distance(dh, dvols, dbb, c->n_cus * 4, cs, dframes, RB);
             if (!e2) e2 = launch_ray_bounds_merge(dh, dframes, dlists, dlb, dbb, RB, n, G.max_cells_x, G.max_cells_y, cs);
-            RaycastLaunch RL{dh, dvols, dframes, dlists, dlb, dtb, tw, th, sch.ray_lanes, G.tile_cost, G.tile_order};
+            RaycastLaunch RL{dh, dvols, dframes, dlists, dlb, dtb, sch.ray_lanes, G.tile_cost, G.tile_order};
             int e3 = e2 ? e2 : launch_raycast(RL, G.ray_blocks, cs);
             hipError_t ee = hipStreamEndCapture(cs, &G.graph);
             if (e3) return set_error(MVF_ERR_HIP, "step capture: %s", hipGetErrorString((hipError_t)e3));
