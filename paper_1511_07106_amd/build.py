@@ -25,12 +25,16 @@ SELFTEST_SRC = "mvf_selftest.hip"
 SELFTEST_LIB = os.path.join(PKG, "libmvf_selftest.so")
 
 # Numeric contract: no contraction of a*b+c into FMA, IEEE division and
-# square root, denormals kept.  Packed FP32 instructions are disabled.
+# square root, denormals kept.  Packed FP32 instructions are disabled, and so
+# is the pairing of scalar operations into vectors: without the packed
+# instructions it computes both halves of a pair twice (raycast of 16 volumes
+# of 256^3: 655 us with it, 645 without; of 128^3 at 320x240: 29.4 and 27.3 us;
+# the other kernels the same).
 COMMON = [
     "-O3", "-fPIC", "-std=c++17", "-ffp-contract=off", "-fno-fast-math",
     "-fhip-fp32-correctly-rounded-divide-sqrt", "-fno-gpu-flush-denormals-to-zero",
     f"--offload-arch={ARCH}",
-    "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-fno-slp-vectorize",
     "-Wall", "-Wno-unused-result",
     f"-I{INCLUDE}", f"-I{CSRC}",
 ]

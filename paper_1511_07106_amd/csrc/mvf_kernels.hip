@@ -1495,8 +1495,8 @@ static __device__ void raycast_pixel(const RaycastLaunch& L, CPTR(LaunchHeader) 
 // 75).  So what counts is instructions per round and per tile: no loop over
 // tiles, the tile from reciprocals, the ray box's slabs and the skip boxes
 // without a case per direction, the group's exchanges as cross-lane operands,
-// table fields read where they are used.  106 us before these, 76 us after;
-// 1001 -> 655 us for 16 volumes of 256^3, 41 -> 29 us for 128^3 at 320 x 240.
+// table fields read where they are used.  106 us before these, 75 us after;
+// 1001 -> 645 us for 16 volumes of 256^3, 41 -> 27 us for 128^3 at 320 x 240.
 // Not taken: one lane testing two bricks a round (93 us), all of a tile's rays
 // skipping before any evaluates (its longest tile 95 -> 271 us), slow tiles
 // split into ray segments (101-142 us).
