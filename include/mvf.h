@@ -282,8 +282,9 @@ mvf_status mvf_step(mvf_ctx* ctx, int32_t n, const mvf_stream_frame* frames,
  *   zchunk            bricks per integration work item along z: 1, 2, 4 or 8
  *   persistent        0: one integration wavefront per work item;
  *                     1: 8 wavefronts per SIMD walking the items
- *   ray_lanes         lanes that march one ray together: 2, 4 or 8 (pixel
- *                     tiles 8x4, 4x4, 4x2)
+ *   ray_lanes         2, 4 or 8: how many lanes march one ray together, at
+ *                     most 16 and more the higher this is (chosen for each 8x8
+ *                     pixel tile by what it took in the last step)
  * Default {4, 0, 4}. */
 typedef struct {
     int32_t zchunk;

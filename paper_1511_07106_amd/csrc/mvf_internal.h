@@ -105,8 +105,7 @@ struct DevFrame {
     int32_t* best_id;
     int32_t* record;         // per pixel: k of the nearest crossing's second sample, -1 = none; or null
     int32_t out_w, out_h;
-    int32_t ray_tiles_x;     // raycast pixel tiles per row of the output
-    float inv_ray_tiles_x;   // its reciprocal (rounded; the kernel corrects the quotient)
+    float inv_cells_x;       // 1 / cells_x (rounded; the kernel corrects the quotient)
     // raycast range bounds per 8x8 output-pixel cell (cells_x * cells_y,
     // row-major), or null: the nearest and farthest camera distance of any
     // sample the march may have to evaluate; a cell no brick reaches holds
@@ -184,6 +183,46 @@ struct PrepItem {
 // (x_w(z) - T[11]), the camera-frame offset of the voxel plane z (binary32,
 // the same operations as the voxel test).  Written by launch_ztable before
 // the integration kernel runs; ztab holds >= hdr->total_z entries.
+// The raycast's work: pixel tiles of 8x8 (one range-bound cell each), each
+// marched by 2^level one-wavefront blocks of 64 >> level pixels, 2^level lanes
+// per ray.  More lanes per ray make a tile's longest chain of rounds shorter
+// and its work larger, so the level is chosen tile by tile (TileOrder).
+constexpr int kRayTile = 8;
+constexpr int kRayLevels = 5;
+constexpr int kBoundCell = kRayTile;   // output pixels per side of a raycast range-bound cell
+constexpr int kXcds = 8;
+// pixels of a block of a level: 8x8, 8x4, 4x4, 4x2, 2x2
+MVF_HD constexpr int ray_block_w(int level) { return kRayTile >> (level / 2); }
+MVF_HD constexpr int ray_block_h(int level) { return kRayTile >> ((level + 1) / 2); }
+// Default of the schedule's ray_lanes.
+constexpr int kRayLanes = 4;
+// Blocks that a launch order may take beyond its tiles' own (each level's tiles
+// are rounded to whole windows of kXcds: less than 8 * 31).
+constexpr int kRaySlack = 512;
+// Wavefronts of the raycast kernel that a compute unit holds.
+constexpr int kRayWavesPerCu = 20;
+
+// A launch order to compute for that many raycast tiles from their last
+// durations, longest first (a slow tile started late bounds the launch), with
+// each tile's level; tiles 0: none.  The order begins with a RayPlan.  Block
+// of the launch -> (tile, part): from block[level] on, 8 tiles at a time (one
+// per XCD, over which blocks are dealt round-robin), all the parts of a tile
+// on one XCD (they gather the same bricks).
+struct RayPlan {
+    int32_t pos[8];     // first position in the order of each level (higher levels come first)
+    int32_t block[8];   // its first block; [kRayLevels]: the number of blocks
+};
+constexpr int kRayPlanInts = 16;
+struct TileOrder {
+    uint32_t* cost;     // per tile: its longest block in the last launch, scaled to level 0; zeroed by the ordering
+    int32_t* order;     // RayPlan, then the tiles
+    int32_t tiles;
+    int32_t level;      // of every tile when a duration is missing
+    int32_t max_blocks; // of the raycast launch
+    int32_t slots;      // wavefronts the device holds
+    int32_t fresh;      // ignore the durations (of another image size)
+};
+
 struct IntegrateLaunch {
     const LaunchHeader* hdr;
     const DevVolume* vols;
@@ -195,11 +234,9 @@ struct IntegrateLaunch {
     // item may hold a voxel the frame updates (written by the z-table
     // launch), or null (visit all); needs zchunk <= kVisitPerItem
     uint8_t* visit;
-    // optional: block 0 computes a raycast tile order (see TileOrder) from
-    // these costs instead of integrating; the grid has one more block
-    const uint32_t* tile_cost;
-    int32_t* tile_order;
-    int32_t order_tiles;
+    // optional (tiles > 0): block 0 computes a raycast tile order instead of
+    // integrating; the grid has one more block
+    TileOrder order;
     // visited work, compacted (needs visit): the z-table launch appends
     // every brick to visit voxel by voxel to list and every deep brick (each
     // voxel updated with phi = 1, proved by the visit test) to deep_list,
@@ -215,22 +252,6 @@ struct IntegrateLaunch {
 };
 constexpr int kVisitPerItem = 8;
 
-// Lanes that march one ray together in the raycast kernel (P consecutive
-// samples per round of gathers: 2, 4 or 8), and the pixel tile of a
-// 64-lane block for each (8x4, 4x4, 4x2).  kRayLanes is the default.
-constexpr int kRayLanes = 4;
-MVF_HD constexpr int ray_tile_w(int lanes) { return lanes == 2 ? 8 : 4; }
-MVF_HD constexpr int ray_tile_h(int lanes) { return 64 / lanes / ray_tile_w(lanes); }
-constexpr int kBoundCell = 8;   // output pixels per side of a raycast range-bound cell (a ray tile lies in one)
-// Raycast launch order: groups of kRayGroup consecutive tiles are ordered by
-// their summed last duration, slowest first.  Blocks are dealt round-robin
-// over the 8 XCDs, so a window of 8 * kRayGroup blocks takes 8 groups, each
-// group's tiles on one XCD (they gather the same bricks).
-constexpr int kRayGroup = 4;
-constexpr int kXcds = 8;
-MVF_HD int ray_groups(int tiles) { return (tiles + kRayGroup - 1) / kRayGroup; }
-MVF_HD int ray_blocks(int tiles) { return (ray_groups(tiles) + kXcds - 1) / kXcds * kXcds * kRayGroup; }
-
 struct RaycastLaunch {
     const LaunchHeader* hdr;
     const DevVolume* vols;      // table
@@ -238,9 +259,8 @@ struct RaycastLaunch {
     const int32_t* lists;       // concatenated per-stream lists of table indices, nearest first
     const int32_t* list_base;   // per stream: [list_base[s], list_base[s+1])
     const int32_t* tile_base;   // per stream: first pixel tile; nstreams + 1 entries
-    int32_t lanes;              // lanes per ray (2, 4 or 8); pixel tile: ray_tile_w(lanes) x ray_tile_h(lanes)
-    uint32_t* tile_cost;        // per tile: its duration in the last launch (10 ns ticks), or null
-    const int32_t* tile_order;  // tile groups in launch order, or null (index order)
+    uint32_t* tile_cost;        // TileOrder::cost, zero before the launch
+    const int32_t* tile_order;  // TileOrder::order
 };
 
 // Host-side launchers (defined in mvf_kernels.hip).  All return hipError_t
@@ -261,21 +281,13 @@ int launch_volume_init(DevVolume v, void* stream);
 int launch_ztable(const IntegrateLaunch& L, int bricks, void* stream);
 // Integration kernel: blocks of 256 threads, 4 items in flight per block; a
 // grid smaller than total_items / 4 walks the items (plus block 0 when
-// L.tile_order is set).
+// L.order.tiles is set).
 // With ev_start/ev_stop (hipEvent_t) the kernel's own dispatch records them.
 int launch_integrate(const IntegrateLaunch& L, int blocks, void* stream, void* ev_start = nullptr,
                      void* ev_stop = nullptr);
-// Raycast kernel; blocks: ray_blocks(total tiles).
+// Raycast kernel; blocks: TileOrder::max_blocks.
 int launch_raycast(const RaycastLaunch& L, int blocks, void* stream, void* ev_start = nullptr,
                    void* ev_stop = nullptr);
-// A launch order to compute for the ray_groups(tiles) groups of that many
-// raycast tiles from their last durations, longest first (a slow tile started
-// late bounds the launch); tiles 0: none.
-struct TileOrder {
-    const uint32_t* cost;
-    int32_t* order;
-    int32_t tiles;
-};
 // Column flag words from the brick flags.
 int launch_column_flags(DevVolume v, void* stream);
 // Brick distance transform of every volume in the table (3 passes).

@@ -202,62 +202,144 @@ int launch_volume_init(DevVolume v, void* stream)
 }
 
 // ---------------------------------------------------------------------------
-// Launch order of the raycast tile groups: counting sort of their summed
-// last durations, longest first, by half octaves (the leading two bits).
-// Run by one block of any size: each thread takes kOrderBatch groups per
+// Launch order of the raycast's tiles and each tile's level, from their last
+// durations t (the longest block of a tile or of one next to it, scaled to
+// level 0): a counting sort, longest first, by quarter octaves.  The levels
+// follow from a bound on a block's duration, a tile taking the lowest level
+// that keeps it, and the bound is the one for which kOrderTail times itself
+// plus the whole work, shared by all the wavefronts that the device holds, is
+// smallest.  (Any kOrderTail from 0.3 to 0.6 is as good: 128^3 at 320 x 240
+// 21.5 us, one 512^3 volume at 640 x 480 46; with 1 it is 40 and 49, with 4
+// 40 and 68.  Bounds by half octaves: 55 for 50 us.  Durations of the tile
+// alone, without its neighbours: 78 us for 55, since a tile that was quick and
+// became slow at a low level ends the launch late.)
+// Run by one block of any size: each thread takes kOrderBatch tiles per
 // round with all their loads in flight, and counts and places them with
 // LDS atomics (aggregating a wavefront's lanes per bin with ballots first
 // serialised the block: up to ~90 us per order in the integration launch's
-// block 0, longer than the integration it runs beside).  The cost array holds
-// ray_groups(n) * kRayGroup entries (zero past n).
+// block 0, longer than the integration it runs beside).
 constexpr int kOrderBins = 64;
-constexpr int kOrderBatch = 4;
+constexpr int kOrderBatch = 8;
+constexpr float kOrderTail = 0.5f;
+constexpr int kOrderFloor = 1;   // levels below the uniform one that a tile may take
 
-static __device__ __forceinline__ int cost_bin(uint4 c)
+// Duration of a tile's longest block at level 0 over that at a level
+static __device__ __forceinline__ float ray_speedup(int level)
 {
-    const uint64_t t = (uint64_t)c.x + c.y + c.z + c.w;
-    if (t < 2) return (int)t;
-    const int e = 63 - __clzll(t);
-    return min(2 * e + (int)((t >> (e - 1)) & 1), kOrderBins - 1);
+    return level == 0 ? 1.0f : level == 1 ? 1.6f : level == 2 ? 2.4f : level == 3 ? 3.7f : 4.6f;
+}
+// the lowest level that keeps a tile of duration e at level 0 within th
+static __device__ __forceinline__ int ray_level(float e, float th, int least)
+{
+    int l = 0;
+#pragma unroll
+    for (int q = 0; q < kRayLevels - 1; ++q) l += e > th * ray_speedup(q) ? 1 : 0;
+    return max(l, least);
+}
+// the summed durations of such a tile's blocks at a level: 300 ticks for each, and
+// what grows with the rounds
+static __device__ __forceinline__ float ray_work(float e, int level)
+{
+    const float g = level == 0 ? 1.0f : level == 1 ? 1.5f : level == 2 ? 1.8f : level == 3 ? 2.15f : 2.7f;
+    return 300.0f * (float)(1 << level) + fmaxf(e - 300.0f, 0.0f) * g;
 }
 
-static __device__ void tile_order_block(const uint32_t* __restrict__ cost, int32_t* __restrict__ order, int ntiles,
-                                        int* hist)
+// 0: not known; 1..63: quarter octaves from 16 ticks (0.16 us) to 10 ms
+static __device__ __forceinline__ int cost_bin(uint32_t t)
 {
-    static_assert(kRayGroup == 4, "one uint4 of costs per group");
-    const int ng = ray_groups(ntiles);
+    if (t == 0) return 0;
+    const int e = 31 - __builtin_clz(max(t, 16u));
+    return min(4 * (e - 4) + (int)(max(t, 16u) >> (e - 2) & 3u) + 1, kOrderBins - 1);
+}
+
+static __device__ __forceinline__ float bin_middle(int b)
+{
+    return b == 0 ? 0.0f : (1.125f + 0.25f * (float)((b - 1) & 3)) * (float)(16u << ((b - 1) >> 2));
+}
+
+// hist: kOrderBins words of LDS
+static __device__ void tile_order_block(const TileOrder& O, int* hist)
+{
     const int nt = blockDim.x;
-    const uint4* c4 = reinterpret_cast<const uint4*>(cost);
+    RayPlan* const plan = reinterpret_cast<RayPlan*>(O.order);
+    int32_t* const order = O.order + kRayPlanInts;
     for (int i = threadIdx.x; i < kOrderBins; i += nt) hist[i] = 0;
     __syncthreads();
+    uint32_t c[kOrderBatch];
     for (int pass = 0; pass < 2; ++pass) {
-        for (int g0 = 0; g0 < ng; g0 += kOrderBatch * nt) {
-            uint4 c[kOrderBatch];
+        for (int g0 = 0; g0 < O.tiles; g0 += kOrderBatch * nt) {
+            // (a single round's costs stay in registers)
+            if (pass == 0 || O.tiles > kOrderBatch * nt) {
 #pragma unroll
-            for (int k = 0; k < kOrderBatch; ++k) {
-                const int g = g0 + k * nt + (int)threadIdx.x;
-                c[k] = g < ng ? c4[g] : make_uint4(0, 0, 0, 0);
+                for (int k = 0; k < kOrderBatch; ++k) {
+                    const int g = g0 + k * nt + (int)threadIdx.x;
+                    c[k] = g < O.tiles && !O.fresh ? O.cost[g] : 0;
+                }
             }
 #pragma unroll
             for (int k = 0; k < kOrderBatch; ++k) {
                 const int g = g0 + k * nt + (int)threadIdx.x;
-                if (g >= ng) continue;
+                if (g >= O.tiles) continue;
                 const int bin = cost_bin(c[k]);
                 // the place within a bin is the atomics' order (the launch
                 // order only steers the timing)
-                if (pass == 0) atomicAdd(&hist[bin], 1);
-                else order[atomicAdd(&hist[bin], 1)] = g;
+                if (pass == 0) {
+                    atomicAdd(&hist[bin], 1);
+                } else {
+                    order[atomicAdd(&hist[bin], 1)] = g;
+                    O.cost[g] = 0;
+                }
             }
         }
         __syncthreads();
-        if (pass == 0 && threadIdx.x == 0) {
-            // start of each bin, longest first
-            int acc = 0;
-            for (int b = kOrderBins - 1; b >= 0; --b) {
-                const int h = hist[b];
-                hist[b] = acc;
-                acc += h;
+        if (pass == 0 && threadIdx.x < 64) {
+            // lane b: bin 63 - b, so that the longest come first
+            const int lane = threadIdx.x, b = kOrderBins - 1 - lane;
+            const int n = hist[b];
+            const bool unknown = hist[0] > 0;
+            const int floor_level = max(O.level - kOrderFloor, 0);
+            // lane c weighs the bound bin_middle(c)
+            const float th = bin_middle(lane);
+            float work = 0.0f, blocks = 0.0f;
+            for (unsigned long long some = __ballot(n > 0); some; some &= some - 1) {
+                const int q = __builtin_ctzll(some);
+                const float m = (float)__builtin_amdgcn_readlane(n, q), e = bin_middle(kOrderBins - 1 - q);
+                const int l = ray_level(e, th, floor_level);
+                work += m * ray_work(e, l);
+                blocks += m * (float)(1 << l);
             }
+            float best = blocks <= (float)(O.max_blocks - kRaySlack) ? kOrderTail * th * (float)O.slots + work : INFINITY;
+            int at = lane;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const float y = __shfl_xor(best, o);
+                const int z = __shfl_xor(at, o);
+                if (y < best || (y == best && z < at)) { best = y; at = z; }
+            }
+            const int level = unknown ? O.level : best < INFINITY ? ray_level(bin_middle(b), bin_middle(at), floor_level) : floor_level;
+            // positions: exclusive sums over the lanes
+            int sum = n;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int y = __shfl_up(sum, o);
+                if (lane >= o) sum += y;
+            }
+            hist[b] = sum - n;
+            // first position of each level, on a whole window of tiles
+            int pos = 0, blk = 0;
+#pragma unroll
+            for (int l = kRayLevels - 1; l >= 0; --l) {
+                if (lane == 0) { plan->pos[l] = pos; plan->block[l] = blk; }
+                // tiles at this level or above
+                const unsigned long long m = __ballot(level >= l);
+                const int upto = l == 0 ? O.tiles : m ? __shfl(sum, 63 - __builtin_clzll(m)) : 0;
+                const int end = min((upto + kXcds - 1) / kXcds * kXcds, O.tiles);
+                if (end > pos) {
+                    blk += (end - pos + kXcds - 1) / kXcds * kXcds << l;
+                    pos = end;
+                }
+            }
+            if (lane == 0) plan->block[kRayLevels] = blk;
         }
         __syncthreads();
     }
@@ -419,10 +501,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void m
 {
     // with a tile order to compute (captured step), block 0 sorts the next
     // raycast's tile groups while the others integrate
-    const int b0 = L.tile_order ? 1 : 0;
+    const int b0 = L.order.tiles > 0 ? 1 : 0;
     if ((int)blockIdx.x < b0) {
         __shared__ int hist[kOrderBins];
-        tile_order_block(L.tile_cost, L.tile_order, L.order_tiles, hist);
+        tile_order_block(L.order, hist);
         return;
     }
     const int lane = threadIdx.x & 63;
@@ -1297,27 +1379,33 @@ static __device__ __forceinline__ int skip_run(const DevVolume& V, const float l
     return max((int)m, 1);
 }
 
-// Exchanges within the P lanes of a group: cross-lane operands where a group
-// lies in four lanes (an LDS exchange takes its whole latency in every round).
-template <int P, int Op>
-static __device__ __forceinline__ int group_move(int x, int gbase)
+// Exchanges within the P lanes of a group, as cross-lane operands (an LDS
+// exchange takes its whole latency in every round).
+template <int Ctrl>
+static __device__ __forceinline__ int lane_move(int x)
 {
-    // Op 0: lane ^ 1, 1: lane ^ 2, 2: the lane before (the first keeps its own), 3: the last lane
-    constexpr int quad = Op == 0 ? 0xb1 : Op == 1 ? 0x4e : Op == 2 ? (P == 2 ? 0xa0 : 0x90) : (P == 2 ? 0xf5 : 0xff);
-    if (P <= 4) return __builtin_amdgcn_update_dpp(x, x, quad, 0xf, 0xf, true);
-    if (Op == 0) return __shfl_xor(x, 1);
-    if (Op == 1) return __shfl_xor(x, 2);
-    if (Op == 2) return __shfl_up(x, 1, P);
-    return __shfl(x, gbase + P - 1);
+    return __builtin_amdgcn_update_dpp(x, x, Ctrl, 0xf, 0xf, true);
 }
 
 template <int P>
-static __device__ __forceinline__ int group_max(int x, int gbase)
+static __device__ __forceinline__ int group_max(int x)
 {
-    x = max(x, group_move<P, 0>(x, gbase));
-    if (P > 2) x = max(x, group_move<P, 1>(x, gbase));
-    if (P > 4) x = max(x, __shfl_xor(x, 4));
+    if (P > 1) x = max(x, lane_move<0xb1>(x));      // lane ^ 1
+    if (P > 2) x = max(x, lane_move<0x4e>(x));      // lane ^ 2
+    if (P > 4) x = max(x, lane_move<0x141>(x));     // the other four of eight
+    if (P > 8) x = max(x, lane_move<0x140>(x));     // the other eight of sixteen
     return x;
+}
+
+// the value of the lane before (the group's first lane does not use it)
+static __device__ __forceinline__ int lane_before(int x) { return lane_move<0x111>(x); }
+
+// the value of the group's last lane, for its first
+template <int P>
+static __device__ __forceinline__ int last_to_first(int x)
+{
+    if (P == 1) return x;
+    return lane_move<P == 2 ? 0xf5 : P == 4 ? 0xff : P == 8 ? 0x141 : 0x140>(x);
 }
 
 // March one volume with the P lanes of a group (lane j of the group; all P
@@ -1330,7 +1418,8 @@ static __device__ __forceinline__ int group_max(int x, int gbase)
 // exactly as the sequential march would find it.  When the sample before
 // the round was not evaluated, w0 is that sample so that it serves as the
 // near end.  Rays that graze a surface evaluate long stretches of samples;
-// two windows a round halve their rounds of dependent loads.
+// two windows a round halve their rounds of dependent loads (measured at every
+// P: one window and four were slower, by 10-40 %).
 constexpr int kEvalWindows = 2;
 
 template <int P>
@@ -1375,14 +1464,14 @@ static __device__ bool march_volume_group(const DevVolume& V, const Ray& r, floa
             reach = jump ? sk + jump : kMust;
         }
         // the window's samples lie in overlapping clear runs
-        const int clear = group_max<P>(reach, gbase);
+        const int clear = group_max<P>(reach);
         if (clear != kMust) {
             k = clear;
             continue;
         }
         // on to the first sample that must be evaluated, from the one before it
         // on unless that has been evaluated
-        k -= group_max<P>(reach == kMust ? -j : -P, gbase);
+        k -= group_max<P>(reach == kMust ? -j : -P);
         const int w0 = (prev_k != k - 1) ? k - 1 : k;
         const int sidx = w0 + j;
         // evaluation round: kEvalWindows windows of P consecutive samples
@@ -1417,17 +1506,17 @@ static __device__ bool march_volume_group(const DevVolume& V, const Ray& r, floa
                 const float Fk = trilinear(cs[w], fs[w]);
                 const int ok = doms[w] && !isnan(Fk);
                 Fs[w] = Fk;
-                float Fn = __int_as_float(group_move<P, 2>(__float_as_int(Fk), gbase));
-                int okn = group_move<P, 2>(ok, gbase);
+                float Fn = __int_as_float(lane_before(__float_as_int(Fk)));
+                int okn = lane_before(ok);
                 if (j == 0) { Fn = Fprev; okn = prev_ok; }
                 Fns[w] = Fn;
                 // the window's last sample is the next one's previous
-                Fprev = __int_as_float(group_move<P, 3>(__float_as_int(Fk), gbase));
-                prev_ok = group_move<P, 3>(ok, gbase);
+                Fprev = __int_as_float(last_to_first<P>(__float_as_int(Fk)));
+                prev_ok = last_to_first<P>(ok);
                 if (sidx + w * P >= k && okn && ok && Fn > 0.0f && Fk <= 0.0f) jc = min(jc, w * P + j);
             }
         }
-        jc = -group_max<P>(-jc, gbase);
+        jc = -group_max<P>(-jc);
         if (jc < S * P) {
             const int wc = jc / P, lc = jc - wc * P;
             float Fn = 0.0f, Fk = 0.0f;
@@ -1485,60 +1574,9 @@ static __device__ void surface_normal(const DevVolume& V, const float x[3], cons
     }
 }
 
-// Pixel (u, v) of stream s; j: lane of the pixel's group.
+// Pixel (u, v) of stream s in range-bound cell `cell`; j: lane of the pixel's group.
 template <int P>
-static __device__ void raycast_pixel(const RaycastLaunch& L, CPTR(LaunchHeader) H, int s, int u, int v, int j);
-
-// Bounds: instruction issue in the bulk, the dependent rounds of the slowest
-// rays at the end (one 512^3 volume at 640 x 480: the tiles' durations sum to
-// 32 us on every resident block, the slowest tile takes 71 us of the launch's
-// 75).  So what counts is instructions per round and per tile: no loop over
-// tiles, the tile from reciprocals, the ray box's slabs and the skip boxes
-// without a case per direction, the group's exchanges as cross-lane operands,
-// table fields read where they are used.  106 us before these, 75 us after;
-// 1001 -> 645 us for 16 volumes of 256^3, 41 -> 27 us for 128^3 at 320 x 240.
-// Not taken: one lane testing two bricks a round (93 us), all of a tile's rays
-// skipping before any evaluates (its longest tile 95 -> 271 us), slow tiles
-// split into ray segments (101-142 us).
-template <int P>
-__global__ __launch_bounds__(64, 5) void mvf_raycast_kernel(RaycastLaunch L)
-{
-    CPTR(LaunchHeader) const H = cptr(L.hdr);
-    // Tile groups are taken in the launch order (the slowest groups of the
-    // last launch first, when an order is given); each block records how
-    // long its tile took.
-    const int total = H->total_tiles, nstreams = H->nstreams;
-    const int win = (int)(blockIdx.x / (kXcds * kRayGroup)), in = (int)(blockIdx.x % (kXcds * kRayGroup));
-    const int k = win * kXcds + in % kXcds;   // position in the order
-    if (k >= ray_groups(total)) return;
-    const int g = L.tile_order ? cptr(L.tile_order)[k] : k;
-    const int tile = g * kRayGroup + in / kXcds;
-    if (tile >= total) return;
-    const unsigned long long t_tile = wall_clock64();
-    CPTR(int32_t) const tile_base = cptr(L.tile_base);
-    int s = 0;
-    while (s + 1 < nstreams && tile_base[s + 1] <= tile) ++s;
-    s = wave_uniform(s);
-    CPTR(DevFrame) const Fr = cptr(L.frames) + s;
-    const int tiles_x = Fr->ray_tiles_x;
-    const int local = tile - tile_base[s];
-    // local / tiles_x: an estimate within one of the quotient, corrected
-    int ty = (int)((float)local * Fr->inv_ray_tiles_x);
-    int tx = local - ty * tiles_x;
-    if (tx < 0) { --ty; tx += tiles_x; }
-    if (tx >= tiles_x) { ++ty; tx -= tiles_x; }
-    constexpr int tw = ray_tile_w(P), th = ray_tile_h(P);
-    const int pix = (int)threadIdx.x / P;   // P lanes per pixel
-    const int u = tx * tw + pix % tw, v = ty * th + pix / tw;
-    if (u < Fr->out_w && v < Fr->out_h) raycast_pixel<P>(L, H, s, u, v, (int)threadIdx.x % P);
-    if (L.tile_cost && threadIdx.x == 0) {
-        const unsigned long long d = wall_clock64() - t_tile;
-        L.tile_cost[tile] = d < 0xffffffffull ? (uint32_t)d : 0xffffffffu;
-    }
-}
-
-template <int P>
-static __device__ void raycast_pixel(const RaycastLaunch& L, CPTR(LaunchHeader) H, int s, int u, int v, int j)
+static __device__ __forceinline__ void raycast_pixel(const RaycastLaunch& L, CPTR(LaunchHeader) H, int s, int cell, int u, int v, int j)
 {
     // fields are read where they are used: the output pointers, loaded with the
     // rest of the frame, would hold scalar registers through the march
@@ -1567,9 +1605,8 @@ static __device__ void raycast_pixel(const RaycastLaunch& L, CPTR(LaunchHeader) 
         r.t_lo = 0.0f;
         r.t_hi = pinf();
         if (Fr->rb_lo) {
-            const int cell = (v / kBoundCell) * Fr->cells_x + u / kBoundCell;
-            r.t_lo = Fr->rb_lo[cell];
-            r.t_hi = Fr->rb_hi[cell];
+            r.t_lo = cptr((const float*)Fr->rb_lo)[cell];
+            r.t_hi = cptr((const float*)Fr->rb_hi)[cell];
         }
     }
     float best_t = pinf();
@@ -1625,26 +1662,91 @@ static __device__ void raycast_pixel(const RaycastLaunch& L, CPTR(LaunchHeader) 
     }
 }
 
-template <int P>
-static void launch_raycast_p(const RaycastLaunch& L, int blocks, hipStream_t stream, hipEvent_t a, hipEvent_t b)
+// Bounds: instruction issue in the bulk, the dependent rounds of the slowest
+// rays at the end.  So what counts is instructions per round and per block:
+// the block's tile from reciprocals, the ray box's slabs and the skip boxes
+// without a case per direction, the group's exchanges as cross-lane operands,
+// table fields read where they are used; and the split of each tile.  P lanes
+// per ray for every tile, one 512^3 volume at 640 x 480 (work on every
+// resident wavefront, longest block; us): P 1: 15, 181; 2: 24, 115; 4: 34, 75;
+// 8: 50, 47; 16: 79, 37.  With few lanes for the many quick tiles and many for
+// the few slow ones the launch takes 50 us on a young map and 46 on a settled
+// one (P = 4 throughout: 75 and 52; with the instructions of an axis by axis
+// march 106 and more); 16 rooms of up to three 384^3 volumes: 426 us (645,
+// 1001), 128^3 at 320 x 240: 22 us (24, 41).
+// Not taken: one lane testing two bricks a round (93 us), all of a tile's rays
+// skipping before any evaluates (its longest tile 95 -> 271 us), slow tiles
+// split into ray segments (101-142 us).
+//
+// A block's part of a tile: 64 >> Level pixels.
+template <int Level>
+static __device__ __forceinline__ void raycast_part(const RaycastLaunch& L, CPTR(LaunchHeader) H, int s, int tx, int ty,
+                                                    int part)
 {
-    if (a)
-        hipExtLaunchKernelGGL(mvf_raycast_kernel<P>, dim3(blocks), dim3(64), 0, stream, a, b, 0, L);
-    else
-        hipLaunchKernelGGL(mvf_raycast_kernel<P>, dim3(blocks), dim3(64), 0, stream, L);
+    CPTR(DevFrame) const Fr = cptr(L.frames) + s;
+    constexpr int P = 1 << Level, bw = ray_block_w(Level), bh = ray_block_h(Level), nx = kRayTile / bw;
+    const int pix = (int)threadIdx.x / P;   // P lanes per pixel
+    const int u = tx * kRayTile + part % nx * bw + pix % bw, v = ty * kRayTile + part / nx * bh + pix / bw;
+    if (u < Fr->out_w && v < Fr->out_h)
+        raycast_pixel<P>(L, H, s, ty * Fr->cells_x + tx, u, v, (int)threadIdx.x % P);
+}
+
+__global__ __launch_bounds__(64, 5) void mvf_raycast_kernel(RaycastLaunch L)
+{
+    CPTR(LaunchHeader) const H = cptr(L.hdr);
+    CPTR(RayPlan) const plan = cptr(reinterpret_cast<const RayPlan*>(L.tile_order));
+    const int b = (int)blockIdx.x;
+    if (b >= plan->block[kRayLevels]) return;
+    int level = 0;
+#pragma unroll
+    for (int l = kRayLevels - 1; l > 0; --l)
+        if (b >= plan->block[l] && b < plan->block[l - 1]) level = l;
+    const int at = b - plan->block[level];
+    const int k = plan->pos[level] + (at >> (3 + level)) * kXcds + at % kXcds;   // position in the order
+    if (k >= H->total_tiles || (level > 0 && k >= plan->pos[level - 1])) return;
+    const int part = (at >> 3) & ((1 << level) - 1);
+    const int tile = cptr(L.tile_order)[kRayPlanInts + k];
+    const unsigned long long t_tile = wall_clock64();
+    const int nstreams = H->nstreams;
+    CPTR(int32_t) const tile_base = cptr(L.tile_base);
+    int s = 0;
+    while (s + 1 < nstreams && tile_base[s + 1] <= tile) ++s;
+    s = wave_uniform(s);
+    CPTR(DevFrame) const Fr = cptr(L.frames) + s;
+    const int tiles_x = Fr->cells_x;
+    const int local = tile - tile_base[s];
+    // local / tiles_x: an estimate within one of the quotient, corrected
+    int ty = (int)((float)local * Fr->inv_cells_x);
+    int tx = local - ty * tiles_x;
+    if (tx < 0) { --ty; tx += tiles_x; }
+    if (tx >= tiles_x) { ++ty; tx -= tiles_x; }
+    tx = wave_uniform(tx);
+    ty = wave_uniform(ty);
+    static_assert(kXcds == 8 && kRayLevels == 5, "levels of the switch, shifts of the part");
+    switch (level) {
+    case 0: raycast_part<0>(L, H, s, tx, ty, part); break;
+    case 1: raycast_part<1>(L, H, s, tx, ty, part); break;
+    case 2: raycast_part<2>(L, H, s, tx, ty, part); break;
+    case 3: raycast_part<3>(L, H, s, tx, ty, part); break;
+    default: raycast_part<4>(L, H, s, tx, ty, part); break;
+    }
+    // counted for the tiles around it too: by the next frame the camera has moved
+    if (threadIdx.x < 9) {
+        const int nx = tx + (int)threadIdx.x % 3 - 1, ny = ty + (int)threadIdx.x / 3 - 1;
+        const float d = (float)(wall_clock64() - t_tile) * ray_speedup(level);
+        if (nx >= 0 && nx < tiles_x && ny >= 0 && ny < Fr->cells_y)
+            atomicMax(&L.tile_cost[tile_base[s] + ny * tiles_x + nx], d < 4e9f ? (uint32_t)d + 1u : 0xffffffffu);
+    }
 }
 
 int launch_raycast(const RaycastLaunch& L, int blocks, void* stream, void* ev_start, void* ev_stop)
 {
     if (blocks <= 0) return 0;
-    hipStream_t s = (hipStream_t)stream;
-    hipEvent_t a = (hipEvent_t)ev_start, b = (hipEvent_t)ev_stop;
-    switch (L.lanes) {
-    case 2: launch_raycast_p<2>(L, blocks, s, a, b); break;
-    case 4: launch_raycast_p<4>(L, blocks, s, a, b); break;
-    case 8: launch_raycast_p<8>(L, blocks, s, a, b); break;
-    default: return (int)hipErrorInvalidValue;
-    }
+    if (ev_start)
+        hipExtLaunchKernelGGL(mvf_raycast_kernel, dim3(blocks), dim3(64), 0, (hipStream_t)stream, (hipEvent_t)ev_start,
+                              (hipEvent_t)ev_stop, 0, L);
+    else
+        hipLaunchKernelGGL(mvf_raycast_kernel, dim3(blocks), dim3(64), 0, (hipStream_t)stream, L);
     return (int)hipGetLastError();
 }
 
@@ -1945,7 +2047,7 @@ __global__ __launch_bounds__(1024) void mvf_ray_bounds_merge_kernel(const Launch
 {
     if (order.tiles > 0 && (int)blockIdx.z == order_z) {
         __shared__ int hist[kOrderBins];
-        if (blockIdx.x == 0 && blockIdx.y == 0) tile_order_block(order.cost, order.order, order.tiles, hist);
+        if (blockIdx.x == 0 && blockIdx.y == 0) tile_order_block(order, hist);
         return;
     }
     const int par = hdr->rb_parity;

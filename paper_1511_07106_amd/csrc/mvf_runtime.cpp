@@ -194,7 +194,7 @@ struct StepGraph {
     size_t dev_bytes = 0;
     size_t off_hdr, off_prep, off_frames, off_vols, off_items, off_lists, off_lbase, off_tbase, off_bbase;
     int max_vols = 0, max_w = 0, max_h = 0;
-    int integ_blocks = 0, ray_tiles = 0, ray_blocks = 0;
+    int integ_blocks = 0, ray_tiles = 0;
     float* ztab = nullptr;  // integration z table read by the captured launch
     int ztab_cap = 0;
     uint8_t* visit = nullptr;  // brick visit mask per integration item
@@ -753,17 +753,30 @@ mvf_status get_scratch(mvf_ctx* c, int sid, int w, int h, bool need_best, Scratc
     return MVF_OK;
 }
 
-// Raycast cost per tile (padded to whole groups) and launch order per tile
-// group, for n tiles.  The costs start at zero; any content still gives a
-// valid order (a permutation), the order only decides which tiles start
-// first.
+// Raycast duration per tile (zero: not known) and launch order, for n tiles.
 mvf_status alloc_tile_buffers(int n, uint32_t** cost, int32_t** order)
 {
-    const size_t nc = (size_t)ray_groups(n) * kRayGroup;  // whole groups (the padding stays 0)
-    CHECK_HIP(hipMalloc((void**)cost, nc * sizeof(uint32_t)));
-    CHECK_HIP(hipMalloc((void**)order, (size_t)ray_groups(n) * sizeof(int32_t)));
-    CHECK_HIP(hipMemset(*cost, 0, nc * sizeof(uint32_t)));
+    CHECK_HIP(hipMalloc((void**)cost, (size_t)n * sizeof(uint32_t)));
+    CHECK_HIP(hipMalloc((void**)order, ((size_t)n + kRayPlanInts) * sizeof(int32_t)));
+    CHECK_HIP(hipMemset(*cost, 0, (size_t)n * sizeof(uint32_t)));
     return MVF_OK;
+}
+
+// 8x8-pixel tiles of a w x h raycast.
+int ray_tiles(int w, int h) { return ((w + kRayTile - 1) / kRayTile) * ((h + kRayTile - 1) / kRayTile); }
+
+// The ordering of a raycast of that many tiles.  Without durations every tile
+// takes the highest level up to 3 with at most 2 * lanes blocks per wavefront
+// that the device holds, so that a small image fills the device and a large
+// one does no more work than it has to.
+TileOrder tile_order(const mvf_ctx* c, uint32_t* cost, int32_t* order, int tiles, int lanes, bool fresh = false)
+{
+    TileOrder o{cost, order, tiles, 0, 0, c->n_cus * kRayWavesPerCu, fresh ? 1 : 0};
+    const long long budget = 2ll * lanes * o.slots;
+    while (o.level < 3 && ((long long)tiles << (o.level + 1)) <= budget) ++o.level;
+    const long long blocks = std::max((long long)tiles << o.level, std::min<long long>(8ll * tiles, tiles + o.slots));
+    o.max_blocks = (int)align_up((size_t)blocks + kRaySlack, kXcds);
+    return o;
 }
 
 mvf_status get_tile_buffers(Scratch* s, int n)
@@ -814,15 +827,14 @@ mvf_status get_footprint_buffers(RayBoundEntry** entries, int* entries_cap, uint
 }
 
 // The raycast side of a frame: output size, tile grid and range bounds.
-void set_output(DevFrame* f, const Scratch* s, int w, int h, int lanes)
+void set_output(DevFrame* f, const Scratch* s, int w, int h)
 {
     f->out_w = w;
     f->out_h = h;
-    f->ray_tiles_x = (w + ray_tile_w(lanes) - 1) / ray_tile_w(lanes);
-    f->inv_ray_tiles_x = 1.0f / (float)f->ray_tiles_x;
     f->rb_lo = s->rb_lo;
     f->rb_hi = s->rb_hi;
     f->cells_x = (w + kBoundCell - 1) / kBoundCell;
+    f->inv_cells_x = 1.0f / (float)f->cells_x;
     f->cells_y = (h + kBoundCell - 1) / kBoundCell;
 }
 
@@ -993,7 +1005,8 @@ mvf_status integrate_plain(mvf_ctx* c, int sid, const mvf_frame* f, const float*
         CHECK_HIP(hipMalloc((void**)&sc->list_count, 2 * sizeof(unsigned long long)));
         CHECK_HIP(hipMemset(sc->list_count, 0, 2 * sizeof(unsigned long long)));
     }
-    bool order_pending = sc->tile_cost && sc->last_tiles > 0;  // once per call
+    // once per raycast (the ordering uses the durations up)
+    bool order_pending = sc->tile_cost && sc->last_tiles > 0 && sc->order_ready_tiles == 0;
     for (auto& wave : waves) {
         CHECK_ST(ensure_resident(c, wave, stream));
         int slot2;
@@ -1042,8 +1055,8 @@ mvf_status integrate_plain(mvf_ctx* c, int sid, const mvf_frame* f, const float*
             const bool order = pi == 0 && order_pending;
             order_pending = false;
             IntegrateLaunch L{p.dh, p.dv, dfr, p.dib, c->counters, sc->ztab, sc->visit,
-                              order ? sc->tile_cost : nullptr, order ? sc->tile_order : nullptr,
-                              order ? sc->last_tiles : 0, sc->list, sc->list_count,
+                              order ? tile_order(c, sc->tile_cost, sc->tile_order, sc->last_tiles, kRayLanes) : TileOrder{},
+                              sc->list, sc->list_count,
                               sc->list + (size_t)sc->visit_cap * kVisitPerItem};
             if (order) sc->order_ready_tiles = sc->last_tiles;
             CHECK_LAUNCH(launch_ztable(L, p.items * kZChunk, stream));
@@ -1075,12 +1088,12 @@ mvf_status raycast_plain(mvf_ctx* c, int sid, const float* T, const mvf_intrinsi
     CHECK_ST(get_scratch(c, sid, out->width, out->height, multi, &sc));
     RayParams rp{};
     if (!c->grids.empty()) rp = ray_params(c, c->grids[ids.empty() ? 0 : c->vols[ids[0]].d.grid_id]);
-    const int tw = ray_tile_w(kRayLanes), th = ray_tile_h(kRayLanes);  // one wavefront per block
-    const int tiles = ((out->width + tw - 1) / tw) * ((out->height + th - 1) / th);
+    const int tiles = ray_tiles(out->width, out->height);
     CHECK_ST(get_tile_buffers(sc, tiles));
     CHECK_ST(get_bound_buffers(sc, out->width, out->height));
     // an order the integration computed holds for this many tiles only (else the merge computes one)
     const bool ordered = sc->order_ready_tiles == tiles && sc->last_tiles == tiles;
+    const bool fresh = sc->last_tiles != tiles;
     sc->order_ready_tiles = 0;
     sc->last_tiles = tiles;
     for (size_t wi = 0; wi < waves.size(); ++wi) {
@@ -1117,7 +1130,7 @@ mvf_status raycast_plain(mvf_ctx* c, int sid, const float* T, const mvf_intrinsi
             fr->best_t = sc->best_t;
             fr->best_id = sc->best_id;
         }
-        set_output(fr, sc, out->width, out->height, kRayLanes);
+        set_output(fr, sc, out->width, out->height);
         // footprint regions: the wave's bricks, 64-aligned per volume
         int32_t* dbb;
         int32_t* bb = w.alloc<int32_t>(wave.size() + 1, &dbb);
@@ -1145,14 +1158,15 @@ mvf_status raycast_plain(mvf_ctx* c, int sid, const float* T, const mvf_intrinsi
         sc->rb_parity ^= 1;
         CHECK_ST(arena_upload(c, w, stream));
         // slowest tiles of the stream's last raycast first
-        RaycastLaunch L{dh, dvols, dfr, dlists, dlb, dtb, kRayLanes, sc->tile_cost, sc->tile_order};
+        const TileOrder order = tile_order(c, sc->tile_cost, sc->tile_order, tiles, kRayLanes, fresh && wi == 0);
+        RaycastLaunch L{dh, dvols, dfr, dlists, dlb, dtb, sc->tile_cost, sc->tile_order};
         hipEvent_t t0, t1;
         CHECK_ST(timing_pair(c, &t0, &t1));
         const RayBounds RB{sc->rb_entries, sc->rb_counts, sc->rb_counts_cap};
         CHECK_LAUNCH(launch_ray_bounds_collect(dh, dvols, dbb, dfr, RB, std::min(1024, (nbr + 255) / 256), stream));
-        const TileOrder order = ordered && wi == 0 ? TileOrder{} : TileOrder{sc->tile_cost, sc->tile_order, tiles};
-        CHECK_LAUNCH(launch_ray_bounds_merge(dh, dfr, dlists, dlb, dbb, RB, 1, fr->cells_x, fr->cells_y, stream, order));
-        CHECK_LAUNCH(launch_raycast(L, ray_blocks(tiles), stream, t0, t1));
+        CHECK_LAUNCH(launch_ray_bounds_merge(dh, dfr, dlists, dlb, dbb, RB, 1, fr->cells_x, fr->cells_y, stream,
+                                             ordered && wi == 0 ? TileOrder{} : order));
+        CHECK_LAUNCH(launch_raycast(L, order.max_blocks, stream, t0, t1));
         CHECK_ST(timing_push(c, t0, t1, 1));
         CHECK_ST(arena_release(c, slot, stream));
         c->stats.raycast_launches += 1;
@@ -2016,7 +2030,6 @@ mvf_status mvf_step(mvf_ctx* c, int32_t n, const mvf_stream_frame* frames, const
         for (int i = 0; i < n; ++i)
             if (G.out_w[i] != outs[i].width || G.out_h[i] != outs[i].height) same_shape = false;
     }
-    const int tw = ray_tile_w(sch.ray_lanes), th = ray_tile_h(sch.ray_lanes);  // one wavefront per block
     if (!same_shape) {
         CHECK_ST(destroy_step_graph(c));
         G.sched = sch;
@@ -2061,9 +2074,8 @@ mvf_status mvf_step(mvf_ctx* c, int32_t n, const mvf_stream_frame* frames, const
         }
         G.integ_blocks = c->n_cus * 8;
         int tiles = 0;
-        for (int i = 0; i < n; ++i) tiles += ((outs[i].width + tw - 1) / tw) * ((outs[i].height + th - 1) / th);
+        for (int i = 0; i < n; ++i) tiles += ray_tiles(outs[i].width, outs[i].height);
         G.ray_tiles = tiles;
-        G.ray_blocks = ray_blocks(tiles);
         CHECK_ST(alloc_tile_buffers(tiles, &G.tile_cost, &G.tile_order));
     }
     // scratch per stream (with the running best of a multi-wave raycast)
@@ -2130,7 +2142,7 @@ mvf_status mvf_step(mvf_ctx* c, int32_t n, const mvf_stream_frame* frames, const
             p.rmax = sc[i]->rmax;
             p.tmax = sc[i]->tmax;
             fill_frame(&dfr[i], sc[i], fr.frame.width, fr.frame.height, fr.T_wc, fr.K);
-            set_output(&dfr[i], sc[i], outs[i].width, outs[i].height, sch.ray_lanes);
+            set_output(&dfr[i], sc[i], outs[i].width, outs[i].height);
             if (!fr.frame.rgb) dfr[i].color = nullptr;
             dfr[i].depth = outs[i].depth;
             dfr[i].vertex = outs[i].vertex;
@@ -2162,7 +2174,7 @@ mvf_status mvf_step(mvf_ctx* c, int32_t n, const mvf_stream_frame* frames, const
             for (int id : order[i])
                 if (slot_of[id] >= 0) lists[li++] = slot_of[id];
             lb[i + 1] = nv;
-            tiles += ((outs[i].width + tw - 1) / tw) * ((outs[i].height + th - 1) / th);
+            tiles += ray_tiles(outs[i].width, outs[i].height);
             tb[i + 1] = tiles;
         }
         ib[nv] = items;
@@ -2200,7 +2212,7 @@ mvf_status mvf_step(mvf_ctx* c, int32_t n, const mvf_stream_frame* frames, const
             // integration's block 0 orders the raycast's tile groups (slowest of
             // the last step first)
             IntegrateLaunch IL{dh, dvols, dframes, ditems, c->counters, G.ztab, G.visit,
-                               G.tile_cost, G.tile_order, G.ray_tiles, G.list, G.list_count,
+                               tile_order(c, G.tile_cost, G.tile_order, G.ray_tiles, sch.ray_lanes), G.list, G.list_count,
                                G.list + (size_t)G.visit_cap * kVisitPerItem};
             int e2 = e1 ? e1 : launch_ztable(IL, items_total * zc, cs);
             // one wavefront per work item of the whole volume set (a larger
@@ -2212,8 +2224,8 @@ mvf_status mvf_step(mvf_ctx* c, int32_t n, const mvf_stream_frame* frames, const
             const RayBounds RB{G.rb_entries, G.rb_counts, G.max_vols};
             if (!e2) e2 = launch_brick_distance(dh, dvols, dbb, c->n_cus * 4, cs, dframes, RB);
             if (!e2) e2 = launch_ray_bounds_merge(dh, dframes, dlists, dlb, dbb, RB, n, G.max_cells_x, G.max_cells_y, cs);
-            RaycastLaunch RL{dh, dvols, dframes, dlists, dlb, dtb, sch.ray_lanes, G.tile_cost, G.tile_order};
-            int e3 = e2 ? e2 : launch_raycast(RL, G.ray_blocks, cs);
+            RaycastLaunch RL{dh, dvols, dframes, dlists, dlb, dtb, G.tile_cost, G.tile_order};
+            int e3 = e2 ? e2 : launch_raycast(RL, IL.order.max_blocks, cs);
             hipError_t ee = hipStreamEndCapture(cs, &G.graph);
             if (e3) return set_error(MVF_ERR_HIP, "step capture: %s", hipGetErrorString((hipError_t)e3));
             if (ee != hipSuccess) return set_error(MVF_ERR_HIP, "step capture: %s", hipGetErrorString(ee));

@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 
 import oracle as O
-from tests.util import log, t
+from tests.util import check_raycast, log, raycast_both, t
 
 pytestmark = pytest.mark.gpu
 
@@ -256,3 +256,35 @@ def test_diffray_backward_edges(mvf, w, h, f, add):
             assert np.linalg.norm(gxi.cpu().numpy() - g_ref) <= 1e-3 * np.linalg.norm(g_ref)
         alone = ctx.diffray_backward(Fd, Wd, og.origin, s, T, K, t(gd), record)
         assert torch.equal(alone, gxi)
+
+
+@pytest.mark.parametrize("w,h", [(1, 1), (9, 7), (16, 8), (65, 33), (321, 243), (803, 700), (1283, 700), (1645, 1001)])
+def test_raycast_tile_levels(mvf, w, h):
+    """Every split of the raycast's tiles: images of less than a tile to ones
+    beyond what the device holds at one lane per ray, the first call (one
+    split for all tiles) and later ones (chosen per tile from the durations
+    of the last, also from another camera).  Integer maps equal, depth within
+    1e-4 m, and a repeated view bit for bit the same."""
+    log(f"raycast tile levels {w}x{h}")
+    n = 40
+    og = O.OGrid((-1.0, -1.0, -1.0), 2.0 / n, 4.0, 128)
+    c = -1.0 + (np.arange(n) + 0.5) * (2.0 / n)
+    z, y, x = np.meshgrid(c, c, c, indexing="ij")
+    r = np.sqrt(x * x + y * y + z * z)
+    F = np.clip((np.minimum(r - 0.5, np.abs(z - 0.8) - 0.02)) / (4.0 * 2.0 / n), -1.0, 1.0)
+    ov = O.OVolume((n, n, n), (0, 0, 0), F, np.ones((n, n, n), np.uint16), np.zeros((n, n, n, 4), np.uint8))
+    f = 0.9 * max(w, h)
+    K = np.array([f, f, w / 2 - 0.3, h / 2 + 0.2], np.float32)
+    poses = [np.array([[1.0, 0.0, 0.0, 0.05 * i], [0.0, 1.0, 0.0, -0.1 * i], [0.0, 0.0, 1.0, -1.6]]) for i in (0, 1, 2)]
+    with mvf.Context() as ctx:
+        gid = ctx.grid((-1.0, -1.0, -1.0), 2.0 / n, 4.0, 128)
+        vid = ctx.volume(gid, (0, 0, 0), (n, n, n))
+        ctx.write_volume(vid, ov.F32(), ov.W, ov.Cc)
+        outs = []
+        for T in (poses[0], poses[0], poses[1], poses[2], poses[0]):
+            g, rc = raycast_both(ctx, [ov], og, K, T, w, h)
+            check_raycast(g, rc, [vid])
+            outs.append(g)
+        for i in (1, 4):
+            for k, v in outs[0].items():
+                np.testing.assert_array_equal(outs[i][k], v)
