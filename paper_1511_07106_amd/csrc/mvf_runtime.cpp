@@ -904,7 +904,6 @@ mvf_status drain_timing(mvf_ctx* c)
 // bricks per integration item along z (the visit masks hold one byte per brick)
 constexpr int kZChunk = 4;
 static_assert(kZChunk <= kVisitPerItem, "visit mask too small for the z chunk");
-int zchunk_for(const Volume&) { return kZChunk; }
 
 void fill_frame(DevFrame* f, const Scratch* s, int w, int h, const float* T, const mvf_intrinsics& K)
 {
@@ -935,8 +934,16 @@ RayParams ray_params(mvf_ctx* c, const Grid& g)
     return rp;
 }
 
-// Integration of one frame into the given volumes, one launch per volume
-// (the paper's per-volume loop), in budget-sized waves.
+// Work items of the volumes that one integration launch takes together (19 MB of
+// visit masks and lists; a larger volume has a launch of its own).  A launch per
+// volume left the device idle between the small ones: eight tiles of 257^3 took
+// 8 x (15.2 + 7.7 + 6.4) us for the integration, the visit pass and the distance
+// transform and the gaps between them, in one launch of each 73 + 12 + 12.5 us;
+// the call with its raycast 350 -> 205 us.
+constexpr int kPlainItems = 1 << 18;
+
+// Integration of one frame into the given volumes (the paper's per-volume
+// loop, as one launch over them), in budget-sized waves.
 mvf_status integrate_plain(mvf_ctx* c, int sid, const mvf_frame* f, const float* T, const mvf_intrinsics& K,
                            const std::vector<int>& ids, hipStream_t stream)
 {
@@ -970,8 +977,25 @@ mvf_status integrate_plain(mvf_ctx* c, int sid, const mvf_frame* f, const float*
     CHECK_ST(arena_upload(c, w, stream));
     CHECK_LAUNCH(launch_frame_prep(dprep, 1, f->width, f->height, stream));
     CHECK_ST(arena_release(c, slot, stream));
-    int zmax = 0;
-    for (int id : ids) zmax = std::max(zmax, kBrick * c->vols[id].bd[2]);
+    // the volumes of each launch, wave by wave
+    auto items_of = [&](const Volume& v) { return v.bd[0] * v.bd[1] * ((v.bd[2] + kZChunk - 1) / kZChunk); };
+    std::vector<std::vector<std::vector<int>>> launches(waves.size());
+    int zmax = 0, max_items = 0;
+    for (size_t wi = 0; wi < waves.size(); ++wi) {
+        int items = 0, z = 0;
+        for (int id : waves[wi]) {
+            const Volume& v = c->vols[id];
+            if (launches[wi].empty() || items + items_of(v) > kPlainItems) {
+                launches[wi].emplace_back();
+                items = z = 0;
+            }
+            launches[wi].back().push_back(id);
+            items += items_of(v);
+            z += kBrick * v.bd[2];
+            zmax = std::max(zmax, z);
+            max_items = std::max(max_items, items);
+        }
+    }
     if (zmax > sc->ztab_cap) {
         // stream-ordered: earlier launches reading the old table have been
         // queued on this stream, so free only after they finish
@@ -982,11 +1006,6 @@ mvf_status integrate_plain(mvf_ctx* c, int sid, const mvf_frame* f, const float*
         }
         CHECK_HIP(hipMalloc((void**)&sc->ztab, (size_t)zmax * 3 * sizeof(float)));
         sc->ztab_cap = zmax;
-    }
-    int max_items = 0;
-    for (int id : ids) {
-        const Volume& v = c->vols[id];
-        max_items = std::max(max_items, v.bd[0] * v.bd[1] * ((v.bd[2] + zchunk_for(v) - 1) / zchunk_for(v)));
     }
     if (max_items > sc->visit_cap) {
         if (sc->visit) {
@@ -1007,8 +1026,8 @@ mvf_status integrate_plain(mvf_ctx* c, int sid, const mvf_frame* f, const float*
     }
     // once per raycast (the ordering uses the durations up)
     bool order_pending = sc->tile_cost && sc->last_tiles > 0 && sc->order_ready_tiles == 0;
-    for (auto& wave : waves) {
-        CHECK_ST(ensure_resident(c, wave, stream));
+    for (size_t wi = 0; wi < waves.size(); ++wi) {
+        CHECK_ST(ensure_resident(c, waves[wi], stream));
         int slot2;
         Writer w2;
         CHECK_ST(arena_acquire(c, &slot2, &w2));
@@ -1017,33 +1036,34 @@ mvf_status integrate_plain(mvf_ctx* c, int sid, const mvf_frame* f, const float*
         *fr = *frame;
         struct Per { LaunchHeader* dh; DevVolume* dv; int32_t* dib; int32_t* dbb; int items; int bricks; };
         std::vector<Per> per;
-        for (int id : wave) {
-            Volume& v = c->vols[id];
+        for (const std::vector<int>& group : launches[wi]) {
             Per p;
             LaunchHeader* h = w2.alloc<LaunchHeader>(1, &p.dh);
-            DevVolume* dv = w2.alloc<DevVolume>(1, &p.dv);
-            int32_t* ib = w2.alloc<int32_t>(2, &p.dib);
-            int32_t* bb = w2.alloc<int32_t>(2, &p.dbb);
+            DevVolume* dv = w2.alloc<DevVolume>(group.size(), &p.dv);
+            int32_t* ib = w2.alloc<int32_t>(group.size() + 1, &p.dib);
+            int32_t* bb = w2.alloc<int32_t>(group.size() + 1, &p.dbb);
             if (!h || !dv || !ib || !bb) return set_error(MVF_ERR_INVALID_ARG, "arena overflow");
-            *dv = make_dev(c, v);
-            dv->frame = 0;
-            dv->zt_base = 0;
-            const int zc = zchunk_for(v);
-            p.items = v.bd[0] * v.bd[1] * ((v.bd[2] + zc - 1) / zc);
             memset(h, 0, sizeof(*h));
-            h->nvol = 1;
-            h->total_items = p.items;
-            h->zchunk = zc;
+            h->nvol = (int32_t)group.size();
+            h->zchunk = kZChunk;
             h->nstreams = 1;
-            p.bricks = (int)v.nbricks;
-            h->total_bricks = (int)align_up((size_t)p.bricks, 64);
-            h->total_z = kBrick * v.bd[2];
+            for (size_t j = 0; j < group.size(); ++j) {
+                Volume& v = c->vols[group[j]];
+                dv[j] = make_dev(c, v);
+                dv[j].frame = 0;
+                dv[j].zt_base = h->total_z;
+                ib[j] = h->total_items;
+                bb[j] = h->total_bricks;
+                h->total_z += kBrick * v.bd[2];
+                h->total_items += items_of(v);
+                h->total_bricks += (int)align_up(v.nbricks, 64);
+            }
+            ib[group.size()] = h->total_items;
+            bb[group.size()] = h->total_bricks;
+            p.items = h->total_items;
+            p.bricks = h->total_bricks;
             h->list_parity = sc->list_parity;
             sc->list_parity ^= 1;
-            ib[0] = 0;
-            ib[1] = p.items;
-            bb[0] = 0;
-            bb[1] = h->total_bricks;
             per.push_back(p);
         }
         CHECK_ST(arena_upload(c, w2, stream));

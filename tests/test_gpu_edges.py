@@ -288,3 +288,35 @@ def test_raycast_tile_levels(mvf, w, h):
         for i in (1, 4):
             for k, v in outs[0].items():
                 np.testing.assert_array_equal(outs[i][k], v)
+
+
+@pytest.mark.parametrize("count", [2, 4, 5])
+def test_integrate_volumes_together(mvf, count):
+    """Volumes of one plain integration share launches up to 2^18 work items
+    (four of these slabs; the fifth has a launch of its own): each volume the
+    same bit for bit as when it is alone in a context."""
+    log(f"integrate {count} slabs together")
+    rng = np.random.default_rng(count)
+    dims = (2048, 2048, 2)
+    w, h = 320, 240
+    d = _random_depth(rng, w, h, 0.95, 1.1)
+    rgb = rng.integers(0, 256, (h, w, 3), dtype=np.uint8)
+    K = np.array([150.0, 151.0, w / 2 - 0.3, h / 2 + 0.2], np.float32)
+    T = np.array([[1.0, 0.0, 0.0, 2.0], [0.0, 1.0, 0.0, 2.0], [0.0, 0.0, 1.0, 0.0]])
+    offs = [(0, 0, 490 + 7 * i) for i in range(count)]
+
+    def fuse(ctx, off):
+        gid = ctx.grid((0.0, 0.0, 0.0), 0.002)
+        ids = [ctx.volume(gid, o, dims) for o in off]
+        for _ in range(2):
+            ctx.integrate(t(d), t(rgb), T, K)
+        return [ctx.read_volume(i) for i in ids]
+
+    with mvf.Context() as ctx:
+        got = fuse(ctx, offs)
+    for o, g in zip(offs, got):
+        with mvf.Context() as ctx:
+            (alone,) = fuse(ctx, [o])
+        assert (alone[1] > 0).any()
+        for a, b in zip(g, alone):
+            np.testing.assert_array_equal(a, b)
