@@ -174,6 +174,12 @@ struct PrepItem {
                              // minima follow (ceil(width / 8) * ceil(height / 8) further on)
 };
 
+// Items that frame preparation takes as kernel arguments.
+constexpr int kPrepInline = 16;
+struct PrepArgs {
+    PrepItem item[kPrepInline];
+};
+
 // Integration work item: a brick column (8x8 voxel columns) of one volume
 // over a chunk of zchunk bricks along z.  Items of table entry v are
 // [item_base[v], item_base[v+1]).
@@ -265,10 +271,11 @@ struct RaycastLaunch {
 
 // Host-side launchers (defined in mvf_kernels.hip).  All return hipError_t
 // as int (0 = success).
-// Frame preparation of n frames.  With tsrc set (a captured step) the items
-// are read from pinned host memory and the launch also copies tbytes (a
-// multiple of 16, 16-byte aligned) from tsrc to tdst; set_frame_prep_node
-// points such a node of an instantiated graph at another host slot.
+// Frame preparation of n frames, their items in pinned host memory (read when
+// the launch runs if there are more than kPrepInline).  With tsrc set the
+// launch also copies tbytes (a multiple of 16, 16-byte aligned) from tsrc,
+// pinned host memory, to tdst; set_frame_prep_node points such a node of an
+// instantiated graph at other items and another host slot.
 int launch_frame_prep(const PrepItem* items, int n, int max_w, int max_h, void* stream, const void* tsrc = nullptr,
                       void* tdst = nullptr, size_t tbytes = 0);
 int set_frame_prep_node(void* exec, void* node, const PrepItem* items, int n, int max_w, int max_h, const void* tsrc,

@@ -63,78 +63,113 @@ static __host__ __device__ __forceinline__ size_t brick_index(const int bd[3], i
 // The range map holds one more element, range[W * H] = 0, read by voxels
 // that project outside the image.  The maximum range is reduced from
 // per-block maxima by the z-table kernel, which runs before integration.
-// In a captured step the items are read from the step's pinned host slot,
-// and every thread of the launch also copies one 16-byte word of the slot's
+// With tables to upload, every thread of the launch also copies one 16-byte word of the slot's
 // table image to the tables' device home (tsrc, tdst: n16 words), which the
 // later kernels of the step read.
+//
+// Bound by memory (15 B/px), and for one image by its latency.  A wavefront
+// takes 32x8 pixels, four neighbours of a row per lane, so that a lane has its
+// loads in flight together and the tile reductions need no LDS; the items of
+// up to kPrepInline images come as kernel arguments (read from the pinned host
+// table by every block, and with one pixel per lane, 16 images of 640x480 took
+// 43 us and one of 320x240 7.2; now 25.5 and 4.6).
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void mvf_frame_prep_kernel(const PrepItem* __restrict__ items, const uint4* tsrc,
-                                                             uint4* tdst, uint32_t n16)
+static_assert(sizeof(PrepArgs) <= 2048, "kernel arguments");
+
+__global__ __launch_bounds__(256) void mvf_frame_prep_kernel(PrepArgs inl, const PrepItem* __restrict__ items,
+                                                             const uint4* tsrc, uint4* tdst, uint32_t n16)
 {
     if (tsrc) {
         const uint32_t nt = gridDim.x * gridDim.y * gridDim.z * 256u;
         const uint32_t t = ((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) * 256u + threadIdx.x;
         for (uint32_t i = t; i < n16; i += nt) tdst[i] = tsrc[i];
     }
-    const PrepItem& it = items[blockIdx.z];
-    const int u = blockIdx.x * 32 + (threadIdx.x & 31);
-    const int v = blockIdx.y * 8 + (threadIdx.x >> 5);
-    float R = 0.0f;
-    if (u < it.width && v < it.height) {
-        const float Dz = it.depth[(size_t)v * it.depth_pitch + u];
-        if (Dz > 0.0f && Dz < INFINITY) {
-            const float a = ((float)u - it.cx) / it.fx;
-            const float b = ((float)v - it.cy) / it.fy;
-            const float lam = sqrtf(((a * a) + (b * b)) + 1.0f);
-            R = Dz * lam;
+    const PrepItem it = items ? items[blockIdx.z] : inl.item[blockIdx.z];
+    const int lane = threadIdx.x & 63;
+    const int bx = wave_uniform((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));   // 32x8-pixel block of the wavefront
+    const int gx = (it.width + 31) / 32, gy = (it.height + 7) / 8;
+    if (bx >= gx || (int)blockIdx.y >= gy) return;
+    const int u0 = bx * 32 + (lane & 7) * 4;
+    const int v = blockIdx.y * 8 + (lane >> 3);
+    float R[4] = {0.0f, 0.0f, 0.0f, 0.0f};   // pixels outside the image count as range 0
+    if (u0 < it.width && v < it.height) {
+        const int n = min(it.width - u0, 4);
+        const float* const dp = it.depth + (size_t)v * it.depth_pitch + u0;
+        const uint8_t* const q = it.rgb ? it.rgb + (size_t)v * it.rgb_pitch + 3 * u0 : nullptr;
+        float D[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        uint32_t c[4] = {0, 0, 0, 0};
+        if (n == 4 && !(((uintptr_t)it.depth | (uint32_t)it.depth_pitch * 4u) & 15u)) {
+            const float4 d4 = *reinterpret_cast<const float4*>(dp);
+            D[0] = d4.x; D[1] = d4.y; D[2] = d4.z; D[3] = d4.w;
+        } else {
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (k < n) D[k] = dp[k];
         }
-        it.range[(size_t)v * it.width + u] = R;
-        uint32_t c = 0;
-        if (it.rgb) {
-            const uint8_t* q = it.rgb + (size_t)v * it.rgb_pitch + 3 * u;
-            c = (uint32_t)q[0] | ((uint32_t)q[1] << 8) | ((uint32_t)q[2] << 16);
+        if (q) {
+            if (n == 4 && !(((uintptr_t)it.rgb | (uint32_t)it.rgb_pitch) & 3u)) {
+                const uint32_t* const q4 = reinterpret_cast<const uint32_t*>(q);
+                const uint32_t x = q4[0], y = q4[1], z = q4[2];
+                c[0] = x & 0xffffffu;
+                c[1] = x >> 24 | (y & 0xffffu) << 8;
+                c[2] = y >> 16 | (z & 0xffu) << 16;
+                c[3] = z >> 8;
+            } else {
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if (k < n) c[k] = (uint32_t)q[3 * k] | ((uint32_t)q[3 * k + 1] << 8) | ((uint32_t)q[3 * k + 2] << 16);
+            }
         }
-        it.color[(size_t)v * it.width + u] = c;
+        const float b = ((float)v - it.cy) / it.fy;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (D[k] > 0.0f && D[k] < INFINITY) {
+                const float a = ((float)(u0 + k) - it.cx) / it.fx;
+                const float lam = sqrtf(((a * a) + (b * b)) + 1.0f);
+                R[k] = D[k] * lam;
+            }
+        }
+        const size_t p = (size_t)v * it.width + u0;
+        if (!(it.width & 3)) {   // the planes are aligned allocations
+            *reinterpret_cast<float4*>(it.range + p) = make_float4(R[0], R[1], R[2], R[3]);
+            *reinterpret_cast<uint4*>(it.color + p) = make_uint4(c[0], c[1], c[2], c[3]);
+        } else {
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (k < n) { it.range[p + k] = R[k]; it.color[p + k] = c[k]; }
+        }
     }
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0)
+    if (bx == 0 && blockIdx.y == 0 && lane == 0)
         it.range[(size_t)it.width * it.height] = 0.0f;
-    // maxima and minima of the block's four 8x8 tiles: a wavefront holds
-    // two rows of 32 pixels, a tile's part of it is 8 consecutive lanes in
-    // each half (pixels outside the image count as range 0)
-    float tm = R, tn = R;
-    for (int o = 1; o <= 4; o <<= 1) {
+    // maxima and minima of the wavefront's four 8x8 tiles: lanes 2 t and 2 t + 1
+    // of each row of eight
+    float tm = fmaxf(fmaxf(R[0], R[1]), fmaxf(R[2], R[3])), tn = fminf(fminf(R[0], R[1]), fminf(R[2], R[3]));
+#pragma unroll
+    for (int o = 1; o <= 32; o = o == 1 ? 8 : 2 * o) {
         tm = fmaxf(tm, __shfl_xor(tm, o));
         tn = fminf(tn, __shfl_xor(tn, o));
     }
-    tm = fmaxf(tm, __shfl_xor(tm, 32));
-    tn = fminf(tn, __shfl_xor(tn, 32));
-    // block maximum into this block's slot; the z-table kernel reduces the
+    // the wavefront's maximum into its slot; the z-table kernel reduces the
     // slots (no atomics on one address)
-    float m = tm;
-    for (int o = 8; o <= 16; o <<= 1) m = fmaxf(m, __shfl_xor(m, o));
-    __shared__ float wmax[4];
-    __shared__ float tw[4][4], tnw[4][4];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    if (lane == 0) wmax[wv] = m;
-    if (lane < 32 && (lane & 7) == 0) {
-        tw[wv][lane >> 3] = tm;
-        tnw[wv][lane >> 3] = tn;
-    }
-    __syncthreads();
-    const int gx = (it.width + 31) / 32, gy = (it.height + 7) / 8;
-    if (threadIdx.x == 0 && (int)blockIdx.x < gx && (int)blockIdx.y < gy) {
-        m = fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]));
-        it.rmax[1 + blockIdx.y * gx + blockIdx.x] = m;
-    }
+    float m = fmaxf(tm, __shfl_xor(tm, 2));
+    m = fmaxf(m, __shfl_xor(m, 4));
+    if (lane == 0) it.rmax[1 + blockIdx.y * gx + bx] = m;
     const int tiles_x = (it.width + 7) / 8;
-    const int tx = (int)blockIdx.x * 4 + (int)threadIdx.x;
-    if (it.tmax && threadIdx.x < 4 && tx < tiles_x && (int)blockIdx.y < gy) {
-        const int t = threadIdx.x;
-        it.tmax[blockIdx.y * tiles_x + tx] = fmaxf(fmaxf(tw[0][t], tw[1][t]), fmaxf(tw[2][t], tw[3][t]));
+    const int tx = bx * 4 + (lane >> 1);
+    if (it.tmax && lane < 8 && !(lane & 1) && tx < tiles_x) {
+        it.tmax[blockIdx.y * tiles_x + tx] = tm;
         // the minima follow the maxima (tiles_x * tiles_y of each)
-        it.tmax[(size_t)tiles_x * gy + blockIdx.y * tiles_x + tx] =
-            fminf(fminf(tnw[0][t], tnw[1][t]), fminf(tnw[2][t], tnw[3][t]));
+        it.tmax[(size_t)tiles_x * gy + blockIdx.y * tiles_x + tx] = tn;
     }
+}
+
+static dim3 prep_grid(int n, int max_w, int max_h) { return dim3((max_w + 127) / 128, (max_h + 7) / 8, n); }
+
+static PrepArgs prep_args(const PrepItem* items, int n)
+{
+    PrepArgs a{};
+    for (int i = 0; i < n && n <= kPrepInline; ++i) a.item[i] = items[i];
+    return a;
 }
 
 int launch_frame_prep(const PrepItem* items, int n, int max_w, int max_h, void* stream, const void* tsrc,
@@ -142,9 +177,8 @@ int launch_frame_prep(const PrepItem* items, int n, int max_w, int max_h, void* 
 {
     if (n <= 0) return 0;
     if (tsrc && ((tbytes & 15) || ((uintptr_t)tsrc & 15) || ((uintptr_t)tdst & 15))) return (int)hipErrorInvalidValue;
-    hipStream_t s = (hipStream_t)stream;
-    dim3 grid((max_w + 31) / 32, (max_h + 7) / 8, n);
-    hipLaunchKernelGGL(mvf_frame_prep_kernel, grid, dim3(256), 0, s, items, (const uint4*)tsrc, (uint4*)tdst,
+    hipLaunchKernelGGL(mvf_frame_prep_kernel, prep_grid(n, max_w, max_h), dim3(256), 0, (hipStream_t)stream,
+                       prep_args(items, n), n <= kPrepInline ? nullptr : items, (const uint4*)tsrc, (uint4*)tdst,
                        (uint32_t)(tsrc ? tbytes / 16 : 0));
     return (int)hipGetLastError();
 }
@@ -154,14 +188,15 @@ int set_frame_prep_node(void* exec, void* node, const PrepItem* items, int n, in
 {
     if (n <= 0 || !tsrc || (tbytes & 15) || ((uintptr_t)tsrc & 15) || ((uintptr_t)tdst & 15))
         return (int)hipErrorInvalidValue;
-    const PrepItem* a0 = items;
-    const uint4* a1 = (const uint4*)tsrc;
-    uint4* a2 = (uint4*)tdst;
-    uint32_t a3 = (uint32_t)(tbytes / 16);
-    void* args[] = {(void*)&a0, (void*)&a1, (void*)&a2, (void*)&a3};
+    PrepArgs a0 = prep_args(items, n);
+    const PrepItem* a1 = n <= kPrepInline ? nullptr : items;
+    const uint4* a2 = (const uint4*)tsrc;
+    uint4* a3 = (uint4*)tdst;
+    uint32_t a4 = (uint32_t)(tbytes / 16);
+    void* args[] = {(void*)&a0, (void*)&a1, (void*)&a2, (void*)&a3, (void*)&a4};
     hipKernelNodeParams p{};
     p.func = reinterpret_cast<void*>(mvf_frame_prep_kernel);
-    p.gridDim = dim3((max_w + 31) / 32, (max_h + 7) / 8, n);
+    p.gridDim = prep_grid(n, max_w, max_h);
     p.blockDim = dim3(256);
     p.sharedMemBytes = 0;
     p.kernelParams = args;

@@ -949,14 +949,9 @@ mvf_status integrate_plain(mvf_ctx* c, int sid, const mvf_frame* f, const float*
 {
     Scratch* sc;
     CHECK_ST(get_scratch(c, sid, f->width, f->height, false, &sc));
-    int slot;
-    Writer w;
-    CHECK_ST(arena_acquire(c, &slot, &w));
-    PrepItem* dprep;
-    PrepItem* prep = w.alloc<PrepItem>(1, &dprep);
-    DevFrame* dframe;
-    DevFrame* frame = w.alloc<DevFrame>(1, &dframe);
-    if (!prep || !frame) return set_error(MVF_ERR_INVALID_ARG, "arena overflow");
+    PrepItem item;
+    PrepItem* const prep = &item;
+    DevFrame frame;
     memset(prep, 0, sizeof(*prep));
     prep->depth = f->depth;
     prep->rgb = f->rgb;
@@ -969,14 +964,10 @@ mvf_status integrate_plain(mvf_ctx* c, int sid, const mvf_frame* f, const float*
     prep->color = sc->color;
     prep->rmax = sc->rmax;
     prep->tmax = sc->tmax;
-    fill_frame(frame, sc, f->width, f->height, T, K);
-    if (!f->rgb) frame->color = nullptr;
+    fill_frame(&frame, sc, f->width, f->height, T, K);
+    if (!f->rgb) frame.color = nullptr;
     // per-volume tables are filled after residency is known (slab pointers)
     std::vector<std::vector<int>> waves = plan_waves(c, ids);
-    // first upload: prep + frame; volume tables go into fresh slots per wave
-    CHECK_ST(arena_upload(c, w, stream));
-    CHECK_LAUNCH(launch_frame_prep(dprep, 1, f->width, f->height, stream));
-    CHECK_ST(arena_release(c, slot, stream));
     // the volumes of each launch, wave by wave
     auto items_of = [&](const Volume& v) { return v.bd[0] * v.bd[1] * ((v.bd[2] + kZChunk - 1) / kZChunk); };
     std::vector<std::vector<std::vector<int>>> launches(waves.size());
@@ -1033,7 +1024,8 @@ mvf_status integrate_plain(mvf_ctx* c, int sid, const mvf_frame* f, const float*
         CHECK_ST(arena_acquire(c, &slot2, &w2));
         DevFrame* dfr;
         DevFrame* fr = w2.alloc<DevFrame>(1, &dfr);
-        *fr = *frame;
+        if (!fr) return set_error(MVF_ERR_INVALID_ARG, "arena overflow");
+        *fr = frame;
         struct Per { LaunchHeader* dh; DevVolume* dv; int32_t* dib; int32_t* dbb; int items; int bricks; };
         std::vector<Per> per;
         for (const std::vector<int>& group : launches[wi]) {
@@ -1066,7 +1058,13 @@ mvf_status integrate_plain(mvf_ctx* c, int sid, const mvf_frame* f, const float*
             sc->list_parity ^= 1;
             per.push_back(p);
         }
-        CHECK_ST(arena_upload(c, w2, stream));
+        // the frame's preparation also copies the first wave's tables
+        if (wi == 0) {
+            if (w2.overflow) return set_error(MVF_ERR_INVALID_ARG, "launch tables exceed %zu bytes", Arena::kSlotBytes);
+            CHECK_LAUNCH(launch_frame_prep(prep, 1, f->width, f->height, stream, w2.host, w2.dev, align_up(w2.used, 16)));
+        } else {
+            CHECK_ST(arena_upload(c, w2, stream));
+        }
         for (size_t pi = 0; pi < per.size(); ++pi) {
             const Per& p = per[pi];
             // the first launch's block 0 orders the tiles of the stream's

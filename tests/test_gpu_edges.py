@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 
 import oracle as O
-from tests.util import check_raycast, log, raycast_both, t
+from tests.util import check_raycast, compare_volume, log, raycast_both, t
 
 pytestmark = pytest.mark.gpu
 
@@ -320,3 +320,74 @@ def test_integrate_volumes_together(mvf, count):
         assert (alone[1] > 0).any()
         for a, b in zip(g, alone):
             np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("w,h,shift,dpitch,rpitch", [(1, 1, 0, 0, 0), (3, 9, 1, 5, 10), (31, 8, 0, 32, 96), (33, 7, 3, 0, 0),
+                                                     (128, 16, 0, 0, 0), (128, 16, 2, 129, 385), (132, 17, 0, 136, 400),
+                                                     (260, 9, 1, 0, 0)])
+def test_frame_alignment(mvf, w, h, shift, dpitch, rpitch):
+    """Frames of every alignment of pointer, pitch and width (four pixels of a
+    row are read together where that is aligned), against the oracle."""
+    import ctypes as C
+    import torch
+    from paper_1511_07106_amd import _lib as L
+    log(f"frame alignment {w}x{h} shift {shift} pitches {dpitch} {rpitch}")
+    rng = np.random.default_rng(w + 7 * h + shift)
+    d = _random_depth(rng, w, h, 0.4, 1.2)
+    rgb = rng.integers(0, 256, (h, w, 3), dtype=np.uint8)
+    dp, rp = dpitch or w, rpitch or 3 * w
+    dbuf = np.full(shift + dp * h, 0.7, np.float32)
+    rbuf = np.full(shift + rp * h, 9, np.uint8)
+    for y in range(h):
+        dbuf[shift + y * dp: shift + y * dp + w] = d[y]
+        rbuf[shift + y * rp: shift + y * rp + 3 * w] = rgb[y].reshape(-1)
+    td, tr = t(dbuf), t(rbuf)
+    f = 0.8 * max(w, h, 8)
+    K = np.array([f, f * 1.02, w / 2 - 0.3, h / 2 + 0.2], np.float32)
+    T = np.array([[1.0, 0.0, 0.0, 0.5], [0.0, 1.0, 0.0, 0.5], [0.0, 0.0, 1.0, -0.3]])
+    og = O.OGrid((0.0, 0.0, 0.0), 0.025, 4.0, 128)
+    ov = O.OVolume.empty((40, 40, 40))
+    with mvf.Context() as ctx:
+        gid = ctx.grid((0.0, 0.0, 0.0), 0.025, 4.0, 128)
+        vid = ctx.volume(gid, (0, 0, 0), (40, 40, 40))
+        fr = L.mvf_frame(td.data_ptr() + 4 * shift, tr.data_ptr() + shift, w, h, dpitch, rpitch)
+        pose = (C.c_float * 12)(*T.astype(np.float32).reshape(-1))
+        k = L.mvf_intrinsics(*[float(x) for x in K])
+        L.check(ctx.lib.mvf_integrate(ctx.h, 0, C.byref(fr), pose, C.byref(k), None), "mvf_integrate")
+        torch.cuda.synchronize()
+        O.integrate(ov, og, d, rgb, K, T)
+        compare_volume(ctx, vid, ov)
+
+
+@pytest.mark.parametrize("n", [16, 17])
+def test_step_many_streams(mvf, n):
+    """Frames whose items fit the kernel arguments, and one more: the batched
+    step's volumes and maps equal the plain calls' bit for bit."""
+    log(f"step {n} streams")
+    rng = np.random.default_rng(n)
+    w, h = 50, 37
+    K = np.array([45.0, 46.0, w / 2 - 0.3, h / 2 + 0.2], np.float32)
+    T = np.array([[1.0, 0.0, 0.0, 0.5], [0.0, 1.0, 0.0, 0.5], [0.0, 0.0, 1.0, -0.3]])
+    frames = [(t(_random_depth(rng, w, h, 0.4, 1.2)), t(rng.integers(0, 256, (h, w, 3), dtype=np.uint8))) for _ in range(n)]
+
+    def run(step):
+        with mvf.Context() as ctx:
+            gid = ctx.grid((0.0, 0.0, 0.0), 0.025, 4.0, 128)
+            ids = [ctx.volume(gid, (0, 0, 0), (40, 40, 40), stream_id=i) for i in range(n)]
+            outs = [ctx.raycast(T, K, w, h, stream_id=i) for i in range(n)]
+            for _ in range(2):
+                if step:
+                    ctx.step([(i, d, c, T, K) for i, (d, c) in enumerate(frames)], outs)
+                else:
+                    for i, (d, c) in enumerate(frames):
+                        ctx.integrate(d, c, T, K, stream_id=i)
+                        ctx.raycast(T, K, w, h, stream_id=i, out=outs[i])
+            vols = [ctx.read_volume(i) for i in ids]
+            return vols, [{k: v.cpu().numpy() for k, v in o.items()} for o in outs]
+
+    (va, oa), (vb, ob) = run(True), run(False)
+    for i in range(n):
+        for a, b in zip(va[i], vb[i]):
+            np.testing.assert_array_equal(a, b)
+        for k in oa[i]:
+            np.testing.assert_array_equal(oa[i][k], ob[i][k])
