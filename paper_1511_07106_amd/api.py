@@ -158,9 +158,9 @@ class Context:
     def read_volume(self, vid: int):
         """(F float32, W uint16, RGBA uint8) arrays of shape (nz, ny, nx[, 4])."""
         nx, ny, nz = self.dims(vid)
-        F = np.zeros((nz, ny, nx), np.float32)
-        W = np.zeros((nz, ny, nx), np.uint16)
-        Cc = np.zeros((nz, ny, nx, 4), np.uint8)
+        F = np.empty((nz, ny, nx), np.float32)
+        W = np.empty((nz, ny, nx), np.uint16)
+        Cc = np.empty((nz, ny, nx, 4), np.uint8)
         L.check(self.lib.mvf_volume_read(self.h, int(vid), F.ctypes.data_as(C.c_void_p),
                                          W.ctypes.data_as(C.c_void_p), Cc.ctypes.data_as(C.c_void_p)),
                 "mvf_volume_read")

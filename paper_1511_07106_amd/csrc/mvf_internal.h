@@ -314,7 +314,9 @@ int launch_ray_bounds_collect(const LaunchHeader* hdr, const DevVolume* vols, co
 int launch_ray_bounds_merge(const LaunchHeader* hdr, const DevFrame* frames, const int32_t* lists,
                             const int32_t* list_base, const int32_t* brick_base, RayBounds rb, int nstreams,
                             int max_cells_x, int max_cells_y, void* stream, TileOrder order = TileOrder{});
-int launch_to_canonical(DevVolume v, float* F, uint16_t* W, uint32_t* C, void* stream);
+// Elements [e0, e0 + n) of a volume's canonical plane (0: F, 1: weights, 2:
+// colours) to out, pinned host memory.
+int launch_read_plane(DevVolume v, int plane, uint32_t e0, uint32_t n, void* out, void* stream);
 // Canonical planes (null: empty) into the volume's bricks, with the brick
 // flags and sub-block masks; full: weights and colours too, else only F.
 int launch_import(DevVolume v, const float* F, const uint16_t* W, const uint32_t* C, bool full, void* stream);

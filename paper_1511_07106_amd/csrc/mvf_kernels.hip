@@ -2149,7 +2149,7 @@ int launch_ray_bounds_merge(const LaunchHeader* hdr, const DevFrame* frames, con
 
 // ---------------------------------------------------------------------------
 // Layout conversion between brick-linear device planes and canonical
-// x-fastest planes.  One thread per canonical voxel.
+// x-fastest planes.
 // ---------------------------------------------------------------------------
 static __device__ __forceinline__ size_t brick_offset(const DevVolume& v, int x, int y, int z)
 {
@@ -2157,20 +2157,21 @@ static __device__ __forceinline__ size_t brick_offset(const DevVolume& v, int x,
            (size_t)(((z & 7) << 6) | ((y & 7) << 3) | (x & 7));
 }
 
-__global__ __launch_bounds__(256) void mvf_to_canonical_kernel(DevVolume v, float* F, uint16_t* W, uint32_t* C)
+// Elements [e0, e0 + n) of a canonical plane (T: float, F; uint16_t, weights;
+// uint32_t, colours) into out, pinned host memory.  Bound by the host link, in
+// stores of whole wavefronts side by side.
+template <class T>
+__global__ __launch_bounds__(256) void mvf_read_plane_kernel(DevVolume v, uint32_t e0, uint32_t n, T* out)
 {
-    const size_t n = (size_t)v.dims[0] * v.dims[1] * v.dims[2];
-    const size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-        const int x = (int)(i % v.dims[0]);
-        const int y = (int)((i / v.dims[0]) % v.dims[1]);
-        const int z = (int)(i / ((size_t)v.dims[0] * v.dims[1]));
-        const size_t b = brick_offset(v, x, y, z);
-        const uint16_t w = v.W[b];
-        if (F) F[i] = w ? v.F[b] : 0.0f;
-        if (W) W[i] = w;
-        if (C) C[i] = v.C[b];
-    }
+    const uint32_t t = blockIdx.x * 256u + threadIdx.x;
+    if (t >= n) return;
+    const uint32_t i = e0 + t, r = i / (uint32_t)v.dims[0];
+    const int x = (int)(i - r * (uint32_t)v.dims[0]);
+    const int z = (int)(r / (uint32_t)v.dims[1]), y = (int)(r - (uint32_t)z * (uint32_t)v.dims[1]);
+    const size_t b = brick_offset(v, x, y, z);
+    if (sizeof(T) == 2) out[t] = (T)v.W[b];
+    else if (std::is_same<T, float>::value) out[t] = v.W[b] ? (T)v.F[b] : (T)0;
+    else out[t] = (T)v.C[b];
 }
 
 // Import of canonical planes into a volume, whole bricks at a time (voxels
@@ -2268,17 +2269,14 @@ __global__ __launch_bounds__(256) void mvf_import_kernel(DevVolume v, const floa
     }
 }
 
-static int conv_blocks(const DevVolume& v)
+int launch_read_plane(DevVolume v, int plane, uint32_t e0, uint32_t n, void* out, void* stream)
 {
-    const size_t n = (size_t)v.dims[0] * v.dims[1] * v.dims[2];
-    size_t b = (n + 255) / 256;
-    return (int)(b > 65536 ? 65536 : (b == 0 ? 1 : b));
-}
-
-int launch_to_canonical(DevVolume v, float* F, uint16_t* W, uint32_t* C, void* stream)
-{
-    hipLaunchKernelGGL(mvf_to_canonical_kernel, dim3(conv_blocks(v)), dim3(256), 0, (hipStream_t)stream,
-                       v, F, W, C);
+    const dim3 grid((n + 255) / 256);
+    hipStream_t s = (hipStream_t)stream;
+    if (n == 0) return 0;
+    if (plane == 0) hipLaunchKernelGGL(mvf_read_plane_kernel<float>, grid, dim3(256), 0, s, v, e0, n, (float*)out);
+    else if (plane == 1) hipLaunchKernelGGL(mvf_read_plane_kernel<uint16_t>, grid, dim3(256), 0, s, v, e0, n, (uint16_t*)out);
+    else hipLaunchKernelGGL(mvf_read_plane_kernel<uint32_t>, grid, dim3(256), 0, s, v, e0, n, (uint32_t*)out);
     return (int)hipGetLastError();
 }
 

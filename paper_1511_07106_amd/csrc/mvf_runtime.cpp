@@ -15,6 +15,7 @@
 #include <map>
 #include <set>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "mvf.h"
@@ -235,6 +236,7 @@ struct mvf_ctx {
     int fault_slab_allocs = 0;
     mvf_stats stats{};
     Arena arena;
+    hipEvent_t read_ev[Arena::kSlots / 2] = {};   // volume reads: a buffer of two slots is written
     Mailbox* mail = nullptr;       // in the arena's pinned memory
     std::vector<TimedPair> timed;
     std::vector<hipEvent_t> event_pool;
@@ -1575,6 +1577,8 @@ mvf_status mvf_destroy(mvf_ctx* c)
     if (c->diff_partials) (void)hipFree(c->diff_partials);
     if (c->extract_buf) (void)hipFree(c->extract_buf);
     if (c->track.dev) (void)hipFree(c->track.dev);
+    for (hipEvent_t e : c->read_ev)
+        if (e) (void)hipEventDestroy(e);
     if (c->tail) (void)hipEventDestroy(c->tail);
     if (c->d2h_stream) (void)hipStreamDestroy(c->d2h_stream);
     if (c->h2d_stream) (void)hipStreamDestroy(c->h2d_stream);
@@ -1840,6 +1844,78 @@ mvf_status mvf_volume_brick_summary(mvf_ctx* c, int32_t id, uint8_t* flag, uint8
     return MVF_OK;
 }
 
+}  // extern "C"
+
+namespace {
+
+// The n voxels' canonical planes (null: not wanted) of a volume, to the
+// caller's memory.  Kernels write chunks of them to the arena, which is idle
+// and pinned, and a few threads copy the chunks on as they arrive: the pages of
+// the caller's memory are mostly new, and the faults of one thread take longer
+// than the link.  (Device planes allocated for the call and copied to pageable
+// memory: 1340 us for integration and read of a 125 x 99 x 130 volume, now 520.)
+hipError_t read_planes(mvf_ctx* c, const DevVolume& dv, size_t n, float* F, uint16_t* W, uint8_t* rgba)
+{
+    struct Chunk { int plane; size_t e0, n; uint8_t* to; };
+    constexpr size_t kBytes = 2 * Arena::kSlotBytes;
+    constexpr int kBuffers = Arena::kSlots / 2, kThreads = 4;
+    static_assert(kBuffers % kThreads == 0, "a buffer's chunks belong to one thread");
+    uint8_t* const planes[3] = {reinterpret_cast<uint8_t*>(F), reinterpret_cast<uint8_t*>(W), rgba};
+    const size_t size[3] = {4, 2, 4};
+    std::vector<Chunk> chunks;
+    for (int p = 0; p < 3; ++p)
+        for (size_t e0 = 0; planes[p] && e0 < n; e0 += kBytes / size[p])
+            chunks.push_back(Chunk{p, e0, std::min(kBytes / size[p], n - e0), planes[p] + e0 * size[p]});
+    const int count = (int)chunks.size();
+    auto buffer = [&](int i) { return c->arena.host + (size_t)(i % kBuffers) * kBytes; };
+    auto start = [&](int i) {
+        const Chunk& k = chunks[i];
+        const int e = launch_read_plane(dv, k.plane, (uint32_t)k.e0, (uint32_t)k.n, buffer(i), nullptr);
+        return e ? (hipError_t)e : hipEventRecord(c->read_ev[i % kBuffers], nullptr);
+    };
+    for (int i = 0; i < kBuffers && i < count; ++i) {
+        if (!c->read_ev[i])
+            if (hipError_t e = hipEventCreateWithFlags(&c->read_ev[i], hipEventDisableTiming)) return e;
+    }
+    hipError_t err[kThreads] = {};
+    const int started = std::min(kBuffers, count);
+    for (int i = 0; i < started && !err[0]; ++i) err[0] = start(i);
+    if (err[0]) {
+        (void)hipDeviceSynchronize();   // nothing writes to the arena any more
+        return err[0];
+    }
+    const int nt = std::min(kThreads, count);
+    auto copy = [&](int t) {
+        hipError_t e = hipSetDevice(c->device);
+        for (int i = t; i < count && !e; i += kThreads) {
+            e = hipEventSynchronize(c->read_ev[i % kBuffers]);
+            if (e) break;
+            memcpy(chunks[i].to, buffer(i), chunks[i].n * size[chunks[i].plane]);
+            if (i + kBuffers < count) e = start(i + kBuffers);
+        }
+        err[t] = e;
+    };
+    std::thread helpers[kThreads];
+    int running = 1;
+    try {
+        for (; running < nt; ++running) helpers[running] = std::thread(copy, running);
+    } catch (...) {   // no more threads: the rest is done here
+    }
+    if (count) copy(0);
+    for (int t = running; t < nt; ++t) copy(t);
+    hipError_t all = hipSuccess;
+    for (int t = 0; t < kThreads; ++t) {
+        if (helpers[t].joinable()) helpers[t].join();
+        if (err[t] && !all) all = err[t];
+    }
+    if (all) (void)hipDeviceSynchronize();
+    return all;
+}
+
+}  // namespace
+
+extern "C" {
+
 mvf_status mvf_volume_read(mvf_ctx* c, int32_t id, float* F, uint16_t* W, uint8_t* rgba)
 {
     if (!c) return set_error(MVF_ERR_INVALID_ARG, "ctx is NULL");
@@ -1866,27 +1942,9 @@ mvf_status mvf_volume_read(mvf_ctx* c, int32_t id, float* F, uint16_t* W, uint8_
     view.dev = slab;
     DevVolume dv = make_dev(c, view);
     dv.id = id;
-    float* dF = nullptr;
-    uint16_t* dW = nullptr;
-    uint32_t* dC = nullptr;
-    mvf_status st = MVF_OK;
-    hipError_t e = hipSuccess;
-    if (F && (e = hipMalloc((void**)&dF, n * 4)) != hipSuccess) st = MVF_ERR_OOM;
-    if (st == MVF_OK && W && (e = hipMalloc((void**)&dW, n * 2)) != hipSuccess) st = MVF_ERR_OOM;
-    if (st == MVF_OK && rgba && (e = hipMalloc((void**)&dC, n * 4)) != hipSuccess) st = MVF_ERR_OOM;
-    if (st == MVF_OK) {
-        int le = launch_to_canonical(dv, dF, dW, dC, nullptr);
-        if (le) { st = MVF_ERR_HIP; e = (hipError_t)le; }
-    }
-    if (st == MVF_OK && (e = hipDeviceSynchronize()) != hipSuccess) st = MVF_ERR_HIP;
-    if (st == MVF_OK && F && (e = hipMemcpy(F, dF, n * 4, hipMemcpyDeviceToHost)) != hipSuccess) st = MVF_ERR_HIP;
-    if (st == MVF_OK && W && (e = hipMemcpy(W, dW, n * 2, hipMemcpyDeviceToHost)) != hipSuccess) st = MVF_ERR_HIP;
-    if (st == MVF_OK && rgba && (e = hipMemcpy(rgba, dC, n * 4, hipMemcpyDeviceToHost)) != hipSuccess) st = MVF_ERR_HIP;
-    if (dF) (void)hipFree(dF);
-    if (dW) (void)hipFree(dW);
-    if (dC) (void)hipFree(dC);
+    const hipError_t e = read_planes(c, dv, n, F, W, rgba);
     if (tmp_slab) (void)hipFree(tmp_slab);
-    if (st != MVF_OK) return set_error(st, "volume_read: %s", hipGetErrorString(e));
+    if (e != hipSuccess) return set_error(MVF_ERR_HIP, "volume_read: %s", hipGetErrorString(e));
     return MVF_OK;
 }
 

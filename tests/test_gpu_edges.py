@@ -391,3 +391,25 @@ def test_step_many_streams(mvf, n):
             np.testing.assert_array_equal(a, b)
         for k in oa[i]:
             np.testing.assert_array_equal(oa[i][k], ob[i][k])
+
+
+@pytest.mark.parametrize("dims", [(1024, 64, 8), (128, 64, 64), (259, 255, 257)])
+def test_read_in_chunks(mvf, dims):
+    """Volumes read in one chunk per plane exactly, in one more, and in more
+    chunks than there are buffers: the planes written come back (F where
+    observed, else 0), the same into memory that has been used before."""
+    log(f"volume read {dims}")
+    nx, ny, nz = dims
+    rng = np.random.default_rng(nx)
+    F = rng.standard_normal((nz, ny, nx), dtype=np.float32).clip(-1, 1)
+    W = rng.integers(0, 3, (nz, ny, nx), dtype=np.uint16)
+    Cc = rng.integers(0, 256, (nz, ny, nx, 4), dtype=np.uint8)
+    with mvf.Context() as ctx:
+        gid = ctx.grid((0.0, 0.0, 0.0), 0.01)
+        vid = ctx.volume(gid, (0, 0, 0), dims)
+        ctx.write_volume(vid, F, W, Cc)
+        for _ in range(2):
+            f, w, c = ctx.read_volume(vid)
+            np.testing.assert_array_equal(w, W)
+            np.testing.assert_array_equal(c, Cc)
+            np.testing.assert_array_equal(f, np.where(W > 0, F, np.float32(0)))
