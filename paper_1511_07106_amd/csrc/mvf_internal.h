@@ -314,6 +314,8 @@ int launch_ray_bounds_collect(const LaunchHeader* hdr, const DevVolume* vols, co
 int launch_ray_bounds_merge(const LaunchHeader* hdr, const DevFrame* frames, const int32_t* lists,
                             const int32_t* list_base, const int32_t* brick_base, RayBounds rb, int nstreams,
                             int max_cells_x, int max_cells_y, void* stream, TileOrder order = TileOrder{});
+// bytes (a multiple of 16) from device to pinned memory, both 16-byte aligned.
+int launch_swap_copy(const void* src, void* dst, size_t bytes, void* stream);
 // Elements [e0, e0 + n) of a volume's canonical plane (0: F, 1: weights, 2:
 // colours) to out, pinned host memory.
 int launch_read_plane(DevVolume v, int plane, uint32_t e0, uint32_t n, void* out, void* stream);

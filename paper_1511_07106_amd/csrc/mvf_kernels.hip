@@ -2148,6 +2148,46 @@ int launch_ray_bounds_merge(const LaunchHeader* hdr, const DevFrame* frames, con
 }
 
 // ---------------------------------------------------------------------------
+// Copy of a volume's slab to its pinned mirror.  Bound by the host link (57
+// GB/s each way).  Few blocks: the uploads that run beside it share the link,
+// and the frames' kernels the device.  (The runtime's copy took an engine of its
+// own choice: behind pending work 12 GB/s, and it held the calling thread for up
+// to 9 ms.  A frame over three volumes of 188 MB with room for one, calls in a
+// row: 15.8 ms with it, 9.4 now; 9.8 and 10.0 with 16 and 64 blocks, and with a
+// wait after each call 8.0 and 8.1 where 4 take 7.6.)
+// ---------------------------------------------------------------------------
+constexpr int kSwapBlocks = 4;
+
+__global__ __launch_bounds__(256) void mvf_swap_copy_kernel(const uint4* __restrict__ src, uint4* __restrict__ dst,
+                                                            size_t n)
+{
+    typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+    constexpr int N = 8;   // loads in flight per lane
+    const u4* const s = reinterpret_cast<const u4*>(src);
+    u4* const d = reinterpret_cast<u4*>(dst);
+    const size_t stride = (size_t)gridDim.x * 256u;
+    size_t i = (size_t)blockIdx.x * 256u + threadIdx.x;
+    for (; i + (N - 1) * stride < n; i += N * stride) {
+        u4 x[N];
+#pragma unroll
+        for (int k = 0; k < N; ++k) x[k] = s[i + k * stride];
+#pragma unroll
+        for (int k = 0; k < N; ++k) __builtin_nontemporal_store(x[k], &d[i + k * stride]);
+    }
+    for (; i < n; i += stride) __builtin_nontemporal_store(s[i], &d[i]);
+    __threadfence_system();
+}
+
+int launch_swap_copy(const void* src, void* dst, size_t bytes, void* stream)
+{
+    if (((uintptr_t)src | (uintptr_t)dst | bytes) & 15) return (int)hipErrorInvalidValue;
+    if (!bytes) return 0;
+    hipLaunchKernelGGL(mvf_swap_copy_kernel, dim3(kSwapBlocks), dim3(256), 0, (hipStream_t)stream, (const uint4*)src,
+                       (uint4*)dst, bytes / 16);
+    return (int)hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
 // Layout conversion between brick-linear device planes and canonical
 // x-fastest planes.
 // ---------------------------------------------------------------------------

@@ -476,7 +476,7 @@ mvf_status swap_out(mvf_ctx* c, Volume& v, hipStream_t stream, bool keep_slab_po
     std::vector<hipEvent_t> chunks;
     for (size_t off = 0; off < v.bytes; off += kSwapChunk) {
         const size_t n = std::min(kSwapChunk, v.bytes - off);
-        CHECK_HIP(hipMemcpyAsync(v.host + off, v.dev + off, n, hipMemcpyDeviceToHost, c->d2h_stream));
+        CHECK_LAUNCH(launch_swap_copy(v.dev + off, v.host + off, n, c->d2h_stream));
         hipEvent_t e;
         CHECK_ST(get_event(c, &e));
         CHECK_HIP(hipEventRecord(e, c->d2h_stream));

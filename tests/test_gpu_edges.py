@@ -413,3 +413,30 @@ def test_read_in_chunks(mvf, dims):
             np.testing.assert_array_equal(w, W)
             np.testing.assert_array_equal(c, Cc)
             np.testing.assert_array_equal(f, np.where(W > 0, F, np.float32(0)))
+
+
+@pytest.mark.parametrize("dims", [(8, 8, 8), (9, 17, 8), (64, 40, 33), (136, 128, 96), (300, 290, 280)])
+def test_swap_out_sizes(mvf, dims):
+    """Slabs smaller than one round of the copy to the mirror, with remainders,
+    and of several chunks: the planes come back from the mirror, and from the
+    device after a swap in."""
+    log(f"swap out {dims}")
+    nx, ny, nz = dims
+    rng = np.random.default_rng(nx)
+    F = rng.standard_normal((nz, ny, nx), dtype=np.float32).clip(-1, 1)
+    W = rng.integers(1, 4, (nz, ny, nx), dtype=np.uint16)
+    Cc = rng.integers(0, 256, (nz, ny, nx, 4), dtype=np.uint8)
+    with mvf.Context() as ctx:
+        gid = ctx.grid((0.0, 0.0, 0.0), 0.01)
+        vid = ctx.volume(gid, (0, 0, 0), dims)
+        ctx.write_volume(vid, F, W, Cc)
+        for _ in range(2):
+            ctx.evict(vid, swap_out=True)
+            for again in range(2):
+                f, w, c = ctx.read_volume(vid)
+                np.testing.assert_array_equal(f, F)
+                np.testing.assert_array_equal(w, W)
+                np.testing.assert_array_equal(c, Cc)
+                if not again:
+                    ctx.swap_in(vid)
+        assert ctx.stats()["swaps_out"] == 2 and ctx.stats()["swaps_in"] == 2
