@@ -296,29 +296,32 @@ static __device__ __forceinline__ void solve_update(const double* tot, TrackStat
 
 // One Gauss-Newton step over the current maps (w x h).  Per block the sums of
 // its pairs (A upper triangle 21, b 6, pairs, sum r^2) go to
-// partials[block * kTrackSums ...]; the last block to finish sums them in block
+// partials[block * kTrackSums ...]; the last block to finish sums them in a fixed
 // order, writes the step's statistics and updates the estimate.
 //
 // Bound: load latency, the chain own maps -> model maps -> reduction -> solve.
 // So a thread's four pixels are loaded together and their model samples
-// gathered together, and the partials reach LDS in wide loads before one lane
-// per sum adds them in order.  16 us a step at 640x480 and 9 us at 160x120: of
-// the 16, association 5, reduction 2, ticket 1.5, sum 4.7 (300 dependent
-// additions), solve 2.8.  As an association kernel of 14 us, whose threads took
-// one pixel after the other, and a solve kernel of 71 us, whose lanes read the
-// partials from memory one by one, a 19-step call took 1.16 ms; now 0.33 ms.
+// gathered together, and the last block adds the partials in eight runs side by
+// side, a lane's loads in flight together (in one run, 300 additions one after
+// the other, the sum took 4.7 us of a step).  13 us a step at 640x480: before,
+// 16.5; as an association kernel of 14 us, whose threads took one pixel after
+// the other, and a solve kernel of 71 us, whose lanes read the partials from
+// memory one by one, 85.
 //
 // The partials cross the XCDs' L2 caches: they are stored and loaded with
 // device-scope atomics, and a block takes its ticket when its stores have
 // reached that scope.  (A fence would write the whole L2 back, once a block.)
-constexpr int kSolveChunk = 128;   // blocks' partials in LDS at a time
+constexpr int kSegLanes = 32;                            // lanes of a run of blocks, one per sum
+constexpr int kSegments = kTrackThreads / kSegLanes;
+constexpr int kSegLoads = 20;                            // a lane's loads in flight
+static_assert(kTrackSums <= kSegLanes, "one lane per sum");
 __global__ __launch_bounds__(kTrackThreads) void mvf_icp_step_kernel(TrackLaunch L, int nblocks, int step,
                                                                      TrackState* out)
 {
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     __shared__ double part[kTrackThreads / 64][kTrackSums];
-    __shared__ double chunk[kSolveChunk * kTrackSums];
+    __shared__ double seg_sum[kSegments][kTrackSums];
     __shared__ double tot[kTrackSums];
     __shared__ bool last;
     double acc[32];
@@ -419,35 +422,31 @@ __global__ __launch_bounds__(kTrackThreads) void mvf_icp_step_kernel(TrackLaunch
     if (threadIdx.x == 0) last = atomicAdd(&L.state->ticket, 1u) + 1 == (uint32_t)nblocks;
     __syncthreads();
     if (!last) return;
-    // the step's sums: block order, one lane per sum
+    // the step's sums, one lane per sum: the blocks in kSegments runs, each in
+    // order, then the runs in order
+    {
+        const int sum = threadIdx.x % kSegLanes, seg = threadIdx.x / kSegLanes;
+        const int per = (nblocks + kSegments - 1) / kSegments;
+        const int b1 = min(nblocks, (seg + 1) * per);
+        double s = 0.0;
+        for (int b0 = seg * per; b0 < b1; b0 += kSegLoads) {
+            double x[kSegLoads];
+#pragma unroll
+            for (int i = 0; i < kSegLoads; ++i)
+                x[i] = b0 + i < b1 && sum < kTrackSums
+                           ? __hip_atomic_load(&L.partials[(size_t)(b0 + i) * kTrackSums + sum], __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT)
+                           : 0.0;
+#pragma unroll
+            for (int i = 0; i < kSegLoads; ++i) s += x[i];
+        }
+        if (sum < kTrackSums) seg_sum[seg][sum] = s;
+    }
+    __syncthreads();
     double s = 0.0;
-    constexpr int kLoads = (kSolveChunk * kTrackSums + kTrackThreads - 1) / kTrackThreads;
-    double x[kLoads];
-    auto load = [&](int b0) {
-        const int n = min(kSolveChunk, nblocks - b0) * kTrackSums;
-        const double* src = L.partials + (size_t)b0 * kTrackSums;
+    if (threadIdx.x < kTrackSums) {
 #pragma unroll
-        for (int i = 0; i < kLoads; ++i) {
-            const int at = i * kTrackThreads + (int)threadIdx.x;
-            x[i] = at < n ? __hip_atomic_load(&src[at], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0;
-        }
-    };
-    load(0);
-    for (int b0 = 0; b0 < nblocks; b0 += kSolveChunk) {
-        const int nb = min(kSolveChunk, nblocks - b0);
-        __syncthreads();   // the last chunk has been added
-#pragma unroll
-        for (int i = 0; i < kLoads; ++i) {
-            const int at = i * kTrackThreads + (int)threadIdx.x;
-            if (at < nb * kTrackSums) chunk[at] = x[i];
-        }
-        __syncthreads();
-        // the next chunk's loads run beside the additions
-        if (b0 + kSolveChunk < nblocks) load(b0 + kSolveChunk);
-        if (threadIdx.x < kTrackSums) {
-#pragma unroll 16
-            for (int b = 0; b < nb; ++b) s += chunk[b * kTrackSums + threadIdx.x];
-        }
+        for (int i = 0; i < kSegments; ++i) s += seg_sum[i][threadIdx.x];
     }
     if (threadIdx.x < kTrackSums) tot[threadIdx.x] = s;
     __syncthreads();
