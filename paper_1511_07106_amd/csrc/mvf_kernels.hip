@@ -1450,11 +1450,12 @@ static __device__ __forceinline__ int last_to_first(int x)
 // group jumps past the longest clear run, otherwise the group evaluates
 // kEvalWindows consecutive windows (lane j: samples w0 + w*P + j, all their
 // gathers in flight together) and takes the first crossing in sample order,
-// exactly as the sequential march would find it.  When the sample before
-// the round was not evaluated, w0 is that sample so that it serves as the
-// near end.  Rays that graze a surface evaluate long stretches of samples;
-// two windows a round halve their rounds of dependent loads (measured at every
-// P: one window and four were slower, by 10-40 %).
+// exactly as the sequential march would find it.  The sample before the round
+// is only evaluated (w0 one earlier, in a round of its own) if the first one may
+// be a far end, F <= 0, and it has not been: always starting at it took 426 us
+// for 16 rooms, 414 without.  Rays that graze a surface evaluate long stretches
+// of samples; two windows a round halve their rounds of dependent loads
+// (measured at every P: one window and four were slower, by 10-40 %).
 constexpr int kEvalWindows = 2;
 
 template <int P>
@@ -1486,6 +1487,7 @@ static __device__ bool march_volume_group(const DevVolume& V, const Ray& r, floa
     int prev_k = -2;
     int prev_ok = 0;
     float Fprev = 0.0f;
+    bool back = false;   // this round starts at the sample before k
     int k = k0;
     while (k <= k1) {
         const int sk = k + j;
@@ -1504,10 +1506,10 @@ static __device__ bool march_volume_group(const DevVolume& V, const Ray& r, floa
             k = clear;
             continue;
         }
-        // on to the first sample that must be evaluated, from the one before it
-        // on unless that has been evaluated
+        // on to the first sample that must be evaluated
         k -= group_max<P>(reach == kMust ? -j : -P);
-        const int w0 = (prev_k != k - 1) ? k - 1 : k;
+        const bool known = prev_k == k - 1;   // the sample before it has been evaluated
+        const int w0 = back ? k - 1 : k;
         const int sidx = w0 + j;
         // evaluation round: kEvalWindows windows of P consecutive samples
         // from w0, lane j taking sample w0 + w*P + j of window w.  Samples of
@@ -1543,15 +1545,21 @@ static __device__ bool march_volume_group(const DevVolume& V, const Ray& r, floa
                 Fs[w] = Fk;
                 float Fn = __int_as_float(lane_before(__float_as_int(Fk)));
                 int okn = lane_before(ok);
-                if (j == 0) { Fn = Fprev; okn = prev_ok; }
+                if (j == 0) { Fn = Fprev; okn = w == 0 ? prev_ok && known : prev_ok; }
                 Fns[w] = Fn;
                 // the window's last sample is the next one's previous
                 Fprev = __int_as_float(last_to_first<P>(__float_as_int(Fk)));
                 prev_ok = last_to_first<P>(ok);
                 if (sidx + w * P >= k && okn && ok && Fn > 0.0f && Fk <= 0.0f) jc = min(jc, w * P + j);
+                // its near end first
+                if (w == 0 && j == 0 && !back && !known && ok && Fk <= 0.0f) jc = -1;
             }
         }
         jc = -group_max<P>(-jc);
+        if (jc < 0) {
+            back = true;
+            continue;
+        }
         if (jc < S * P) {
             const int wc = jc / P, lc = jc - wc * P;
             float Fn = 0.0f, Fk = 0.0f;
@@ -1574,6 +1582,7 @@ static __device__ bool march_volume_group(const DevVolume& V, const Ray& r, floa
         // k1 the march ends)
         prev_k = w0 + S * P - 1;
         k = prev_k + 1;
+        back = false;
     }
     return false;
 }
@@ -1707,7 +1716,7 @@ static __device__ __forceinline__ void raycast_pixel(const RaycastLaunch& L, CPT
 // 8: 50, 47; 16: 79, 37.  With few lanes for the many quick tiles and many for
 // the few slow ones the launch takes 50 us on a young map and 46 on a settled
 // one (P = 4 throughout: 75 and 52; with the instructions of an axis by axis
-// march 106 and more); 16 rooms of up to three 384^3 volumes: 426 us (645,
+// march 106 and more); 16 rooms of up to three 384^3 volumes: 414 us (645,
 // 1001), 128^3 at 320 x 240: 22 us (24, 41).
 // Not taken: one lane testing two bricks a round (93 us), all of a tile's rays
 // skipping before any evaluates (its longest tile 95 -> 271 us), slow tiles
