@@ -58,6 +58,10 @@ constexpr int kDistCap = 12;
 
 // 64-bit words per brick column of the colm flag bits
 MVF_HD int col_words(int bd2) { return (bd2 + 63) >> 6; }
+// Lines of the brick distance transform: (bx, kDistRows columns along y,
+// 64-brick word of the columns).
+constexpr int kDistRows = 64 - 2 * kDistCap;
+MVF_HD int dist_lines(const int bd[3]) { return bd[0] * ((bd[1] + kDistRows - 1) / kDistRows) * col_words(bd[2]); }
 
 struct DevVolume {
     float* F;
@@ -80,6 +84,7 @@ struct DevVolume {
     int32_t w_max;
     int32_t frame;       // index of the stream's frame in the frame table
     int32_t zt_base;     // first entry of this volume in the launch's z table
+    int32_t line_base;   // distance lines of the launch's volumes before this one
     // world box that a raycast looks for samples in: the sample domain grown
     // by a voxel
     float ray_lo[3], ray_hi[3];
@@ -139,6 +144,7 @@ struct LaunchHeader {
     int32_t first_wave;    // raycast: 1 = start from no hit, 0 = merge with best_t/best_id
     RayParams rp;
     int32_t total_z;       // entries of the integration z table (sum of 8 * bd[2])
+    int32_t total_lines;   // distance lines over all volumes of the table
     int32_t rb_parity;     // raycast range bounds: which half of RayBounds::counts this launch fills
     int32_t list_parity;   // integration: which of the two visited-item counts this launch uses
 };
@@ -297,12 +303,13 @@ int launch_raycast(const RaycastLaunch& L, int blocks, void* stream, void* ev_st
                    void* ev_stop = nullptr);
 // Column flag words from the brick flags.
 int launch_column_flags(DevVolume v, void* stream);
-// Brick distance transform of every volume in the table (3 passes).
-// brick_base: nvol + 1 prefix sums of the volumes' brick counts (each a
+// Brick distance transform of every volume in the table; lines and bricks:
+// their totals, for the grid (the header's count).  brick_base: nvol + 1 prefix sums of the volumes' brick counts (each a
 // multiple of 64).  With frames and rb.entries set, the last pass also
 // collects the range-bound footprints (as launch_ray_bounds_collect).
 int launch_brick_distance(const LaunchHeader* hdr, const DevVolume* vols, const int32_t* brick_base,
-                          int blocks, void* stream, const DevFrame* frames = nullptr, RayBounds rb = RayBounds{});
+                          int lines, int bricks, void* stream, const DevFrame* frames = nullptr,
+                          RayBounds rb = RayBounds{});
 // Range-bound footprints of the bricks of every volume of the table whose
 // cell mask is not empty, for the volume's frame.
 int launch_ray_bounds_collect(const LaunchHeader* hdr, const DevVolume* vols, const int32_t* brick_base,

@@ -1827,7 +1827,7 @@ int launch_column_flags(DevVolume v, void* stream)
 // Brick distance transform and cell masks: one launch for every volume of
 // the table, two kinds of wavefronts.
 //
-// Distance lines (the first kDistWaves wavefronts): one per (bx, chunk of
+// Distance lines (the first dist_waves wavefronts): one per (bx, chunk of
 // kDistRows columns along y, 64-brick word w of the columns).  Lane l holds
 // the row y = y0 - kDistCap + l and ORs that row's column words along x
 // outwards, X_k = OR over |dx| <= k; C_k, the OR of X_k over the lanes
@@ -1845,8 +1845,11 @@ int launch_column_flags(DevVolume v, void* stream)
 // bounds, the brick's footprint.
 // ---------------------------------------------------------------------------
 constexpr int kDistSide = 2 * kDistCap + 1;
-constexpr int kDistRows = 64 - 2 * kDistCap;  // output columns of a distance line
-constexpr int kDistWaves = 256;               // wavefronts of the distance lines
+// Wavefronts of the distance lines (1.3 us a line): one a line up to half of
+// what the device holds.  With 256 for any number of volumes, each of which
+// walked the whole volume table for its lines, 48 volumes of up to 384^3 took
+// 42 us, now 30; eight of 257^3 12.5 and 8.5.
+constexpr int kDistWavesMax = 2048;
 
 // Dilation by r (r < 16) in shift steps of 1, 2, 4 and the rest: a step s
 // with s <= c + 1 widens the covered offsets [-c, c] to [-(c + s), c + s]
@@ -1963,39 +1966,35 @@ static __device__ void distance_line(const DevVolume& V, int bx, int y0, int w, 
 // at most 96 VGPRs: five wavefronts per SIMD still hold every brick wavefront of
 // a 512^3 volume at once
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void mvf_brick_distance_kernel(
-    const LaunchHeader* hdr, const DevVolume* vols, const int32_t* brick_base, const DevFrame* frames, RayBounds rb)
+    const LaunchHeader* hdr, const DevVolume* vols, const int32_t* brick_base, const DevFrame* frames, RayBounds rb,
+    int dist_waves)
 {
     const int lane = threadIdx.x & 63;
     const int wave = wave_uniform((int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)));
     const int nvol = cptr(hdr)->nvol;
-    if (wave < kDistWaves) {
-        // the lines of all volumes, numbered volume by volume, are dealt to
-        // the distance wavefronts in turn; acc = lines before volume v,
-        // modulo kDistWaves
-        int acc = 0;
-        for (int v = 0; v < nvol; ++v) {
-            CPTR(DevVolume) const Vp = cptr(vols) + v;
-            const int nw = col_words(Vp->bd[2]);
-            const int nyc = (Vp->bd[1] + kDistRows - 1) / kDistRows;
-            const int nl = Vp->bd[0] * nyc * nw;
-            int first = (wave - acc) % kDistWaves;
-            if (first < 0) first += kDistWaves;
-            acc = (int)(((long long)acc + nl) % kDistWaves);
-            if (first >= nl) continue;
-            const DevVolume V = *Vp;
-            for (int t = first; t < nl; t += kDistWaves) {
-                const int w = t % nw, r = t / nw;
-                const int yc = r % nyc, bx = r / nyc;
-                if (nw == 1) distance_line<false>(V, bx, yc * kDistRows, w, lane);
-                else distance_line<true>(V, bx, yc * kDistRows, w, lane);
+    if (wave < dist_waves) {
+        const int lines = cptr(hdr)->total_lines;
+        for (int l = wave; l < lines; l += dist_waves) {
+            int lo = 0, hi = nvol - 1;
+            while (lo < hi) {
+                const int mid = (lo + hi + 1) >> 1;
+                if (cptr(vols)[mid].line_base <= l) lo = mid; else hi = mid - 1;
             }
+            lo = wave_uniform(lo);
+            const DevVolume V = cptr(vols)[lo];
+            const int nw = col_words(V.bd[2]), nyc = (V.bd[1] + kDistRows - 1) / kDistRows;
+            const int t = l - V.line_base;
+            const int w = t % nw, r = t / nw;
+            const int yc = r % nyc, bx = r / nyc;
+            if (nw == 1) distance_line<false>(V, bx, yc * kDistRows, w, lane);
+            else distance_line<true>(V, bx, yc * kDistRows, w, lane);
         }
         return;
     }
     const int total = cptr(hdr)->total_bricks;
-    const int bwaves = (int)(gridDim.x * (blockDim.x >> 6)) - kDistWaves;
+    const int bwaves = (int)(gridDim.x * (blockDim.x >> 6)) - dist_waves;
     CPTR(int32_t) const bbase = cptr(brick_base);
-    for (int g = wave - kDistWaves; g * 64 < total; g += bwaves) {
+    for (int g = wave - dist_waves; g * 64 < total; g += bwaves) {
         const int gw = g * 64;
         int lo = 0, hi = nvol - 1;
         while (lo < hi) {
@@ -2033,14 +2032,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void m
     }
 }
 
-// blocks: wavefront groups of four for the bricks; the distance lines get
-// kDistWaves more wavefronts
-int launch_brick_distance(const LaunchHeader* hdr, const DevVolume* vols, const int32_t* brick_base, int blocks,
-                          void* stream, const DevFrame* frames, RayBounds rb)
+int launch_brick_distance(const LaunchHeader* hdr, const DevVolume* vols, const int32_t* brick_base, int lines,
+                          int bricks, void* stream, const DevFrame* frames, RayBounds rb)
 {
-    if (blocks <= 0) return 0;
-    hipLaunchKernelGGL(mvf_brick_distance_kernel, dim3(blocks + kDistWaves / 4), dim3(256), 0, (hipStream_t)stream,
-                       hdr, vols, brick_base, frames, rb);
+    if (bricks <= 0) return 0;
+    const int dist_blocks = (min(max(lines, 1), kDistWavesMax) + 3) / 4;
+    const int blocks = min(1024, (bricks + 255) / 256);
+    hipLaunchKernelGGL(mvf_brick_distance_kernel, dim3(dist_blocks + blocks), dim3(256), 0, (hipStream_t)stream, hdr,
+                       vols, brick_base, frames, rb, 4 * dist_blocks);
     return (int)hipGetLastError();
 }
 

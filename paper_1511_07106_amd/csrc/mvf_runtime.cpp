@@ -1028,7 +1028,7 @@ mvf_status integrate_plain(mvf_ctx* c, int sid, const mvf_frame* f, const float*
         DevFrame* fr = w2.alloc<DevFrame>(1, &dfr);
         if (!fr) return set_error(MVF_ERR_INVALID_ARG, "arena overflow");
         *fr = frame;
-        struct Per { LaunchHeader* dh; DevVolume* dv; int32_t* dib; int32_t* dbb; int items; int bricks; };
+        struct Per { LaunchHeader* dh; DevVolume* dv; int32_t* dib; int32_t* dbb; int items, bricks, lines; };
         std::vector<Per> per;
         for (const std::vector<int>& group : launches[wi]) {
             Per p;
@@ -1046,6 +1046,8 @@ mvf_status integrate_plain(mvf_ctx* c, int sid, const mvf_frame* f, const float*
                 dv[j] = make_dev(c, v);
                 dv[j].frame = 0;
                 dv[j].zt_base = h->total_z;
+                dv[j].line_base = h->total_lines;
+                h->total_lines += dist_lines(v.bd);
                 ib[j] = h->total_items;
                 bb[j] = h->total_bricks;
                 h->total_z += kBrick * v.bd[2];
@@ -1056,6 +1058,7 @@ mvf_status integrate_plain(mvf_ctx* c, int sid, const mvf_frame* f, const float*
             bb[group.size()] = h->total_bricks;
             p.items = h->total_items;
             p.bricks = h->total_bricks;
+            p.lines = h->total_lines;
             h->list_parity = sc->list_parity;
             sc->list_parity ^= 1;
             per.push_back(p);
@@ -1085,7 +1088,7 @@ mvf_status integrate_plain(mvf_ctx* c, int sid, const mvf_frame* f, const float*
             CHECK_ST(timing_pair(c, &t0, &t1));
             CHECK_LAUNCH(launch_integrate(L, (p.items + 3) / 4 + (order ? 1 : 0), stream, t0, t1));
             CHECK_ST(timing_push(c, t0, t1, 0));
-            CHECK_LAUNCH(launch_brick_distance(p.dh, p.dv, p.dbb, std::min(1024, (p.bricks + 255) / 256), stream));
+            CHECK_LAUNCH(launch_brick_distance(p.dh, p.dv, p.dbb, p.lines, p.bricks, stream));
             c->stats.integrate_launches += 1;
         }
         CHECK_ST(arena_release(c, slot2, stream));
@@ -1214,11 +1217,12 @@ mvf_status recompute_summaries(mvf_ctx* c, const Volume& v, hipStream_t stream)
     memset(h, 0, sizeof(*h));
     h->nvol = 1;
     h->total_bricks = (int)align_up(v.nbricks, 64);
+    h->total_lines = dist_lines(v.bd);
     *vt = dv;
     bb[0] = 0;
     bb[1] = h->total_bricks;
     CHECK_ST(arena_upload(c, w, stream));
-    CHECK_LAUNCH(launch_brick_distance(dh, dvv, dbb, std::min<int>(1024, ((int)v.nbricks + 255) / 256), stream));
+    CHECK_LAUNCH(launch_brick_distance(dh, dvv, dbb, h->total_lines, h->total_bricks, stream));
     return arena_release(c, slot, stream);
 }
 
@@ -2092,12 +2096,13 @@ mvf_status mvf_step(mvf_ctx* c, int32_t n, const mvf_stream_frame* frames, const
         max_h = std::max(max_h, frames[i].frame.height);
     }
     // capacities from the whole set (every wave is a subset of it)
-    int ztotal = 0, items_total = 0, bricks_total = 0;
+    int ztotal = 0, items_total = 0, bricks_total = 0, lines_total = 0;
     for (int id : all) {
         const Volume& v = c->vols[id];
         ztotal += kBrick * v.bd[2];
         items_total += v.bd[0] * v.bd[1] * ((v.bd[2] + sch.zchunk - 1) / sch.zchunk);
         bricks_total += (int)align_up(v.nbricks, 64);
+        lines_total += dist_lines(v.bd);
     }
     bool same_shape = G.valid && G.n == n && (int)all.size() <= G.max_vols && max_w <= G.max_w && max_h <= G.max_h &&
                       ztotal <= G.ztab_cap && items_total <= G.visit_cap && bricks_total <= G.rb_entries_cap &&
@@ -2199,7 +2204,7 @@ mvf_status mvf_step(mvf_ctx* c, int32_t n, const mvf_stream_frame* frames, const
         int32_t* lb = reinterpret_cast<int32_t*>(img + G.off_lbase);
         int32_t* tb = reinterpret_cast<int32_t*>(img + G.off_tbase);
         int32_t* bbase = reinterpret_cast<int32_t*>(img + G.off_bbase);
-        int nbr = 0, nv = 0, items = 0, zt = 0, tiles = 0;
+        int nbr = 0, nv = 0, items = 0, zt = 0, lines = 0, tiles = 0;
         const int zc = sch.zchunk;
         lb[0] = 0;
         tb[0] = 0;
@@ -2238,6 +2243,8 @@ mvf_status mvf_step(mvf_ctx* c, int32_t n, const mvf_stream_frame* frames, const
                 vt[nv] = make_dev(c, v);
                 vt[nv].frame = i;
                 vt[nv].zt_base = zt;
+                vt[nv].line_base = lines;
+                lines += dist_lines(v.bd);
                 zt += kBrick * v.bd[2];
                 ib[nv] = items;
                 bbase[nv] = nbr;
@@ -2259,6 +2266,7 @@ mvf_status mvf_step(mvf_ctx* c, int32_t n, const mvf_stream_frame* frames, const
         h->total_bricks = nbr;
         h->total_items = items;
         h->total_z = zt;
+        h->total_lines = lines;
         h->zchunk = zc;
         h->nstreams = n;
         h->total_tiles = tiles;
@@ -2296,9 +2304,10 @@ mvf_status mvf_step(mvf_ctx* c, int32_t n, const mvf_stream_frame* frames, const
             G.integ_blocks = (sch.persistent ? c->n_cus * 8 : std::max(c->n_cus * 8, (items_total + 3) / 4)) + 1;
             if (!e2) e2 = launch_integrate(IL, G.integ_blocks, cs);
             // the last distance pass also collects the raycast range-bound
-            // footprints; the merge folds them per cell
+            // footprints; the merge folds them per cell (the launch is there for
+            // volumes of later steps also when this one has none)
             const RayBounds RB{G.rb_entries, G.rb_counts, G.max_vols};
-            if (!e2) e2 = launch_brick_distance(dh, dvols, dbb, c->n_cus * 4, cs, dframes, RB);
+            if (!e2) e2 = launch_brick_distance(dh, dvols, dbb, lines_total, std::max(bricks_total, 64), cs, dframes, RB);
             if (!e2) e2 = launch_ray_bounds_merge(dh, dframes, dlists, dlb, dbb, RB, n, G.max_cells_x, G.max_cells_y, cs);
             RaycastLaunch RL{dh, dvols, dframes, dlists, dlb, dtb, G.tile_cost, G.tile_order};
             int e3 = e2 ? e2 : launch_raycast(RL, IL.order.max_blocks, cs);

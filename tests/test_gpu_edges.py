@@ -293,7 +293,8 @@ def test_raycast_tile_levels(mvf, w, h):
 @pytest.mark.parametrize("count", [2, 4, 5])
 def test_integrate_volumes_together(mvf, count):
     """Volumes of one plain integration share launches up to 2^18 work items
-    (four of these slabs; the fifth has a launch of its own): each volume the
+    (four of these slabs; the fifth has a launch of its own), and more distance
+    lines than wavefronts for them: each volume and its brick summary the
     same bit for bit as when it is alone in a context."""
     log(f"integrate {count} slabs together")
     rng = np.random.default_rng(count)
@@ -310,7 +311,7 @@ def test_integrate_volumes_together(mvf, count):
         ids = [ctx.volume(gid, o, dims) for o in off]
         for _ in range(2):
             ctx.integrate(t(d), t(rgb), T, K)
-        return [ctx.read_volume(i) for i in ids]
+        return [ctx.read_volume(i) + ctx.brick_summary(i) for i in ids]
 
     with mvf.Context() as ctx:
         got = fuse(ctx, offs)
