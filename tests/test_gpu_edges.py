@@ -441,3 +441,38 @@ def test_swap_out_sizes(mvf, dims):
                 if not again:
                     ctx.swap_in(vid)
         assert ctx.stats()["swaps_out"] == 2 and ctx.stats()["swaps_in"] == 2
+
+
+def test_calls_on_alternating_streams(mvf):
+    """Each call runs after the one before it also on another stream: plain
+    integrations and raycasts dealt over three streams give the single
+    stream's maps and volumes bit for bit."""
+    import torch
+    log("alternating streams")
+    rng = np.random.default_rng(3)
+    w, h, n = 160, 120, 12
+    K = np.array([140.0, 141.0, w / 2 - 0.3, h / 2 + 0.2], np.float32)
+    T = [np.array([[1.0, 0.0, 0.0, 1.0 + 0.02 * i], [0.0, 1.0, 0.0, 1.0], [0.0, 0.0, 1.0, -0.3]]) for i in range(n)]
+    frames = [t(_random_depth(rng, w, h, 1.0, 1.4)) for _ in range(n)]
+    torch.cuda.synchronize()
+
+    def run(streams):
+        with mvf.Context() as ctx:
+            gid = ctx.grid((0.0, 0.0, 0.0), 0.01, 4.0, 128)
+            ids = [ctx.volume(gid, o, (100, 100, 128)) for o in ((0, 0, 0), (99, 0, 0), (0, 99, 0), (99, 99, 0))]
+            outs = [ctx.raycast(T[i], K, w, h) for i in range(n)]
+            torch.cuda.synchronize()
+            for i in range(n):
+                ctx.integrate(frames[i], None, T[i], K, stream=streams[(2 * i) % len(streams)])
+                ctx.raycast(T[i], K, w, h, out=outs[i], stream=streams[(2 * i + 1) % len(streams)])
+            torch.cuda.synchronize()
+            return [ctx.read_volume(i) for i in ids], [{k: v.cpu().numpy() for k, v in o.items()} for o in outs]
+
+    (va, oa), (vb, ob) = run([torch.cuda.Stream() for _ in range(3)]), run([None])
+    assert (vb[0][1] > 0).any()
+    for a, b in zip(va, vb):
+        for x, y in zip(a, b):
+            np.testing.assert_array_equal(x, y)
+    for a, b in zip(oa, ob):
+        for k in b:
+            np.testing.assert_array_equal(a[k], b[k])
