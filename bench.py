@@ -14,11 +14,11 @@ Phases (all run by default):
                mvf_integrate + mvf_raycast calls (each kernel timed with HIP
                events: the roofline figures come from here)
   single_step  the same volume through mvf_step (the per-frame sequence
-               replayed as a HIP graph); the headline value
+               in one call); the headline value
   tiled        8 volumes of 257^3 at offsets {0,255}^3 (same voxels), plain
                per-volume calls
   batched      the same 8 volumes through mvf_step (one persistent launch each
-               for integration and raycast, replayed as a HIP graph)
+               for integration and raycast)
   probe        roofline probe (not a workload of the paper): one 512^3 volume
                wholly inside the view in front of a far plane, so that every
                voxel is updated in every frame (1.6 GB of TSDF traffic per
@@ -222,7 +222,7 @@ def phase_small(mvf, torch, reps=6, warmup=1):
     the ten 320x240 frames of the small room (3 spheres) on its 1 m circle;
     each step integrates one frame and raycasts its view.  The ten frames are
     replayed `reps` times after `warmup` passes (each pass fuses them again),
-    through mvf_step (a graph replay per frame) and through the plain calls."""
+    through mvf_step (a call per frame) and through the plain calls."""
     from synth import scenes as S
     seq = S.small_room_sequence(seed=1)
     K = seq.K.as_array()
@@ -434,7 +434,7 @@ CORRIDOR_CLASSES = [(512, 4), (384, 6), (256, 6)]
 def phase_corridor(mvf, torch, n_steps=40, stride=10, classes=CORRIDOR_CLASSES, budget_gb=8.0):
     """Dynamic placement down the 20 m corridor: every `stride`-th frame of the
     2000-frame walk is integrated into the live volumes and raycast in one
-    mvf_step (one graph replay, or one per wave when the live volumes exceed
+    mvf_step (one chain of launches, or one per wave when the live volumes exceed
     the budget), then the endpoint-count placement adds/removes volumes of
     three sizes (512^3, 384^3, 256^3 at 2.93 mm: 1.5, 1.125 and 0.75 m; at
     most 4, 6 and 6 live, the largest taking the highest-count regions,
@@ -768,7 +768,7 @@ def main():
     ap.add_argument("--no-cpu", action="store_true", help="skip the CPU oracle baseline")
     ap.add_argument("--phases", default=DEFAULT_PHASES, help="comma list of phases (default: all)")
     ap.add_argument("--schedule-cache", default=None,
-                    help="path prefix of the captured phases' schedule files: read when present (no tuning), "
+                    help="path prefix of the batched phases' schedule files: read when present (no tuning), "
                          "else tuned and written (to profile a run with the schedule of an unprofiled one)")
     ap.add_argument("--copy-probe-mib", type=int, default=0,
                     help="after the phases, copy a buffer of this size 5 times (counter calibration)")
@@ -852,7 +852,7 @@ def main():
         del a, b
     except RuntimeError:
         pass
-    # headline: the single 512^3 volume through the graph path; the roofline
+    # headline: the single 512^3 volume through the batched path; the roofline
     # comes from the plain phase, whose kernels are timed one by one
     core = {k: v for k, v in phases.items() if k not in EXTRA_PHASES}
     if not core:
@@ -863,7 +863,7 @@ def main():
     steps = args.steps
     # roofline of the integration kernel
     upd, band = main_ph["voxels_updated"], main_ph["voxels_band"]
-    # the graph path counts no launches of its own: one integration launch per step
+    # the batched path counts no launches of its own: one integration launch per step
     launches = main_ph["integrate_launches"] or steps
     bytes_per_launch = (B_UPDATED * upd + B_BAND * band + B_PIXEL * W_IMG * H_IMG * steps) / launches
     achieved = None
@@ -900,7 +900,7 @@ def main():
                                "synthetic depth+RGB, 300-frame handheld path, integrate + raycast every frame",
                    "volume_voxels": N_VOX ** 3, "image": [W_IMG, H_IMG], "trunc_voxels": 4, "w_max": 128,
                    "ray_step_voxels": 0.5, "global_batch": 1, "parallelism": "none",
-                   "path": "mvf_step (graph)" if head_ph is phases.get("single_step") else "plain calls"},
+                   "path": "mvf_step" if head_ph is phases.get("single_step") else "plain calls"},
         "raycast_mpix_s": head_ph["raycast_mpix_s"],
         "integrate_kernel_voxel_updates_per_s": main_ph.get("integrate_kernel_voxel_updates_per_s"),
         "raycast_kernel_mpix_s": main_ph.get("raycast_kernel_mpix_s"),

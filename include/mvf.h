@@ -116,7 +116,7 @@ typedef struct {
     uint64_t integrate_launches, raycast_launches, step_launches;
     double integrate_ms;         /* HIP-event time of integrate kernels (MVF_FLAG_TIMING) */
     double raycast_ms;           /* HIP-event time of raycast kernels (MVF_FLAG_TIMING) */
-    double step_ms;              /* HIP-event time of batched step graphs (MVF_FLAG_TIMING) */
+    double step_ms;              /* HIP-event time of batched steps (MVF_FLAG_TIMING) */
     uint64_t resident_bytes;     /* device bytes held by volumes now */
     int32_t resident_volumes;
     int32_t reserved;
@@ -267,11 +267,10 @@ typedef struct {
 /* Integrate frames[i] into the active volumes of frames[i].stream_id, then
  * raycast every stream at its frame's pose into outs[i], for all n streams
  * at once: one persistent integration launch and one persistent raycast
- * launch over a device volume table, captured once into a HIP graph and
- * replayed.  Results equal the plain calls bit for bit.  When the active
+ * launch over a device volume table.  Results equal the plain calls bit for bit.  When the active
  * in-view volumes of the streams do not fit the budget together they are
  * processed in waves that do (swapping volumes in and out, Memory Passing
- * section), one graph replay per wave, the raycast of each wave merged
+ * section), one chain of launches per wave, the raycast of each wave merged
  * with the earlier ones per pixel; MVF_ERR_BUDGET only when one volume
  * alone exceeds the budget.  Steps split into waves are not autotuned. */
 mvf_status mvf_step(mvf_ctx* ctx, int32_t n, const mvf_stream_frame* frames,
@@ -308,7 +307,7 @@ mvf_status mvf_get_schedule(mvf_ctx* ctx, mvf_schedule* out);
  * schedule between each two of the 7 other candidates (timed with HIP events
  * on the call's stream; the step's results are unaffected); each block
  * counts by the mean of its last seven runs without their highest and lowest
- * (the first pays the graph capture), and the shape keeps the candidate
+ * (the first pays the allocations), and the shape keeps the candidate
  * fastest relative to the mean of the default blocks around it.  Tune on
  * representative frames: the fastest schedule depends on how much of the
  * volumes the frames see.  cache_path (may be NULL: memory

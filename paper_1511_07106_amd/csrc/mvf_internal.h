@@ -131,9 +131,7 @@ struct RayParams {
 enum Counter { kCntUpdated = 0, kCntBand = 1, kCntBricks = 2, kCntDeep = 3, kCntNum = 16 };
 constexpr int kCntSlots = 64;
 
-// Launch parameters that live in device memory, so that a captured graph
-// replays with new tables (volume set, frame pointers, poses) without
-// re-capture.
+// Launch parameters that live in device memory with the other tables of a call.
 struct LaunchHeader {
     int32_t nvol;          // entries of the volume table used by integration
     int32_t total_items;   // integration work items
@@ -280,12 +278,9 @@ struct RaycastLaunch {
 // Frame preparation of n frames, their items in pinned host memory (read when
 // the launch runs if there are more than kPrepInline).  With tsrc set the
 // launch also copies tbytes (a multiple of 16, 16-byte aligned) from tsrc,
-// pinned host memory, to tdst; set_frame_prep_node points such a node of an
-// instantiated graph at other items and another host slot.
+// pinned host memory, to tdst.
 int launch_frame_prep(const PrepItem* items, int n, int max_w, int max_h, void* stream, const void* tsrc = nullptr,
                       void* tdst = nullptr, size_t tbytes = 0);
-int set_frame_prep_node(void* exec, void* node, const PrepItem* items, int n, int max_w, int max_h, const void* tsrc,
-                        void* tdst, size_t tbytes);
 int launch_volume_init(DevVolume v, void* stream);
 // The z table of a launch and, when L.visit is set, the visit pass over
 // the launch's `bricks` bricks (total_items * zchunk; one thread per brick,

@@ -183,27 +183,6 @@ int launch_frame_prep(const PrepItem* items, int n, int max_w, int max_h, void* 
     return (int)hipGetLastError();
 }
 
-int set_frame_prep_node(void* exec, void* node, const PrepItem* items, int n, int max_w, int max_h, const void* tsrc,
-                        void* tdst, size_t tbytes)
-{
-    if (n <= 0 || !tsrc || (tbytes & 15) || ((uintptr_t)tsrc & 15) || ((uintptr_t)tdst & 15))
-        return (int)hipErrorInvalidValue;
-    PrepArgs a0 = prep_args(items, n);
-    const PrepItem* a1 = n <= kPrepInline ? nullptr : items;
-    const uint4* a2 = (const uint4*)tsrc;
-    uint4* a3 = (uint4*)tdst;
-    uint32_t a4 = (uint32_t)(tbytes / 16);
-    void* args[] = {(void*)&a0, (void*)&a1, (void*)&a2, (void*)&a3, (void*)&a4};
-    hipKernelNodeParams p{};
-    p.func = reinterpret_cast<void*>(mvf_frame_prep_kernel);
-    p.gridDim = prep_grid(n, max_w, max_h);
-    p.blockDim = dim3(256);
-    p.sharedMemBytes = 0;
-    p.kernelParams = args;
-    p.extra = nullptr;
-    return (int)hipGraphExecKernelNodeSetParams((hipGraphExec_t)exec, (hipGraphNode_t)node, &p);
-}
-
 // ---------------------------------------------------------------------------
 // Volume initialisation: F = NaN (unobserved), W = 0, C = 0, flags = 0.
 // ---------------------------------------------------------------------------
@@ -534,8 +513,8 @@ static __device__ __forceinline__ void integrate_deep_bricks(const IntegrateLaun
 // eight wavefronts per SIMD: the kernel is latency-bound, and its state fits 64 VGPRs
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void mvf_integrate_kernel(IntegrateLaunch L)
 {
-    // with a tile order to compute (captured step), block 0 sorts the next
-    // raycast's tile groups while the others integrate
+    // with a tile order to compute, block 0 sorts the next
+    // raycast's tiles while the others integrate
     const int b0 = L.order.tiles > 0 ? 1 : 0;
     if ((int)blockIdx.x < b0) {
         __shared__ int hist[kOrderBins];
@@ -1128,10 +1107,10 @@ int launch_integrate(const IntegrateLaunch& L, int blocks, void* stream, void* e
 }
 
 // ---------------------------------------------------------------------------
-// Raycast.  One thread per pixel; a one-wavefront block covers an 8x8 pixel
-// tile of coherent rays (a free wave slot is refilled as soon as any ray
-// tile finishes); tiles are assigned so that neighbouring tiles land on the
-// same XCD (shared L2 for the voxels they gather).  Each ray walks the global sample lattice t_k = k delta through
+// Raycast.  One-wavefront blocks over 8x8-pixel tiles, 1 to 16 lanes per ray
+// and as many blocks per tile (a free wave slot is refilled as soon as a block
+// finishes); a tile's blocks land on one XCD (shared L2 for the voxels they
+// gather).  Each ray walks the global sample lattice t_k = k delta through
 // every volume of its stream (nearest first), skipping runs of samples
 // whose cell lies in bricks flagged "no F <= 0" (exact: such samples can
 // never be the far end of a plus-to-minus crossing), and keeps the nearest
@@ -1238,8 +1217,6 @@ static __host__ __device__ __forceinline__ float trilinear(const float c[8], con
     return lerp32(c0, c1, f[2]);
 }
 
-// Conservative sample range [k0, k1] of the ray inside V's domain box grown
-// by one voxel, plus two samples each side.
 // Raycast range bounds.  Every sample the march must evaluate (a possible
 // far end of a crossing) lies in a cell with a corner that may hold F <= 0:
 // a cell whose base voxel lies in a sub-block set in its brick's cell mask,
@@ -1325,6 +1302,8 @@ static __device__ void collect_footprint(const DevVolume& V, const DevFrame& Fr,
     if (has) rb.entries[brick_base[v] + base + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = e;
 }
 
+// Conservative sample range [k0, k1] of the ray inside V's domain box grown
+// by one voxel, plus two samples each side.
 static __device__ __forceinline__ void ray_k_range(const DevVolume& V, const Ray& r, float delta, int kmax, int& k0,
                                                    int& k1)
 {
@@ -2081,7 +2060,7 @@ int launch_ray_bounds_collect(const LaunchHeader* hdr, const DevVolume* vols, co
 // Block (x, y, s): cells [8x, 8x + 8) x [8y, 8y + 8) of stream s, folded in
 // LDS from every footprint of the stream's volumes.  Block (0, 0, 0) also
 // clears the other half of the counts.  With a tile order to compute, block
-// (0, 0, order_z) sorts the tile groups beside the others (a launch of its own
+// (0, 0, order_z) sorts the tiles beside the others (a launch of its own
 // between the merge and the raycast took 8 us and its gap).
 __global__ __launch_bounds__(1024) void mvf_ray_bounds_merge_kernel(const LaunchHeader* hdr, const DevFrame* frames,
                                                                    const int32_t* lists, const int32_t* list_base,

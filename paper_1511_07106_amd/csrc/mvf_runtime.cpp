@@ -1,7 +1,7 @@
 // Host runtime of libmvf: context, grid/volume registry, residency manager
 // (device budget, slab pool, pinned host mirrors, swaps on a side copy
 // stream ordered by events), launch-table arena, the plain per-volume
-// integrate/raycast, the batched graph-captured step, placement, the
+// integrate/raycast, the batched step, placement, the
 // differentiable raycast, read/write and statistics.  Implements include/mvf.h.
 // Paper: Salvato, Finman, Leonard, arXiv 1511.07106.
 #include <hip/hip_runtime.h>
@@ -134,8 +134,8 @@ struct Scratch {
 
 // Ring of pinned host + device slots for per-launch tables.  A slot is
 // reused only after an event recorded behind the launches that read it.
-// Captured steps release their slots in batches of kBatch behind one event
-// (each event record between two graph launches cost the step 3-6 us); the
+// Batched steps release their slots in batches of kBatch behind one event
+// (each event record between two steps cost 3-6 us); the
 // batch's last slot is the latest in ring order, so every slot of a batch is
 // reacquired, and has waited, before that slot's event is recorded again.
 struct Arena {
@@ -183,20 +183,17 @@ struct TimedPair {
     int kind;  // 0 integrate, 1 raycast, 2 batched step
 };
 
-struct StepGraph {
+struct StepBuffers {
     bool valid = false;
     int n = 0;
     std::vector<int> widths, heights, out_w, out_h;
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
-    hipGraphNode_t copy_node = nullptr;  // frame preparation, which also uploads the tables (the root)
-    // persistent device tables read by the captured kernels
+    // persistent device tables read by the step's kernels
     uint8_t* dev = nullptr;
     size_t dev_bytes = 0;
     size_t off_hdr, off_prep, off_frames, off_vols, off_items, off_lists, off_lbase, off_tbase, off_bbase;
     int max_vols = 0, max_w = 0, max_h = 0;
-    int integ_blocks = 0, ray_tiles = 0;
-    float* ztab = nullptr;  // integration z table read by the captured launch
+    int ray_tiles = 0;
+    float* ztab = nullptr;  // integration z table
     int ztab_cap = 0;
     uint8_t* visit = nullptr;  // brick visit mask per integration item
     int visit_cap = 0;
@@ -208,7 +205,7 @@ struct StepGraph {
     uint32_t* rb_counts = nullptr;        // 2 * max_vols
     int rb_parity = 0;
     int max_cells_x = 0, max_cells_y = 0;
-    mvf_schedule sched{4, 0, kRayLanes, 0};  // schedule the graph was captured with
+    mvf_schedule sched{4, 0, kRayLanes, 0};  // schedule of the last step
     uint32_t* tile_cost = nullptr;  // raycast tiles: last duration, then launch order
     int32_t* tile_order = nullptr;
 };
@@ -283,8 +280,7 @@ struct mvf_ctx {
     } track;
     uint8_t* extract_buf = nullptr;   // surface points: scratch (extract_buffer_bytes)
     size_t extract_buf_n = 0;         // nbricks it holds
-    StepGraph step;
-    hipStream_t capture_stream = nullptr;
+    StepBuffers step;
 };
 
 namespace {
@@ -398,7 +394,7 @@ mvf_status arena_release(mvf_ctx* c, int slot, hipStream_t stream)
     return MVF_OK;
 }
 
-// A captured step's slot: released with the next kBatch - 1 step slots of
+// A batched step's slot: released with the next kBatch - 1 step slots of
 // the same stream behind one event (arena_flush); the call's tail is that
 // event once recorded.
 mvf_status arena_release_step(mvf_ctx* c, int slot, hipStream_t stream)
@@ -1253,12 +1249,9 @@ std::vector<int> stream_volumes(mvf_ctx* c, int sid, const float* T, const mvf_i
     return ids;
 }
 
-mvf_status destroy_step_graph(mvf_ctx* c)
+mvf_status destroy_step_buffers(mvf_ctx* c)
 {
-    StepGraph& g = c->step;
-    if (g.exec) { CHECK_HIP(hipGraphExecDestroy(g.exec)); g.exec = nullptr; }
-    if (g.graph) { CHECK_HIP(hipGraphDestroy(g.graph)); g.graph = nullptr; }
-    g.copy_node = nullptr;
+    StepBuffers& g = c->step;
     if (g.dev) { CHECK_HIP(hipFree(g.dev)); g.dev = nullptr; }
     if (g.ztab) { CHECK_HIP(hipFree(g.ztab)); g.ztab = nullptr; }
     if (g.visit) { CHECK_HIP(hipFree(g.visit)); g.visit = nullptr; }
@@ -1278,7 +1271,7 @@ mvf_status destroy_step_graph(mvf_ctx* c)
 
 // ---- step schedules and their autotuner -------------------------------------
 
-// runs per block of one schedule; the first (which pays the graph capture and
+// runs per block of one schedule; the first (which pays the allocations and
 // starts the raycast tile order afresh) is not counted, and a block scores
 // the mean of the others without their highest and lowest.  The blocks alternate
 // between the reference schedule (the first candidate, the default) and the
@@ -1521,7 +1514,6 @@ mvf_status mvf_create(mvf_ctx** out, const mvf_config* cfg)
     if ((e = hipStreamCreateWithFlags(&c->d2h_stream, hipStreamNonBlocking)) != hipSuccess ||
         (e = hipStreamCreateWithFlags(&c->h2d_stream, hipStreamNonBlocking)) != hipSuccess ||
         (e = hipEventCreateWithFlags(&c->h2d_last, hipEventDisableTiming | hipEventDisableSystemFence)) != hipSuccess ||
-        (e = hipStreamCreateWithFlags(&c->capture_stream, hipStreamNonBlocking)) != hipSuccess ||
         (e = hipMalloc((void**)&c->counters, sizeof(unsigned long long) * kCntNum * kCntSlots)) != hipSuccess ||
         (e = hipMemset(c->counters, 0, sizeof(unsigned long long) * kCntNum * kCntSlots)) != hipSuccess ||
         (e = hipHostMalloc((void**)&c->arena.host, Arena::kSlots * Arena::kSlotBytes + sizeof(Mailbox),
@@ -1550,7 +1542,7 @@ mvf_status mvf_destroy(mvf_ctx* c)
     if (!c) return MVF_OK;
     (void)hipSetDevice(c->device);
     (void)hipDeviceSynchronize();
-    destroy_step_graph(c);
+    destroy_step_buffers(c);
     for (auto& v : c->vols) {
         if (v.dev) (void)hipFree(v.dev);
         if (v.host) (void)hipHostFree(v.host);
@@ -1604,7 +1596,6 @@ mvf_status mvf_destroy(mvf_ctx* c)
     if (c->d2h_stream) (void)hipStreamDestroy(c->d2h_stream);
     if (c->h2d_stream) (void)hipStreamDestroy(c->h2d_stream);
     if (c->h2d_last) (void)hipEventDestroy(c->h2d_last);
-    if (c->capture_stream) (void)hipStreamDestroy(c->capture_stream);
     delete c;
     return MVF_OK;
 }
@@ -2089,7 +2080,7 @@ mvf_status mvf_step(mvf_ctx* c, int32_t n, const mvf_stream_frame* frames, const
     }
     // volumes that do not all fit the budget are processed in waves (the
     // paper's memory passing, down to one volume at a time): each wave is one
-    // replay of the captured step over the wave's volumes, raycasts merged
+    // chain of launches over the wave's volumes, raycasts merged
     // through the per-pixel best (t*, id) of the earlier waves
     std::vector<std::vector<int>> waves = plan_waves(c, all);
     if (waves.empty()) waves.push_back({});
@@ -2104,20 +2095,19 @@ mvf_status mvf_step(mvf_ctx* c, int32_t n, const mvf_stream_frame* frames, const
         sch = c->tune_cache.count(key) ? c->tune_cache[key].first : c->fixed_sched;
         if (c->tune_mode != MVF_AUTOTUNE_OFF && !c->tune_cache.count(key)) sch = mvf_schedule{4, 0, kRayLanes, 0};
     }
-    StepGraph& G = c->step;
+    StepBuffers& G = c->step;
     int max_w = 0, max_h = 0;
     for (int i = 0; i < n; ++i) {
         max_w = std::max(max_w, frames[i].frame.width);
         max_h = std::max(max_h, frames[i].frame.height);
     }
     // capacities from the whole set (every wave is a subset of it)
-    int ztotal = 0, items_total = 0, bricks_total = 0, lines_total = 0;
+    int ztotal = 0, items_total = 0, bricks_total = 0;
     for (int id : all) {
         const Volume& v = c->vols[id];
         ztotal += kBrick * v.bd[2];
         items_total += v.bd[0] * v.bd[1] * ((v.bd[2] + sch.zchunk - 1) / sch.zchunk);
         bricks_total += (int)align_up(v.nbricks, 64);
-        lines_total += dist_lines(v.bd);
     }
     bool same_shape = G.valid && G.n == n && (int)all.size() <= G.max_vols && max_w <= G.max_w && max_h <= G.max_h &&
                       ztotal <= G.ztab_cap && items_total <= G.visit_cap && bricks_total <= G.rb_entries_cap &&
@@ -2127,7 +2117,7 @@ mvf_status mvf_step(mvf_ctx* c, int32_t n, const mvf_stream_frame* frames, const
             if (G.out_w[i] != outs[i].width || G.out_h[i] != outs[i].height) same_shape = false;
     }
     if (!same_shape) {
-        CHECK_ST(destroy_step_graph(c));
+        CHECK_ST(destroy_step_buffers(c));
         G.sched = sch;
         G.n = n;
         G.max_vols = std::max<int>((int)all.size() * 2, 16);
@@ -2168,11 +2158,11 @@ mvf_status mvf_step(mvf_ctx* c, int32_t n, const mvf_stream_frame* frames, const
             G.max_cells_x = std::max(G.max_cells_x, (outs[i].width + kBoundCell - 1) / kBoundCell);
             G.max_cells_y = std::max(G.max_cells_y, (outs[i].height + kBoundCell - 1) / kBoundCell);
         }
-        G.integ_blocks = c->n_cus * 8;
         int tiles = 0;
         for (int i = 0; i < n; ++i) tiles += ray_tiles(outs[i].width, outs[i].height);
         G.ray_tiles = tiles;
         CHECK_ST(alloc_tile_buffers(tiles, &G.tile_cost, &G.tile_order));
+        G.valid = true;
     }
     // scratch per stream (with the running best of a multi-wave raycast)
     std::vector<Scratch*> sc(n);
@@ -2203,7 +2193,7 @@ mvf_status mvf_step(mvf_ctx* c, int32_t n, const mvf_stream_frame* frames, const
         CHECK_ST(ensure_resident(c, wave, s));
         std::vector<char> in_wave(c->vols.size(), 0);
         for (int id : wave) in_wave[id] = 1;
-        // host image of the tables, uploaded to G.dev by the graph's first node
+        // host image of the tables, uploaded to G.dev by the chain's first launch
         int slot;
         Writer w;
         CHECK_ST(arena_acquire(c, &slot, &w));
@@ -2291,69 +2281,50 @@ mvf_status mvf_step(mvf_ctx* c, int32_t n, const mvf_stream_frame* frames, const
         G.rb_parity ^= 1;
         h->list_parity = G.list_parity;
         G.list_parity ^= 1;
-        // The graph's first node (frame preparation) copies this image into the
-        // fixed tables; its source is pointed at this wave's arena slot.
-        if (!G.valid) {
-            hipStream_t cs = c->capture_stream;
-            const LaunchHeader* dh = reinterpret_cast<const LaunchHeader*>(G.dev + G.off_hdr);
-            const DevFrame* dframes = reinterpret_cast<const DevFrame*>(G.dev + G.off_frames);
-            const DevVolume* dvols = reinterpret_cast<const DevVolume*>(G.dev + G.off_vols);
-            const int32_t* ditems = reinterpret_cast<const int32_t*>(G.dev + G.off_items);
-            const int32_t* dlists = reinterpret_cast<const int32_t*>(G.dev + G.off_lists);
-            const int32_t* dlb = reinterpret_cast<const int32_t*>(G.dev + G.off_lbase);
-            const int32_t* dtb = reinterpret_cast<const int32_t*>(G.dev + G.off_tbase);
-            const int32_t* dbb = reinterpret_cast<const int32_t*>(G.dev + G.off_bbase);
-            CHECK_HIP(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
-            // the first node reads this step's prep items from the slot and
-            // copies the slot's tables to G.dev
-            int e1 = launch_frame_prep(reinterpret_cast<const PrepItem*>(w.host + G.off_prep), n, G.max_w, G.max_h, cs,
-                                       w.host, G.dev, G.dev_bytes);
-            // integration's block 0 orders the raycast's tile groups (slowest of
-            // the last step first)
-            IntegrateLaunch IL{dh, dvols, dframes, ditems, c->counters, G.ztab, G.visit,
-                               tile_order(c, G.tile_cost, G.tile_order, G.ray_tiles, sch.ray_lanes), G.list, G.list_count,
-                               G.list + (size_t)G.visit_cap * kVisitPerItem};
-            int e2 = e1 ? e1 : launch_ztable(IL, items_total * zc, cs);
-            // one wavefront per work item of the whole volume set (a larger
-            // set later is walked by the kernel's grid-stride loop)
-            G.integ_blocks = (sch.persistent ? c->n_cus * 8 : std::max(c->n_cus * 8, (items_total + 3) / 4)) + 1;
-            if (!e2) e2 = launch_integrate(IL, G.integ_blocks, cs);
-            // the last distance pass also collects the raycast range-bound
-            // footprints; the merge folds them per cell (the launch is there for
-            // volumes of later steps also when this one has none)
-            const RayBounds RB{G.rb_entries, G.rb_counts, G.max_vols};
-            if (!e2) e2 = launch_brick_distance(dh, dvols, dbb, lines_total, std::max(bricks_total, 64), cs, dframes, RB);
-            if (!e2) e2 = launch_ray_bounds_merge(dh, dframes, dlists, dlb, dbb, RB, n, G.max_cells_x, G.max_cells_y, cs);
-            RaycastLaunch RL{dh, dvols, dframes, dlists, dlb, dtb, G.tile_cost, G.tile_order};
-            int e3 = e2 ? e2 : launch_raycast(RL, IL.order.max_blocks, cs);
-            hipError_t ee = hipStreamEndCapture(cs, &G.graph);
-            if (e3) return set_error(MVF_ERR_HIP, "step capture: %s", hipGetErrorString((hipError_t)e3));
-            if (ee != hipSuccess) return set_error(MVF_ERR_HIP, "step capture: %s", hipGetErrorString(ee));
-            CHECK_HIP(hipGraphInstantiate(&G.exec, G.graph, nullptr, nullptr, 0));
-            // frame preparation (with the table upload) is the graph's only root
-            G.copy_node = nullptr;
-            size_t nr = 1;
-            CHECK_HIP(hipGraphGetRootNodes(G.graph, &G.copy_node, &nr));
-            if (nr != 1 || !G.copy_node) return set_error(MVF_ERR_HIP, "step capture: no frame preparation node");
-            G.valid = true;
-        } else {
-            CHECK_HIP((hipError_t)set_frame_prep_node(G.exec, G.copy_node,
-                                                      reinterpret_cast<const PrepItem*>(w.host + G.off_prep), n,
-                                                      G.max_w, G.max_h, w.host, G.dev, G.dev_bytes));
-        }
+        // The chain's first launch (frame preparation) copies this image from
+        // the slot into the fixed tables that the others read.  Six launches one
+        // by one: replayed as a graph the device idled 8 us between two steps and
+        // the replay took the host longer (128^3 at 320 x 240 65.4 us a step, one
+        // 512^3 volume at 640 x 480 151; 60.7 and 146 now, and 105 -> 90 and 191 ->
+        // 174 with a wait after each step).
+        const LaunchHeader* dh = reinterpret_cast<const LaunchHeader*>(G.dev + G.off_hdr);
+        const DevFrame* dframes = reinterpret_cast<const DevFrame*>(G.dev + G.off_frames);
+        const DevVolume* dvols = reinterpret_cast<const DevVolume*>(G.dev + G.off_vols);
+        const int32_t* ditems = reinterpret_cast<const int32_t*>(G.dev + G.off_items);
+        const int32_t* dlists = reinterpret_cast<const int32_t*>(G.dev + G.off_lists);
+        const int32_t* dlb = reinterpret_cast<const int32_t*>(G.dev + G.off_lbase);
+        const int32_t* dtb = reinterpret_cast<const int32_t*>(G.dev + G.off_tbase);
+        const int32_t* dbb = reinterpret_cast<const int32_t*>(G.dev + G.off_bbase);
+        // integration's block 0 orders the raycast's tiles (slowest of the last
+        // step first)
+        const IntegrateLaunch IL{dh, dvols, dframes, ditems, c->counters, G.ztab, G.visit,
+                                 tile_order(c, G.tile_cost, G.tile_order, G.ray_tiles, sch.ray_lanes), G.list,
+                                 G.list_count, G.list + (size_t)G.visit_cap * kVisitPerItem};
+        const RayBounds RB{G.rb_entries, G.rb_counts, G.max_vols};
+        const RaycastLaunch RL{dh, dvols, dframes, dlists, dlb, dtb, G.tile_cost, G.tile_order};
+        // one wavefront per work item of the wave's volumes
+        const int integ_blocks = (sch.persistent ? c->n_cus * 8 : std::max(c->n_cus * 8, (items + 3) / 4)) + 1;
         hipEvent_t tune_a = nullptr, tune_b = nullptr;
         if (tuning) {
             CHECK_ST(get_event(c, &tune_a));
             CHECK_ST(get_event(c, &tune_b));
             CHECK_HIP(hipEventRecord(tune_a, s));
         }
-        CHECK_HIP(hipGraphLaunch(G.exec, s));
+        CHECK_LAUNCH(launch_frame_prep(reinterpret_cast<const PrepItem*>(w.host + G.off_prep), n, max_w, max_h, s,
+                                       w.host, G.dev, G.dev_bytes));
+        CHECK_LAUNCH(launch_ztable(IL, items * zc, s));
+        CHECK_LAUNCH(launch_integrate(IL, integ_blocks, s));
+        // the distance transform also collects the raycast range-bound
+        // footprints; the merge folds them per cell
+        CHECK_LAUNCH(launch_brick_distance(dh, dvols, dbb, lines, nbr, s, dframes, RB));
+        CHECK_LAUNCH(launch_ray_bounds_merge(dh, dframes, dlists, dlb, dbb, RB, n, G.max_cells_x, G.max_cells_y, s));
+        CHECK_LAUNCH(launch_raycast(RL, IL.order.max_blocks, s));
         if (tuning) {
             CHECK_HIP(hipEventRecord(tune_b, s));
             c->tuning.ev.push_back(std::make_pair(tune_a, tune_b));
             c->tuning.next += 1;
         }
-        CHECK_ST(arena_release_step(c, slot, s));  // reused once the replay that reads it is done
+        CHECK_ST(arena_release_step(c, slot, s));  // reused once the launch that reads it is done
     }
     CHECK_ST(timing_end(c, s, t0, 2));
     c->last_sched = sch;
