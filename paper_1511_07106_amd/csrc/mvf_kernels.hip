@@ -2139,7 +2139,7 @@ int launch_ray_bounds_merge(const LaunchHeader* hdr, const DevFrame* frames, con
 // GB/s each way).  Few blocks: the uploads that run beside it share the link,
 // and the frames' kernels the device.  (The runtime's copy took an engine of its
 // own choice: behind pending work 12 GB/s, and it held the calling thread for up
-// to 9 ms.  A frame over three volumes of 188 MB with room for one, calls in a
+// to 9 ms.  A frame over three volumes of 168 MB with room for one, calls in a
 // row: 15.8 ms with it, 9.4 now; 9.8 and 10.0 with 16 and 64 blocks, and with a
 // wait after each call 8.0 and 8.1 where 4 take 7.6.)
 // ---------------------------------------------------------------------------
