@@ -1747,6 +1747,7 @@ mvf_status mvf_volume_evict(mvf_ctx* c, int32_t id, uint32_t flags)
     if (!v) return set_error(MVF_ERR_NOT_FOUND, "volume %d", id);
     v->active = false;
     if (flags & MVF_EVICT_SWAP_OUT) {
+        CHECK_HIP(hipSetDevice(c->device));
         hipStream_t s = c->tail_valid ? c->tail_stream : nullptr;
         CHECK_ST(swap_out(c, *v, s));
     }

@@ -1,0 +1,103 @@
+"""The library's host side on the CPU: mvf_runtime.cpp against a HIP runtime
+and kernel launchers over host memory (native/host_hip.cpp), which note the
+device that is current at each call and count allocations."""
+import ctypes as C
+import os
+import subprocess
+import tempfile
+
+import numpy as np
+import pytest
+
+from paper_1511_07106_amd import _lib as L
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1511_07106_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def lib():
+    if not os.path.exists("/opt/rocm/include/hip/hip_runtime.h"):
+        pytest.skip("needs the HIP headers")
+    so = os.path.join(tempfile.mkdtemp(prefix="mvf_host_"), "libmvf_host.so")
+    # bound to each other: a HIP runtime in the process (torch's) has the same names
+    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-w", "-Wl,-Bsymbolic", "-D__HIP_PLATFORM_AMD__",
+                    "-I/opt/rocm/include", f"-I{ROOT}/include", f"-I{CSRC}", os.path.join(CSRC, "mvf_runtime.cpp"),
+                    os.path.join(ROOT, "tests", "native", "host_hip.cpp"), "-o", so, "-lpthread"], check=True)
+    lib = C.CDLL(so)
+    for name, args in L.SIGNATURES.items():
+        getattr(lib, name).argtypes = args
+        getattr(lib, name).restype = C.c_int32
+    lib.mvf_last_error.restype = C.c_char_p
+    lib.t_elsewhere.restype = C.c_char_p
+    return lib
+
+
+class Map:
+    """A context on a device, with volumes of 16^3 of one stream in front of the camera and a frame on the host."""
+
+    def __init__(self, lib, device=0, volumes=1, width=32, height=24):
+        self.lib, self.h = lib, C.c_void_p()
+        self.ok("mvf_create", C.byref(self.h), C.byref(L.mvf_config(0, 0.5, 10.0, device, 0)), ctx=False)
+        gid = C.c_int32()
+        self.ok("mvf_grid_create", C.byref(L.mvf_grid_desc((C.c_float * 3)(-0.8, -0.8, 1.0), 0.1, 4.0, 128, 0)), C.byref(gid))
+        self.ids = []
+        for i in range(volumes):
+            vid = C.c_int32()
+            d = L.mvf_volume_desc(gid.value, (C.c_int32 * 3)(0, 0, 16 * i), (C.c_int32 * 3)(16, 16, 16), 0)
+            self.ok("mvf_volume_create", C.byref(d), C.byref(vid))
+            self.ok("mvf_volume_place", vid)
+            self.ids.append(vid.value)
+        self.pose = (C.c_float * 12)(1, 0, 0, 0, 0, 1, 0, 0, 0, 0, 1, 0)
+        self.K = L.mvf_intrinsics(30.0, 30.0, (width - 1) / 2, (height - 1) / 2)
+        self.size(width, height)
+
+    def size(self, width, height, out=None):
+        ow, oh = out or (width, height)
+        self.depth = np.ones((height, width), np.float32)
+        self.maps = [np.zeros((oh, ow), np.float32), np.zeros((oh, ow, 3), np.float32), np.zeros((oh, ow, 3), np.float32),
+                     np.zeros((oh, ow), np.int32)]
+        self.frame = L.mvf_frame(self.depth.ctypes.data, None, width, height, 0, 0)
+        self.out = L.mvf_raycast_out(*[m.ctypes.data for m in self.maps], ow, oh)
+
+    def ok(self, name, *args, ctx=True):
+        st = getattr(self.lib, name)(*([self.h] if ctx else []), *args)
+        assert st == 0, (name, st, self.lib.mvf_last_error())
+
+    def step(self):
+        fr = L.mvf_stream_frame(0, self.frame, self.pose, self.K)
+        self.ok("mvf_step", 1, C.byref(fr), C.byref(self.out), None)
+
+    def close(self):
+        self.ok("mvf_destroy")
+
+
+CALLS = {
+    "integrate": lambda m: m.ok("mvf_integrate", 0, C.byref(m.frame), m.pose, C.byref(m.K), None),
+    "raycast": lambda m: m.ok("mvf_raycast", 0, m.pose, C.byref(m.K), C.byref(m.out), None),
+    "step": lambda m: m.step(),
+    "evict": lambda m: m.ok("mvf_volume_evict", m.ids[0], L.MVF_EVICT_SWAP_OUT),
+    "swap_out": lambda m: m.ok("mvf_volume_swap_out", m.ids[0], None),
+    "swap_in": lambda m: (m.ok("mvf_volume_swap_out", m.ids[0], None), m.lib.t_set_device(0),
+                          m.ok("mvf_volume_swap_in", m.ids[0], None)),
+    "extract": lambda m: m.ok("mvf_volume_extract", m.ids[0], None, None, None, 0, C.byref(C.c_int64()), None),
+    "read": lambda m: m.ok("mvf_volume_read", m.ids[0], m.maps[0].ctypes.data, None, None),
+    "write": lambda m: m.ok("mvf_volume_write", m.ids[0], None, None, None),
+}
+
+
+@pytest.mark.parametrize("call", CALLS)
+def test_calls_select_their_device(lib, call):
+    """A context on the second device, called by a thread whose current device
+    is the first: everything that the call allocates or launches is on the
+    context's device."""
+    m = Map(lib, device=1)
+    m.size(128, 96)   # the read's plane of 16^3 fits a map
+    CALLS["integrate"](m)
+    lib.t_expect(1)
+    lib.t_set_device(0)
+    CALLS[call](m)
+    elsewhere = lib.t_elsewhere().decode()
+    lib.t_expect(-1)
+    m.close()
+    assert elsewhere == "", elsewhere
