@@ -764,13 +764,25 @@ mvf_status get_scratch(mvf_ctx* c, int sid, int w, int h, bool need_best, Scratc
     return MVF_OK;
 }
 
-// Raycast duration per tile (zero: not known) and launch order, for n tiles.
-mvf_status alloc_tile_buffers(int n, uint32_t** cost, int32_t** order)
+// New device memory (64-bit words) is cleared on the stream of the call that uses
+// it: hipMemset runs on the null stream, returns before the clear has run, and a
+// caller's non-blocking stream does not wait for it (a context's first
+// integration, on such a stream, could read its lists' counts, and write
+// behind the lists, before they were zero).  Later calls run after the clear,
+// also if this one fails.
+mvf_status clear_new(mvf_ctx* c, void* p, int words, hipStream_t stream)
 {
-    CHECK_HIP(hipMalloc((void**)cost, (size_t)n * sizeof(uint32_t)));
+    CHECK_LAUNCH(launch_fill_u64(static_cast<unsigned long long*>(p), words, 0ull, stream));
+    return mark_tail(c, stream);
+}
+
+// Raycast duration per tile (zero: not known) and launch order, for n tiles.
+mvf_status alloc_tile_buffers(mvf_ctx* c, int n, uint32_t** cost, int32_t** order, hipStream_t stream)
+{
+    const int words = (n + 1) / 2;
+    CHECK_HIP(hipMalloc((void**)cost, (size_t)words * sizeof(unsigned long long)));
     CHECK_HIP(hipMalloc((void**)order, ((size_t)n + kRayPlanInts) * sizeof(int32_t)));
-    CHECK_HIP(hipMemset(*cost, 0, (size_t)n * sizeof(uint32_t)));
-    return MVF_OK;
+    return clear_new(c, *cost, words, stream);
 }
 
 // 8x8-pixel tiles of a w x h raycast.
@@ -790,13 +802,13 @@ TileOrder tile_order(const mvf_ctx* c, uint32_t* cost, int32_t* order, int tiles
     return o;
 }
 
-mvf_status get_tile_buffers(Scratch* s, int n)
+mvf_status get_tile_buffers(mvf_ctx* c, Scratch* s, int n, hipStream_t stream)
 {
     if (n <= s->tiles_cap) return MVF_OK;
     if (s->tile_cost) { CHECK_HIP(hipFree(s->tile_cost)); s->tile_cost = nullptr; }
     if (s->tile_order) { CHECK_HIP(hipFree(s->tile_order)); s->tile_order = nullptr; }
     s->tiles_cap = 0;
-    CHECK_ST(alloc_tile_buffers(n, &s->tile_cost, &s->tile_order));
+    CHECK_ST(alloc_tile_buffers(c, n, &s->tile_cost, &s->tile_order, stream));
     s->tiles_cap = n;
     return MVF_OK;
 }
@@ -818,8 +830,8 @@ mvf_status get_bound_buffers(Scratch* s, int w, int h)
 
 // Footprint list for `bricks` (64-aligned per volume) and zeroed counts for
 // `vols` volume slots.
-mvf_status get_footprint_buffers(RayBoundEntry** entries, int* entries_cap, uint32_t** counts, int* counts_cap,
-                                 int bricks, int vols)
+mvf_status get_footprint_buffers(mvf_ctx* c, RayBoundEntry** entries, int* entries_cap, uint32_t** counts,
+                                 int* counts_cap, int bricks, int vols, hipStream_t stream)
 {
     if (bricks > *entries_cap) {
         if (*entries) { CHECK_HIP(hipFree(*entries)); *entries = nullptr; }
@@ -831,7 +843,7 @@ mvf_status get_footprint_buffers(RayBoundEntry** entries, int* entries_cap, uint
         if (*counts) { CHECK_HIP(hipFree(*counts)); *counts = nullptr; }
         *counts_cap = 0;
         CHECK_HIP(hipMalloc((void**)counts, (size_t)2 * vols * sizeof(uint32_t)));
-        CHECK_HIP(hipMemset(*counts, 0, (size_t)2 * vols * sizeof(uint32_t)));
+        CHECK_ST(clear_new(c, *counts, vols, stream));
         *counts_cap = vols;
     }
     return MVF_OK;
@@ -1024,7 +1036,7 @@ mvf_status integrate_plain(mvf_ctx* c, int sid, const mvf_frame* f, const float*
     }
     if (!sc->list_count) {
         CHECK_HIP(hipMalloc((void**)&sc->list_count, 2 * sizeof(unsigned long long)));
-        CHECK_HIP(hipMemset(sc->list_count, 0, 2 * sizeof(unsigned long long)));
+        CHECK_ST(clear_new(c, sc->list_count, 2, stream));
     }
     // once per raycast (the ordering uses the durations up)
     bool order_pending = sc->tile_cost && sc->last_tiles > 0 && sc->order_ready_tiles == 0;
@@ -1123,7 +1135,7 @@ mvf_status raycast_plain(mvf_ctx* c, int sid, const float* T, const mvf_intrinsi
     RayParams rp{};
     if (!c->grids.empty()) rp = ray_params(c, c->grids[ids.empty() ? 0 : c->vols[ids[0]].d.grid_id]);
     const int tiles = ray_tiles(out->width, out->height);
-    CHECK_ST(get_tile_buffers(sc, tiles));
+    CHECK_ST(get_tile_buffers(c, sc, tiles, stream));
     CHECK_ST(get_bound_buffers(sc, out->width, out->height));
     // an order the integration computed holds for this many tiles only (else the merge computes one)
     const bool ordered = sc->order_ready_tiles == tiles && sc->last_tiles == tiles;
@@ -1176,8 +1188,8 @@ mvf_status raycast_plain(mvf_ctx* c, int sid, const float* T, const mvf_intrinsi
             nbr += (int)align_up(c->vols[wave[j]].nbricks, 64);
         }
         bb[wave.size()] = nbr;
-        CHECK_ST(get_footprint_buffers(&sc->rb_entries, &sc->rb_entries_cap, &sc->rb_counts, &sc->rb_counts_cap,
-                                       std::max(nbr, 64), std::max<int>((int)wave.size(), 16)));
+        CHECK_ST(get_footprint_buffers(c, &sc->rb_entries, &sc->rb_entries_cap, &sc->rb_counts, &sc->rb_counts_cap,
+                                       std::max(nbr, 64), std::max<int>((int)wave.size(), 16), stream));
         lb[0] = 0;
         lb[1] = (int32_t)wave.size();
         tb[0] = 0;
@@ -1515,7 +1527,8 @@ mvf_status mvf_create(mvf_ctx** out, const mvf_config* cfg)
         (e = hipStreamCreateWithFlags(&c->h2d_stream, hipStreamNonBlocking)) != hipSuccess ||
         (e = hipEventCreateWithFlags(&c->h2d_last, hipEventDisableTiming | hipEventDisableSystemFence)) != hipSuccess ||
         (e = hipMalloc((void**)&c->counters, sizeof(unsigned long long) * kCntNum * kCntSlots)) != hipSuccess ||
-        (e = hipMemset(c->counters, 0, sizeof(unsigned long long) * kCntNum * kCntSlots)) != hipSuccess ||
+        (e = (hipError_t)launch_fill_u64(c->counters, kCntNum * kCntSlots, 0ull, c->d2h_stream)) != hipSuccess ||
+        (e = hipStreamSynchronize(c->d2h_stream)) != hipSuccess ||   // any stream may count next
         (e = hipHostMalloc((void**)&c->arena.host, Arena::kSlots * Arena::kSlotBytes + sizeof(Mailbox),
                             hipHostMallocDefault)) != hipSuccess ||
         (e = hipMalloc((void**)&c->arena.dev, Arena::kSlots * Arena::kSlotBytes)) != hipSuccess ||
@@ -2150,10 +2163,10 @@ mvf_status mvf_step(mvf_ctx* c, int32_t n, const mvf_stream_frame* frames, const
         CHECK_HIP(hipMalloc((void**)&G.visit, (size_t)G.visit_cap * kVisitPerItem));
         CHECK_HIP(hipMalloc((void**)&G.list, (size_t)G.visit_cap * (2 * kVisitPerItem) * sizeof(int32_t)));
         CHECK_HIP(hipMalloc((void**)&G.list_count, 2 * sizeof(unsigned long long)));
-        CHECK_HIP(hipMemset(G.list_count, 0, 2 * sizeof(unsigned long long)));
+        CHECK_ST(clear_new(c, G.list_count, 2, s));
         int counts_cap = 0;
-        CHECK_ST(get_footprint_buffers(&G.rb_entries, &G.rb_entries_cap, &G.rb_counts, &counts_cap,
-                                       std::max(bricks_total * 2, 1024), G.max_vols));
+        CHECK_ST(get_footprint_buffers(c, &G.rb_entries, &G.rb_entries_cap, &G.rb_counts, &counts_cap,
+                                       std::max(bricks_total * 2, 1024), G.max_vols, s));
         G.max_cells_x = G.max_cells_y = 0;
         for (int i = 0; i < n; ++i) {
             G.max_cells_x = std::max(G.max_cells_x, (outs[i].width + kBoundCell - 1) / kBoundCell);
@@ -2162,7 +2175,7 @@ mvf_status mvf_step(mvf_ctx* c, int32_t n, const mvf_stream_frame* frames, const
         int tiles = 0;
         for (int i = 0; i < n; ++i) tiles += ray_tiles(outs[i].width, outs[i].height);
         G.ray_tiles = tiles;
-        CHECK_ST(alloc_tile_buffers(tiles, &G.tile_cost, &G.tile_order));
+        CHECK_ST(alloc_tile_buffers(c, tiles, &G.tile_cost, &G.tile_order, s));
         G.valid = true;
     }
     // scratch per stream (with the running best of a multi-wave raycast)

@@ -1,11 +1,17 @@
 // The HIP runtime and the kernel launchers over host memory, so that the host
 // side of libmvf runs in a process without a GPU: kernels do nothing, copies
 // are made at once, and every call that allocates, records or launches is
-// noted with the device that was current in the calling thread.
+// noted with the device that was current in the calling thread.  Work on a
+// stream that nothing orders after all the earlier work on the others is noted
+// too: streams, events and the host carry vector clocks; no stream waits for the
+// null stream (a caller's are non-blocking), and hipMemset does not wait for
+// its clear.
 #include <hip/hip_runtime.h>
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
+#include <map>
 #include <string>
 
 #include "mvf.h"
@@ -17,10 +23,30 @@ int g_expect = -1;          // device that all device work belongs on (-1: not c
 std::string g_elsewhere;    // names of calls made while another device was current
 int g_allocs = 0;           // device allocations and frees
 
+typedef std::map<void*, long> Clock;   // stream -> work on it that is known to be done
+void join(Clock& a, const Clock& b)
+{
+    for (auto& kv : b) a[kv.first] = std::max(a[kv.first], kv.second);
+}
+Clock g_host, g_issued;
+std::map<void*, Clock> g_stream, g_event;
+std::string g_unordered;
+
 int work(const char* name)
 {
     if (g_expect >= 0 && g_device != g_expect) g_elsewhere += std::string(name) + " ";
     return 0;
+}
+
+int work(const char* name, void* stream)
+{
+    Clock& seen = g_stream[stream];
+    join(seen, g_host);
+    bool after_all = true;
+    for (auto& kv : g_issued) after_all = after_all && (kv.first == stream || seen[kv.first] >= kv.second);
+    if (!after_all) g_unordered += std::string(name) + " ";
+    seen[stream] = ++g_issued[stream];
+    return work(name);
 }
 }  // namespace
 
@@ -29,6 +55,14 @@ void t_expect(int device) { g_expect = device; g_elsewhere.clear(); }
 const char* t_elsewhere() { return g_elsewhere.c_str(); }
 int t_allocs() { return g_allocs; }
 void t_set_device(int device) { g_device = device; }
+void* t_stream()
+{
+    hipStream_t s;
+    hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
+    return s;
+}
+void t_watch() { g_unordered.clear(); }
+const char* t_unordered() { return g_unordered.c_str(); }
 
 hipError_t hipGetDeviceCount(int* n) { *n = 2; return hipSuccess; }
 hipError_t hipSetDevice(int d) { g_device = d; return hipSuccess; }
@@ -38,56 +72,71 @@ hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600* p, int)
     p->multiProcessorCount = 256;
     return hipSuccess;
 }
-hipError_t hipDeviceSynchronize() { return hipSuccess; }
+hipError_t hipDeviceSynchronize() { join(g_host, g_issued); return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
 const char* hipGetErrorString(hipError_t) { return "error"; }
 hipError_t hipMalloc(void** p, size_t n) { ++g_allocs; *p = calloc(1, n ? n : 1); return (hipError_t)work("hipMalloc"); }
 hipError_t hipFree(void* p) { ++g_allocs; free(p); return hipSuccess; }
 hipError_t hipHostMalloc(void** p, size_t n, unsigned) { *p = calloc(1, n ? n : 1); return hipSuccess; }
 hipError_t hipHostFree(void* p) { free(p); return hipSuccess; }
-hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { memcpy(d, s, n); return hipSuccess; }
-hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t)
+hipError_t hipStreamSynchronize(hipStream_t s) { join(g_host, g_stream[s]); return hipSuccess; }
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t stream)
 {
     memcpy(d, s, n);
-    return (hipError_t)work("hipMemcpyAsync");
+    return (hipError_t)work("hipMemcpyAsync", stream);
 }
-hipError_t hipMemset(void* d, int v, size_t n) { memset(d, v, n); return (hipError_t)work("hipMemset"); }
+hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind k)
+{
+    hipMemcpyAsync(d, s, n, k, nullptr);
+    return hipStreamSynchronize(nullptr);
+}
+hipError_t hipMemset(void* d, int v, size_t n) { memset(d, v, n); return (hipError_t)work("hipMemset", nullptr); }
 hipError_t hipEventCreate(hipEvent_t* e) { *e = (hipEvent_t)malloc(1); return (hipError_t)work("hipEventCreate"); }
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return hipEventCreate(e); }
-hipError_t hipEventDestroy(hipEvent_t e) { free((void*)e); return hipSuccess; }
-hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
-hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t e) { g_event.erase(e); free((void*)e); return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t s)
+{
+    g_event[e] = g_host;
+    join(g_event[e], g_stream[s]);
+    return hipSuccess;
+}
+hipError_t hipEventSynchronize(hipEvent_t e) { join(g_host, g_event[e]); return hipSuccess; }
 hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 1.0f; return hipSuccess; }
 hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { *s = (hipStream_t)malloc(1); return (hipError_t)work("hipStreamCreate"); }
-hipError_t hipStreamDestroy(hipStream_t s) { free((void*)s); return hipSuccess; }
-hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
-hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+hipError_t hipStreamDestroy(hipStream_t s)
+{
+    g_stream.erase(s);
+    g_issued.erase(s);
+    free((void*)s);
+    return hipSuccess;
+}
+hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) { join(g_stream[s], g_event[e]); return hipSuccess; }
 }
 
 namespace mvf {
-int launch_frame_prep(const PrepItem*, int, int, int, void*, const void*, void*, size_t) { return work("frame_prep"); }
-int launch_volume_init(DevVolume, void*) { return work("volume_init"); }
-int launch_ztable(const IntegrateLaunch&, int, void*) { return work("ztable"); }
-int launch_integrate(const IntegrateLaunch&, int, void*, void*, void*) { return work("integrate"); }
-int launch_raycast(const RaycastLaunch&, int, void*, void*, void*) { return work("raycast"); }
-int launch_column_flags(DevVolume, void*) { return work("column_flags"); }
-int launch_brick_distance(const LaunchHeader*, const DevVolume*, const int32_t*, int, int, void*, const DevFrame*,
-                          RayBounds) { return work("brick_distance"); }
+int launch_frame_prep(const PrepItem*, int, int, int, void* s, const void*, void*, size_t) { return work("frame_prep", s); }
+int launch_volume_init(DevVolume, void* s) { return work("volume_init", s); }
+int launch_ztable(const IntegrateLaunch&, int, void* s) { return work("ztable", s); }
+int launch_integrate(const IntegrateLaunch&, int, void* s, void*, void*) { return work("integrate", s); }
+int launch_raycast(const RaycastLaunch&, int, void* s, void*, void*) { return work("raycast", s); }
+int launch_column_flags(DevVolume, void* s) { return work("column_flags", s); }
+int launch_brick_distance(const LaunchHeader*, const DevVolume*, const int32_t*, int, int, void* s, const DevFrame*,
+                          RayBounds) { return work("brick_distance", s); }
 int launch_ray_bounds_collect(const LaunchHeader*, const DevVolume*, const int32_t*, const DevFrame*, RayBounds, int,
-                              void*) { return work("ray_bounds_collect"); }
+                              void* s) { return work("ray_bounds_collect", s); }
 int launch_ray_bounds_merge(const LaunchHeader*, const DevFrame*, const int32_t*, const int32_t*, const int32_t*,
-                            RayBounds, int, int, int, void*, TileOrder) { return work("ray_bounds_merge"); }
-int launch_swap_copy(const void* src, void* dst, size_t bytes, void*)
+                            RayBounds, int, int, int, void* s, TileOrder) { return work("ray_bounds_merge", s); }
+int launch_swap_copy(const void* src, void* dst, size_t bytes, void* s)
 {
     memcpy(dst, src, bytes);
-    return work("swap_copy");
+    return work("swap_copy", s);
 }
-int launch_read_plane(DevVolume, int plane, uint32_t, uint32_t n, void* out, void*)
+int launch_read_plane(DevVolume, int plane, uint32_t, uint32_t n, void* out, void* s)
 {
     memset(out, 0, (size_t)n * (plane == 1 ? 2 : 4));
-    return work("read_plane");
+    return work("read_plane", s);
 }
-int launch_import(DevVolume, const float*, const uint16_t*, const uint32_t*, bool, void*) { return work("import"); }
+int launch_import(DevVolume, const float*, const uint16_t*, const uint32_t*, bool, void* s) { return work("import", s); }
 size_t extract_buffer_bytes(size_t nbricks) { return 64 * nbricks; }
 ExtractBuffers extract_buffers(void*, size_t, long long* total)
 {
@@ -95,21 +144,26 @@ ExtractBuffers extract_buffers(void*, size_t, long long* total)
     B.total = total;
     return B;
 }
-int launch_extract(DevVolume, const ExtractBuffers&, float*, float*, int32_t*, long long, void*) { return work("extract"); }
-int launch_placement_clear(unsigned long long*, int, int*, void*) { return work("placement_clear"); }
-int launch_placement_count(const PlacementCount&, PlacementCells* out, void*)
+int launch_extract(DevVolume, const ExtractBuffers&, float*, float*, int32_t*, long long, void* s) { return work("extract", s); }
+int launch_fill_u64(unsigned long long* p, int n, unsigned long long value, void* s)
+{
+    std::fill(p, p + n, value);
+    return work("fill", s);
+}
+int launch_placement_clear(unsigned long long*, int, int*, void* s) { return work("placement_clear", s); }
+int launch_placement_count(const PlacementCount&, PlacementCells* out, void* s)
 {
     out->n = out->overflow = 0;
-    return work("placement_count");
+    return work("placement_count", s);
 }
-int launch_track_smooth(const float*, int, int, int, float, float*, void*) { return work("track_smooth"); }
-int launch_track_down(const float*, int, int, int, float, float*, void*) { return work("track_down"); }
-int launch_track_maps(TrackMaps, void*) { return work("track_maps"); }
+int launch_track_smooth(const float*, int, int, int, float, float*, void* s) { return work("track_smooth", s); }
+int launch_track_down(const float*, int, int, int, float, float*, void* s) { return work("track_down", s); }
+int launch_track_maps(TrackMaps, void* s) { return work("track_maps", s); }
 int track_blocks(int, int) { return 1; }
-int launch_icp_step(const TrackLaunch&, int, TrackState*, void*) { return work("icp_step"); }
+int launch_icp_step(const TrackLaunch&, int, TrackState*, void* s) { return work("icp_step", s); }
 int diffray_scratch_init(int) { return 0; }
 double* diffray_scratch(int) { return nullptr; }
 int diffray_partials_needed(int, int) { return 1; }
 int launch_diffray_backward(DiffVolume, const float*, float, float, float, float, int, int, RayParams, const float*,
-                            const int32_t*, float*, double*, int, double*, void*) { return work("diffray_backward"); }
+                            const int32_t*, float*, double*, int, double*, void* s) { return work("diffray_backward", s); }
 }  // namespace mvf

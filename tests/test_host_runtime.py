@@ -1,6 +1,7 @@
 """The library's host side on the CPU: mvf_runtime.cpp against a HIP runtime
 and kernel launchers over host memory (native/host_hip.cpp), which note the
-device that is current at each call and count allocations."""
+device that is current at each call, work that nothing orders after the
+earlier work on other streams, and allocations."""
 import ctypes as C
 import os
 import subprocess
@@ -29,7 +30,8 @@ def lib():
         getattr(lib, name).argtypes = args
         getattr(lib, name).restype = C.c_int32
     lib.mvf_last_error.restype = C.c_char_p
-    lib.t_elsewhere.restype = C.c_char_p
+    lib.t_elsewhere.restype = lib.t_unordered.restype = C.c_char_p
+    lib.t_stream.restype = C.c_void_p
     return lib
 
 
@@ -41,7 +43,7 @@ class Map:
         self.ok("mvf_create", C.byref(self.h), C.byref(L.mvf_config(0, 0.5, 10.0, device, 0)), ctx=False)
         gid = C.c_int32()
         self.ok("mvf_grid_create", C.byref(L.mvf_grid_desc((C.c_float * 3)(-0.8, -0.8, 1.0), 0.1, 4.0, 128, 0)), C.byref(gid))
-        self.ids = []
+        self.stream, self.ids = None, []
         for i in range(volumes):
             vid = C.c_int32()
             d = L.mvf_volume_desc(gid.value, (C.c_int32 * 3)(0, 0, 16 * i), (C.c_int32 * 3)(16, 16, 16), 0)
@@ -66,21 +68,21 @@ class Map:
 
     def step(self):
         fr = L.mvf_stream_frame(0, self.frame, self.pose, self.K)
-        self.ok("mvf_step", 1, C.byref(fr), C.byref(self.out), None)
+        self.ok("mvf_step", 1, C.byref(fr), C.byref(self.out), self.stream)
 
     def close(self):
         self.ok("mvf_destroy")
 
 
 CALLS = {
-    "integrate": lambda m: m.ok("mvf_integrate", 0, C.byref(m.frame), m.pose, C.byref(m.K), None),
-    "raycast": lambda m: m.ok("mvf_raycast", 0, m.pose, C.byref(m.K), C.byref(m.out), None),
+    "integrate": lambda m: m.ok("mvf_integrate", 0, C.byref(m.frame), m.pose, C.byref(m.K), m.stream),
+    "raycast": lambda m: m.ok("mvf_raycast", 0, m.pose, C.byref(m.K), C.byref(m.out), m.stream),
     "step": lambda m: m.step(),
     "evict": lambda m: m.ok("mvf_volume_evict", m.ids[0], L.MVF_EVICT_SWAP_OUT),
-    "swap_out": lambda m: m.ok("mvf_volume_swap_out", m.ids[0], None),
-    "swap_in": lambda m: (m.ok("mvf_volume_swap_out", m.ids[0], None), m.lib.t_set_device(0),
-                          m.ok("mvf_volume_swap_in", m.ids[0], None)),
-    "extract": lambda m: m.ok("mvf_volume_extract", m.ids[0], None, None, None, 0, C.byref(C.c_int64()), None),
+    "swap_out": lambda m: m.ok("mvf_volume_swap_out", m.ids[0], m.stream),
+    "swap_in": lambda m: (m.ok("mvf_volume_swap_out", m.ids[0], m.stream), m.lib.t_set_device(0),
+                          m.ok("mvf_volume_swap_in", m.ids[0], m.stream)),
+    "extract": lambda m: m.ok("mvf_volume_extract", m.ids[0], None, None, None, 0, C.byref(C.c_int64()), m.stream),
     "read": lambda m: m.ok("mvf_volume_read", m.ids[0], m.maps[0].ctypes.data, None, None),
     "write": lambda m: m.ok("mvf_volume_write", m.ids[0], None, None, None),
 }
@@ -101,3 +103,36 @@ def test_calls_select_their_device(lib, call):
     lib.t_expect(-1)
     m.close()
     assert elsewhere == "", elsewhere
+
+
+@pytest.mark.parametrize("call", ["integrate", "raycast", "step", "extract"])
+def test_first_call_on_a_stream(lib, call):
+    """A new context's first call of each kind on a non-blocking stream: nothing
+    that it launches is left unordered with the clearing of new memory, in
+    the call or in a next one on another stream."""
+    m = Map(lib, volumes=3)
+    streams = [lib.t_stream() for _ in range(2)]
+    lib.t_watch()
+    for m.stream in streams:
+        CALLS[call](m)
+    unordered = lib.t_unordered().decode()
+    m.close()
+    assert unordered == "", unordered
+
+
+def test_clears_of_a_call_that_fails(lib):
+    """A call that clears new memory and then fails (a budget below its volume):
+    the next call, on another stream, runs after the clear."""
+    m = Map(lib)
+    a, b = lib.t_stream(), lib.t_stream()
+    for call in ("integrate", "step"):
+        m.ok("mvf_set_budget", 1000)
+        lib.t_watch()
+        m.stream = a
+        with pytest.raises(AssertionError):
+            CALLS[call](m)
+        m.ok("mvf_set_budget", 0)
+        m.stream = b
+        CALLS[call](m)
+        assert lib.t_unordered().decode() == ""
+    m.close()
