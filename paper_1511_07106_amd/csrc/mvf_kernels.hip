@@ -2136,12 +2136,19 @@ int launch_ray_bounds_merge(const LaunchHeader* hdr, const DevFrame* frames, con
 
 // ---------------------------------------------------------------------------
 // Copy of a volume's slab to its pinned mirror.  Bound by the host link (57
-// GB/s each way).  Few blocks: the uploads that run beside it share the link,
-// and the frames' kernels the device.  (The runtime's copy took an engine of its
-// own choice: behind pending work 12 GB/s, and it held the calling thread for up
-// to 9 ms.  A frame over three volumes of 168 MB with room for one, calls in a
-// row: 15.8 ms with it, 9.4 now; 9.8 and 10.0 with 16 and 64 blocks, and with a
-// wait after each call 8.0 and 8.1 where 4 take 7.6.)
+// GB/s one way, about 90 both ways together).  Few blocks: the uploads that run
+// beside it share the link, and the frames' kernels the device.  All of them on
+// one XCD (blocks are dealt to the XCDs in turn): four blocks on four XCDs write
+// 52 GB/s and share the link worse, one block or two to eight no better.
+// The runtime's copy writes 57 GB/s, but where frames are queued ahead it takes
+// an engine of its own choice, and the link mostly stands still.  In ms, in
+// chunks of 64 MB:                              runtime's  on four XCDs  on one
+//   swap-out of a 512^3 volume (1.35 GB) alone       23.9      25.9       24.5
+//   frame over three 256^3 volumes, room for one      9.1       9.8        9.3
+//   over four 512^3 volumes                          88.0      92.4       86.9
+//   the same, frames queued                          95       104         92.7
+//   over eight 256^3 volumes, frames queued          57        35.1       33.5
+//   three contexts of three 256^3 volumes, queued    23.9      11.0       10.5
 // ---------------------------------------------------------------------------
 constexpr int kSwapBlocks = 4;
 
@@ -2152,8 +2159,9 @@ __global__ __launch_bounds__(256) void mvf_swap_copy_kernel(const uint4* __restr
     constexpr int N = 8;   // loads in flight per lane
     const u4* const s = reinterpret_cast<const u4*>(src);
     u4* const d = reinterpret_cast<u4*>(dst);
-    const size_t stride = (size_t)gridDim.x * 256u;
-    size_t i = (size_t)blockIdx.x * 256u + threadIdx.x;
+    if (blockIdx.x % kXcds) return;
+    const size_t stride = (size_t)kSwapBlocks * 256u;
+    size_t i = (size_t)(blockIdx.x / kXcds) * 256u + threadIdx.x;
     for (; i + (N - 1) * stride < n; i += N * stride) {
         u4 x[N];
 #pragma unroll
@@ -2169,8 +2177,8 @@ int launch_swap_copy(const void* src, void* dst, size_t bytes, void* stream)
 {
     if (((uintptr_t)src | (uintptr_t)dst | bytes) & 15) return (int)hipErrorInvalidValue;
     if (!bytes) return 0;
-    hipLaunchKernelGGL(mvf_swap_copy_kernel, dim3(kSwapBlocks), dim3(256), 0, (hipStream_t)stream, (const uint4*)src,
-                       (uint4*)dst, bytes / 16);
+    hipLaunchKernelGGL(mvf_swap_copy_kernel, dim3(kXcds * kSwapBlocks), dim3(256), 0, (hipStream_t)stream,
+                       (const uint4*)src, (uint4*)dst, bytes / 16);
     return (int)hipGetLastError();
 }
 

@@ -87,11 +87,21 @@ struct Volume {
     bool internal = false;  // the library's own (the differentiable raycast's mirror): no public id
 };
 
-// Swaps move a slab in chunks of kSwapChunk bytes, each with its own event,
-// so that a swap-in into a slab still being swapped out copies chunk k as
-// soon as the download of chunk k is done: the two directions of the host
-// link then run at once.
-constexpr size_t kSwapChunk = (size_t)64 << 20;
+// Swaps move a slab in chunks, each with its own event, so that a swap-in into
+// a slab still being swapped out copies chunk k as soon as the download of
+// chunk k is done: the two directions of the host link then run at once, but
+// for the first and the last chunk.  A sixth of the slab, since those cost
+// small slabs most: a frame over three volumes with room for one, waited for,
+// in 64 MB and in such chunks, 128^3 1.80 and 1.48 ms, 192^3 5.31 and 3.75,
+// 256^3 9.33 and 8.19.  At least 8 MB (a launch and an event each: in 4 MB
+// chunks the swap-out of a 128^3 volume alone takes 0.51 ms, in these 0.46),
+// and at most 64 MB: more chunks queued ahead slow the host link down (four
+// volumes of 512^3 in 32 MB chunks 107 ms a frame, in these 93).
+size_t swap_chunk(size_t bytes)
+{
+    constexpr size_t kMb = (size_t)1 << 20;
+    return std::min(std::max((bytes / 6 + kMb - 1) / kMb * kMb, 8 * kMb), 64 * kMb);
+}
 
 struct Slab {
     uint8_t* ptr;
@@ -483,8 +493,9 @@ mvf_status swap_out(mvf_ctx* c, Volume& v, hipStream_t stream, bool keep_slab_po
     // the mirror may still be the source of a swap-in copy
     CHECK_HIP(hipStreamWaitEvent(c->d2h_stream, c->h2d_last, 0));
     std::vector<hipEvent_t> chunks;
-    for (size_t off = 0; off < v.bytes; off += kSwapChunk) {
-        const size_t n = std::min(kSwapChunk, v.bytes - off);
+    const size_t chunk = swap_chunk(v.bytes);
+    for (size_t off = 0; off < v.bytes; off += chunk) {
+        const size_t n = std::min(chunk, v.bytes - off);
         CHECK_LAUNCH(launch_swap_copy(v.dev + off, v.host + off, n, c->d2h_stream));
         hipEvent_t e;
         CHECK_ST(get_event(c, &e));
@@ -608,9 +619,10 @@ mvf_status ensure_resident(mvf_ctx* c, const std::vector<int>& need, hipStream_t
             // chunk k after the slab's previous download of chunk k (same
             // slab size, same chunks)
             size_t k = 0;
-            for (size_t off = 0; off < v.bytes; off += kSwapChunk, ++k) {
+            const size_t chunk = swap_chunk(v.bytes);
+            for (size_t off = 0; off < v.bytes; off += chunk, ++k) {
                 if (k < pending.size()) CHECK_HIP(hipStreamWaitEvent(c->h2d_stream, pending[k], 0));
-                CHECK_HIP(hipMemcpyAsync(v.dev + off, v.host + off, std::min(kSwapChunk, v.bytes - off),
+                CHECK_HIP(hipMemcpyAsync(v.dev + off, v.host + off, std::min(chunk, v.bytes - off),
                                          hipMemcpyHostToDevice, c->h2d_stream));
             }
             for (hipEvent_t e : pending) c->event_pool.push_back(e);

@@ -443,6 +443,46 @@ def test_swap_out_sizes(mvf, dims):
         assert ctx.stats()["swaps_out"] == 2 and ctx.stats()["swaps_in"] == 2
 
 
+@pytest.mark.parametrize("dims", [(104, 80, 96), (112, 80, 96), (128, 128, 128), (192, 168, 160)])
+def test_passing_chunks(mvf, dims):
+    """Slabs of one chunk of a swap, of two, of the smallest chunks and of
+    larger ones: two volumes with room for one, each swapped into the slab that
+    the other is leaving, are the same bit for bit as with room for both."""
+    log(f"passing chunks {dims}")
+    rng = np.random.default_rng(dims[0])
+    w, h = 64, 48
+    K = np.array([60.0, 61.0, w / 2 - 0.3, h / 2 + 0.2], np.float32)
+    T = np.array([[1.0, 0.0, 0.0, 0.005 * dims[0]], [0.0, 1.0, 0.0, 0.005 * dims[1]], [0.0, 0.0, 1.0, -0.2]])
+    frames = [t(_random_depth(rng, w, h, 0.3, 0.2 + 0.018 * dims[2])) for _ in range(4)]
+
+    def run(room):
+        with mvf.Context() as ctx:
+            gid = ctx.grid((0.0, 0.0, 0.0), 0.01, 4.0, 128)
+            ids = [ctx.volume(gid, (0, 0, z), dims) for z in (0, dims[2] - 2)]
+            ctx.set_budget(room * ctx.query(ids[0])[1])
+            maps = []
+            for i, d in enumerate(frames):
+                out = ctx.raycast(T, K, w, h)
+                if i % 2:
+                    ctx.integrate(d, None, T, K)
+                    ctx.raycast(T, K, w, h, out=out)
+                else:
+                    ctx.step([(0, d, None, T, K)], [out])
+                maps.append(out)
+            vols = [ctx.read_volume(i) + ctx.brick_summary(i) for i in ids]
+            return vols, [{k: v.cpu().numpy() for k, v in m.items()} for m in maps], ctx.stats()
+
+    (va, ma, sa), (vb, mb, sb) = run(1), run(2)
+    assert sa["swaps_in"] > 4 and sb["swaps_in"] == 0
+    assert all((v[1] > 0).any() for v in va) and (ma[-1]["hit"] >= 0).any()
+    for a, b in zip(va, vb):
+        for x, y in zip(a, b):
+            np.testing.assert_array_equal(x, y)
+    for a, b in zip(ma, mb):
+        for k in b:
+            np.testing.assert_array_equal(a[k], b[k])
+
+
 def test_calls_on_alternating_streams(mvf):
     """Each call runs after the one before it also on another stream: plain
     integrations and raycasts dealt over three streams give the single
