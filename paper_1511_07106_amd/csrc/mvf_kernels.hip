@@ -2554,9 +2554,9 @@ int launch_placement_count(const PlacementCount& P, PlacementCells* out, void* s
 //
 // Launches: the bricks with a set cell mask are counted per chunk of 1024 and
 // listed in brick order; the listed bricks' points are counted, 16 bricks a
-// block, into sums per block group and per 64 groups; the emission adds up
-// the sums before its group and writes brick by brick (inside a brick z-slice
-// by z-slice, x fastest), so the order is fixed.
+// block (4 in small volumes), into sums per block group and per 64 groups; the
+// emission adds up the sums before its group and writes brick by brick (inside
+// a brick z-slice by z-slice, x fastest), so the order is fixed.
 //
 // Bound: launch and load latency (the surface's bricks of a 512^3 room are 7 %
 // of 262k): 2.8 + 4.5 + 15 + 4 us to count and 26 us to emit.  A wavefront for
@@ -2570,15 +2570,23 @@ struct SurfVoxel {
     float c[8];   // corner (x + (k & 1), y + (k >> 1 & 1), z + (k >> 2))
 };
 
-constexpr int kExtractGroup = 16;              // bricks per group: four wavefronts of four
+constexpr int kExtractGroup = 16;              // bricks per group of a larger volume: four wavefronts of four
 constexpr int kExtractSuper = 64;              // groups per super sum
 constexpr int kExtractChunk = 1024;            // bricks per listing block
 constexpr int kExtractBlocks = 2048;           // most blocks of the counting and the emission
 // Volumes of at most this many bricks take every brick as listed: the two
 // listing launches cost more than the skipped bricks' masks.  Count and
-// emission with / without the listing, cubes of 343, 3375, 15625, 21952, 32768
+// emission with / without the listing, in groups of 16, cubes of 343, 3375, 15625, 21952, 32768
 // and 64000 bricks: 119/88, 122/101, 126/114, 125/121, 128/127, 129/151 us.
 constexpr uint32_t kExtractDirect = 24576;
+// Up to this many, a group is a brick per wavefront: in groups of 16 the four
+// bricks that a wavefront takes one after the other would be all that the device
+// does.  Count and emission in groups of 16 / of 4, every voxel in the band and a
+// sphere: 8 bricks 84/55 and 81/55 us, 512 bricks 94/60 and 79/59, 8000 bricks
+// 120/116 and 97/81, 13824 bricks 165/160 and 107/102, 21952 bricks 228/245 and
+// 117/134 (there the sum over the groups before a block's costs more).
+constexpr int kExtractSmallGroup = 4;
+constexpr uint32_t kExtractSmall = 16384;
 
 // The values a brick's cells read: lane (lx, ly) holds, for each of the
 // planes z = 0 .. 8, the voxels (x, y), (x + 1, y), (x, y + 1), (x + 1, y + 1).
@@ -2702,16 +2710,16 @@ static __device__ __forceinline__ void brick_coords(const DevVolume& v, uint32_t
 
 // Points of every listed brick, per group and per super.  Direct: every brick
 // is listed, and there are no super sums.
-template <bool Direct>
+template <bool Direct, int Group>
 __global__ __launch_bounds__(256) void mvf_extract_count_kernel(DevVolume v, ExtractBuffers B, uint32_t nbricks)
 {
     __shared__ uint32_t wave_n[4];
     const int lane = threadIdx.x & 63, wave = wave_uniform((int)(threadIdx.x >> 6));
     const uint32_t nlist = Direct ? nbricks : *B.list_n;
-    for (uint32_t g = blockIdx.x; g * kExtractGroup < nlist; g += gridDim.x) {
+    for (uint32_t g = blockIdx.x; g * Group < nlist; g += gridDim.x) {
         uint32_t sum = 0;
-        for (int j = 0; j < kExtractGroup / 4; ++j) {
-            const uint32_t i = g * kExtractGroup + wave * (kExtractGroup / 4) + j;
+        for (int j = 0; j < Group / 4; ++j) {
+            const uint32_t i = g * Group + wave * (Group / 4) + j;
             if (i >= nlist) break;
             const uint32_t b = Direct ? i : (uint32_t)wave_uniform((int)B.list[i]);
             const uint64_t cm = cptr(v.cmask)[b];
@@ -2748,10 +2756,10 @@ __global__ __launch_bounds__(256) void mvf_extract_count_kernel(DevVolume v, Ext
 // The number of points, to the host.  A launch of its own (one wavefront, 2 to
 // 4 us): counting blocks that fence and take a ticket, so that the last one
 // can sum, took the count from 15 to 46 us (a cache writeback per block).
-template <bool Direct>
+template <bool Direct, int Group>
 __global__ __launch_bounds__(64) void mvf_extract_total_kernel(ExtractBuffers B, uint32_t nbricks)
 {
-    const uint32_t per = Direct ? kExtractGroup : kExtractGroup * kExtractSuper;
+    const uint32_t per = Direct ? Group : Group * kExtractSuper;
     const uint32_t n = ((Direct ? nbricks : *B.list_n) + per - 1) / per;
     const uint32_t* sums = Direct ? B.group_n : B.super_n;
     unsigned long long t = 0;
@@ -2761,7 +2769,7 @@ __global__ __launch_bounds__(64) void mvf_extract_total_kernel(ExtractBuffers B,
     if (threadIdx.x == 0) *B.total = (long long)t;
 }
 
-template <bool Direct>
+template <bool Direct, int Group>
 __global__ __launch_bounds__(256) void mvf_extract_emit_kernel(DevVolume v, ExtractBuffers B, uint32_t nbricks, float* V,
                                                                float* N, int32_t* G, long long cap)
 {
@@ -2769,21 +2777,21 @@ __global__ __launch_bounds__(256) void mvf_extract_emit_kernel(DevVolume v, Extr
     const int lane = threadIdx.x & 63, wave = wave_uniform((int)(threadIdx.x >> 6));
     const unsigned long long below = (1ull << lane) - 1ull;
     const uint32_t nlist = Direct ? nbricks : *B.list_n;
-    for (uint32_t g = blockIdx.x; g * kExtractGroup < nlist; g += gridDim.x) {
+    for (uint32_t g = blockIdx.x; g * Group < nlist; g += gridDim.x) {
         const uint32_t sg = Direct ? 0 : g / kExtractSuper;
         uint32_t before = 0;
         for (uint32_t i = threadIdx.x; i < sg; i += 256) before += B.super_n[i];
         for (uint32_t i = sg * kExtractSuper + threadIdx.x; i < g; i += 256) before += B.group_n[i];
         before = block_sum256(before, part);
         // the group's bricks before this wavefront's first
-        const uint32_t i0 = g * kExtractGroup;
-        const uint32_t cnt = lane < kExtractGroup && i0 + lane < nlist ? B.counts[i0 + lane] : 0u;
+        const uint32_t i0 = g * Group;
+        const uint32_t cnt = lane < Group && i0 + lane < nlist ? B.counts[i0 + lane] : 0u;
         unsigned long long base = before;
-        for (int q = 0; q < wave * (kExtractGroup / 4); ++q) base += (uint32_t)__shfl((int)cnt, q);
-        for (int j = 0; j < kExtractGroup / 4; ++j) {
-            const uint32_t i = i0 + wave * (kExtractGroup / 4) + j;
+        for (int q = 0; q < wave * (Group / 4); ++q) base += (uint32_t)__shfl((int)cnt, q);
+        for (int j = 0; j < Group / 4; ++j) {
+            const uint32_t i = i0 + wave * (Group / 4) + j;
             if (i >= nlist || (long long)base >= cap) break;
-            if (__shfl((int)cnt, wave * (kExtractGroup / 4) + j) == 0) continue;
+            if (__shfl((int)cnt, wave * (Group / 4) + j) == 0) continue;
             const uint32_t b = Direct ? i : (uint32_t)wave_uniform((int)B.list[i]);
             const uint64_t cm = cptr(v.cmask)[b];
             int bx, by, bz;
@@ -2827,10 +2835,14 @@ __global__ __launch_bounds__(256) void mvf_extract_emit_kernel(DevVolume v, Extr
     }
 }
 
+// Room for the smaller groups whatever the volume, so that no smaller volume
+// needs more.
+static size_t extract_groups(size_t nbricks) { return (nbricks + kExtractSmallGroup - 1) / kExtractSmallGroup; }
+
 size_t extract_buffer_bytes(size_t nbricks)
 {
     const size_t chunks = (nbricks + kExtractChunk - 1) / kExtractChunk;
-    return sizeof(uint32_t) * (2 * nbricks + (nbricks + kExtractGroup - 1) / kExtractGroup + 2 * chunks + 1);
+    return sizeof(uint32_t) * (2 * nbricks + extract_groups(nbricks) + 2 * chunks + 1);
 }
 
 ExtractBuffers extract_buffers(void* mem, size_t nbricks, long long* total)
@@ -2841,35 +2853,37 @@ ExtractBuffers extract_buffers(void* mem, size_t nbricks, long long* total)
     B.list = static_cast<uint32_t*>(mem);
     B.counts = B.list + nbricks;
     B.group_n = B.counts + nbricks;
-    B.chunk_n = B.group_n + (nbricks + kExtractGroup - 1) / kExtractGroup;
+    B.chunk_n = B.group_n + extract_groups(nbricks);
     B.super_n = B.chunk_n + chunks;
     B.list_n = B.super_n + chunks;
     B.total = total;
     return B;
 }
 
-template <bool Direct>
+template <bool Direct, int Group>
 static void launch_extract_points(DevVolume v, const ExtractBuffers& B, uint32_t nb, float* V, float* N, int32_t* G,
                                   long long cap, hipStream_t s)
 {
-    const unsigned blocks = std::min<unsigned>(kExtractBlocks, (nb + kExtractGroup - 1) / kExtractGroup);
-    hipLaunchKernelGGL(mvf_extract_count_kernel<Direct>, dim3(blocks), dim3(256), 0, s, v, B, nb);
-    hipLaunchKernelGGL(mvf_extract_total_kernel<Direct>, dim3(1), dim3(64), 0, s, B, nb);
+    const unsigned blocks = std::min<unsigned>(kExtractBlocks, (nb + Group - 1) / Group);
+    hipLaunchKernelGGL((mvf_extract_count_kernel<Direct, Group>), dim3(blocks), dim3(256), 0, s, v, B, nb);
+    hipLaunchKernelGGL((mvf_extract_total_kernel<Direct, Group>), dim3(1), dim3(64), 0, s, B, nb);
     if (cap > 0)
-        hipLaunchKernelGGL(mvf_extract_emit_kernel<Direct>, dim3(blocks), dim3(256), 0, s, v, B, nb, V, N, G, cap);
+        hipLaunchKernelGGL((mvf_extract_emit_kernel<Direct, Group>), dim3(blocks), dim3(256), 0, s, v, B, nb, V, N, G, cap);
 }
 
 int launch_extract(DevVolume v, const ExtractBuffers& B, float* V, float* N, int32_t* G, long long cap, void* stream)
 {
     hipStream_t s = (hipStream_t)stream;
     const uint32_t nb = (uint32_t)v.bd[0] * (uint32_t)v.bd[1] * (uint32_t)v.bd[2];
-    if (nb <= kExtractDirect) {
-        launch_extract_points<true>(v, B, nb, V, N, G, cap, s);
+    if (nb <= kExtractSmall) {
+        launch_extract_points<true, kExtractSmallGroup>(v, B, nb, V, N, G, cap, s);
+    } else if (nb <= kExtractDirect) {
+        launch_extract_points<true, kExtractGroup>(v, B, nb, V, N, G, cap, s);
     } else {
         const unsigned chunks = (nb + kExtractChunk - 1) / kExtractChunk;
         hipLaunchKernelGGL(mvf_extract_mark_kernel, dim3(chunks), dim3(256), 0, s, v, nb, B);
         hipLaunchKernelGGL(mvf_extract_list_kernel, dim3(chunks), dim3(256), 0, s, v, nb, B);
-        launch_extract_points<false>(v, B, nb, V, N, G, cap, s);
+        launch_extract_points<false, kExtractGroup>(v, B, nb, V, N, G, cap, s);
     }
     return (int)hipGetLastError();
 }

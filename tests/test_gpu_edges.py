@@ -112,6 +112,40 @@ def test_surface_points_edges(mvf, dims, share):
         assert not ok.any() or np.abs(Nd[ok] - No[ok]).max() <= 2e-3
 
 
+def test_surface_points_group_sizes(mvf):
+    """Volumes on both sides of the lines between small groups of bricks, large
+    ones and listed bricks, one after the other in one context, each into the
+    scratch that a larger one or none has left: points of random values in a
+    share of the bricks, against the oracle on the same values, with the bounds of
+    test_surface_points_edges."""
+    rng = np.random.default_rng(12)
+    og = O.OGrid((-0.3, 0.1, 0.2), 0.02, 4.0, 128)
+    with mvf.Context() as ctx:
+        gid = ctx.grid((-0.3, 0.1, 0.2), 0.02)
+        for dims, share in (((24, 16, 8), 1.0), ((256, 256, 136), 0.01), ((256, 256, 128), 0.01), ((240, 232, 232), 0.004),
+                            ((232, 232, 232), 0.004), ((256, 256, 128), 0.02), ((16, 8, 8), 1.0)):
+            log(f"surface points group sizes {dims}")
+            nx, ny, nz = dims
+            F = rng.uniform(0.05, 0.95, (nz, ny, nx)).astype(np.float32)
+            bricks = rng.random([n // 8 for n in (nz, ny, nx)]) < share
+            F[np.kron(bricks, np.ones((8, 8, 8), bool)) & (rng.random(F.shape, np.float32) < 0.3)] *= -1.0
+            W = np.full(F.shape, 7, np.uint16)
+            vid = ctx.volume(gid, (3, -5, 11), dims)
+            ctx.write_volume(vid, F, W, None)
+            ov = O.OVolume(dims, (3, -5, 11), F.astype(np.float64), W, np.zeros(W.shape + (4,), np.uint8))
+            ref = O.extract(ov, og, F32=F)
+            got = {k: v.cpu().numpy() if hasattr(v, "cpu") else v for k, v in ctx.extract(vid).items()}
+            ctx.destroy_volume(vid)
+            assert got["n"] == ref["n"] > 0
+            order = [np.lexsort(x["G"].T) for x in (got, ref)]
+            np.testing.assert_array_equal(got["G"][order[0]], ref["G"][order[1]])
+            assert np.abs(got["V"][order[0]].astype(np.float64) - ref["V"][order[1]]).max() <= 1e-4
+            No, Nd = ref["N"][order[1]], got["N"][order[0]]
+            ok = np.isfinite(No).all(axis=1)
+            assert np.array_equal(ok, np.isfinite(Nd).all(axis=1))
+            assert np.abs(Nd[ok] - No[ok]).max() <= 2e-3
+
+
 @pytest.mark.parametrize("w,h,iters", [(17, 13, (2,)), (64, 48, (2, 2)), (333, 251, (2, 1, 2)), (1100, 500, (2, 2, 1))])
 def test_track_edges(mvf, w, h, iters):
     """Images of less than a block, of partial blocks and of more blocks than
