@@ -307,7 +307,7 @@ mvf_status mvf_get_schedule(mvf_ctx* ctx, mvf_schedule* out);
  * schedule between each two of the 7 other candidates (timed with HIP events
  * on the call's stream; the step's results are unaffected); each block
  * counts by the mean of its last seven runs without their highest and lowest
- * (the first pays the allocations), and the shape keeps the candidate
+ * (the first may pay allocations), and the shape keeps the candidate
  * fastest relative to the mean of the default blocks around it.  Tune on
  * representative frames: the fastest schedule depends on how much of the
  * volumes the frames see.  cache_path (may be NULL: memory

@@ -196,12 +196,12 @@ struct TimedPair {
 struct StepBuffers {
     bool valid = false;
     int n = 0;
-    std::vector<int> widths, heights, out_w, out_h;
+    std::vector<int> out_w, out_h;
     // persistent device tables read by the step's kernels
     uint8_t* dev = nullptr;
     size_t dev_bytes = 0;
     size_t off_hdr, off_prep, off_frames, off_vols, off_items, off_lists, off_lbase, off_tbase, off_bbase;
-    int max_vols = 0, max_w = 0, max_h = 0;
+    int max_vols = 0;
     int ray_tiles = 0;
     float* ztab = nullptr;  // integration z table
     int ztab_cap = 0;
@@ -215,7 +215,6 @@ struct StepBuffers {
     uint32_t* rb_counts = nullptr;        // 2 * max_vols
     int rb_parity = 0;
     int max_cells_x = 0, max_cells_y = 0;
-    mvf_schedule sched{4, 0, kRayLanes, 0};  // schedule of the last step
     uint32_t* tile_cost = nullptr;  // raycast tiles: last duration, then launch order
     int32_t* tile_order = nullptr;
 };
@@ -1295,9 +1294,9 @@ mvf_status destroy_step_buffers(mvf_ctx* c)
 
 // ---- step schedules and their autotuner -------------------------------------
 
-// runs per block of one schedule; the first (which pays the allocations and
-// starts the raycast tile order afresh) is not counted, and a block scores
-// the mean of the others without their highest and lowest.  The blocks alternate
+// runs per block of one schedule; the first (which may pay allocations, and
+// orders the raycast's tiles by durations under another schedule) is not counted,
+// and a block scores the mean of the others without their highest and lowest.  The blocks alternate
 // between the reference schedule (the first candidate, the default) and the
 // other candidates in turn: ref, c1, ref, c2, ..., ref.  A candidate is scored
 // by its score over the mean of the two reference scores around it, so that
@@ -1315,14 +1314,9 @@ bool valid_schedule(const mvf_schedule& s)
            (s.ray_lanes == 2 || s.ray_lanes == 4 || s.ray_lanes == 8);
 }
 
-bool same_schedule(const mvf_schedule& a, const mvf_schedule& b)
-{
-    return a.zchunk == b.zchunk && a.persistent == b.persistent && a.ray_lanes == b.ray_lanes;
-}
-
 // Candidates tried for a new shape: the default first (the reference), then
-// every other z chunk and integration grid at 4 lanes per ray, then the other
-// lane counts at the default.
+// every other z chunk and integration grid at the default ray_lanes, then the
+// other ray_lanes at the default z chunk and grid.
 std::vector<mvf_schedule> tune_candidates()
 {
     std::vector<mvf_schedule> c{mvf_schedule{kZChunk, 0, kRayLanes, 0}};
@@ -2135,20 +2129,18 @@ mvf_status mvf_step(mvf_ctx* c, int32_t n, const mvf_stream_frame* frames, const
         items_total += v.bd[0] * v.bd[1] * ((v.bd[2] + sch.zchunk - 1) / sch.zchunk);
         bricks_total += (int)align_up(v.nbricks, 64);
     }
-    bool same_shape = G.valid && G.n == n && (int)all.size() <= G.max_vols && max_w <= G.max_w && max_h <= G.max_h &&
-                      ztotal <= G.ztab_cap && items_total <= G.visit_cap && bricks_total <= G.rb_entries_cap &&
-                      same_schedule(sch, G.sched);
+    // (a change of schedule or of the frames' sizes needs no new buffers, and keeps
+    // the tiles' durations)
+    bool same_shape = G.valid && G.n == n && (int)all.size() <= G.max_vols && ztotal <= G.ztab_cap &&
+                      items_total <= G.visit_cap && bricks_total <= G.rb_entries_cap;
     if (same_shape) {
         for (int i = 0; i < n; ++i)
             if (G.out_w[i] != outs[i].width || G.out_h[i] != outs[i].height) same_shape = false;
     }
     if (!same_shape) {
         CHECK_ST(destroy_step_buffers(c));
-        G.sched = sch;
         G.n = n;
         G.max_vols = std::max<int>((int)all.size() * 2, 16);
-        G.max_w = max_w;
-        G.max_h = max_h;
         G.out_w.assign(n, 0);
         G.out_h.assign(n, 0);
         for (int i = 0; i < n; ++i) {

@@ -136,3 +136,27 @@ def test_clears_of_a_call_that_fails(lib):
         CALLS[call](m)
         assert lib.t_unordered().decode() == ""
     m.close()
+
+
+def test_step_buffers_are_kept(lib):
+    """A batched step's buffers depend on its outputs' sizes and its volumes:
+    another schedule allocates nothing, and other input frames only what a plain
+    integration does."""
+    m, plain = Map(lib, volumes=3), Map(lib, volumes=3)
+    m.step()
+    before = lib.t_allocs()
+    for z, persistent, lanes in ((2, 0, 4), (8, 1, 2), (4, 1, 8), (4, 0, 4)):
+        m.ok("mvf_set_schedule", C.byref(L.mvf_schedule(z, persistent, lanes, 0)))
+        m.step()
+        assert lib.t_allocs() == before, (z, persistent, lanes)
+    CALLS["integrate"](plain)
+    for width, height in ((48, 40), (40, 48), (16, 8)):
+        counts = []
+        for x, call in ((plain, CALLS["integrate"]), (m, CALLS["step"])):
+            x.size(width, height, out=(32, 24))
+            before = lib.t_allocs()
+            call(x)
+            counts.append(lib.t_allocs() - before)
+        assert counts[0] == counts[1], (width, height)
+    for x in (m, plain):
+        x.close()
