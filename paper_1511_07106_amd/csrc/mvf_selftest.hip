@@ -1,14 +1,17 @@
-// Self-test of the hardware square-root estimate that the integration
-// kernel's square-root filter relies on (not part of the libmvf ABI; built
-// as libmvf_selftest.so for the GPU tests).
+// Self-tests of device code that no entry point shows alone (not part of the
+// libmvf ABI; built as libmvf_selftest.so for the GPU tests): the hardware
+// square-root estimate that the integration kernel's square-root filter relies
+// on, and the raycast's launch order.
 //
-// For every binary32 x with bit pattern in [first, first + count) (positive
+// The estimate: for every binary32 x with bit pattern in [first, first + count) (positive
 // values), compares the estimate (v_sqrt_f32) with the correctly rounded
 // root: the largest distance in units in the last place for x >= 2^-96, and
 // the largest absolute difference for x < 2^-96.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <string.h>
+
+#include "mvf_tile_order.h"
 
 namespace {
 
@@ -38,7 +41,40 @@ __global__ __launch_bounds__(256) void sqrt_check_kernel(uint32_t first, uint32_
     }
 }
 
+__global__ __launch_bounds__(1024) void tile_order_kernel(mvf::TileOrder O)
+{
+    __shared__ int hist[mvf::kOrderBins];
+    mvf::tile_order_block(O, hist);
+}
+
 }  // namespace
+
+// The launch order of `tiles` tiles from their durations (zeroed on return), by
+// a block of `threads` threads: the plan's kRayPlanInts words, then the tiles.
+// Returns 0 on success.  Synchronous.
+extern "C" int mvf_selftest_tile_order(uint32_t* cost, int32_t* order, int tiles, int level, int max_blocks, int slots,
+                                       int fresh, int threads)
+{
+    if (!cost || !order || tiles <= 0 || tiles > (1 << 22) || level < 0 || level >= mvf::kRayLevels || max_blocks <= 0 ||
+        slots <= 0 || (threads != 256 && threads != 1024))
+        return 1;
+    const size_t nc = (size_t)tiles * sizeof(uint32_t), no = ((size_t)tiles + mvf::kRayPlanInts) * sizeof(int32_t);
+    uint8_t* d = nullptr;
+    if (hipMalloc((void**)&d, nc + no) != hipSuccess) return 2;
+    mvf::TileOrder O{reinterpret_cast<uint32_t*>(d), reinterpret_cast<int32_t*>(d + nc), tiles, level, max_blocks, slots,
+                     fresh};
+    int rc = 0;
+    if (hipMemcpy(d, cost, nc, hipMemcpyHostToDevice) != hipSuccess) rc = 3;
+    if (!rc) {
+        hipLaunchKernelGGL(tile_order_kernel, dim3(1), dim3(threads), 0, nullptr, O);
+        if (hipGetLastError() != hipSuccess) rc = 4;
+    }
+    if (!rc && (hipMemcpy(cost, d, nc, hipMemcpyDeviceToHost) != hipSuccess ||
+                hipMemcpy(order, d + nc, no, hipMemcpyDeviceToHost) != hipSuccess))
+        rc = 5;
+    (void)hipFree(d);
+    return rc;
+}
 
 // Returns 0 on success.  max_ulp: largest ulp distance for x >= 2^-96;
 // max_abs: largest absolute difference for x < 2^-96.  Synchronous.
