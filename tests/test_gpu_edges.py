@@ -550,3 +550,117 @@ def test_calls_on_alternating_streams(mvf):
     for a, b in zip(oa, ob):
         for k in b:
             np.testing.assert_array_equal(a[k], b[k])
+
+
+@pytest.mark.parametrize("steps", [1, 2, 3, 4, 5])
+def test_steps_and_plain_calls_on_streams(mvf, steps):
+    """Batched steps, whose table slots are released in fours, between plain
+    integrations and raycasts, dealt over three streams, over more calls than
+    there are slots: the single stream's maps and volumes bit for bit."""
+    import torch
+    log(f"{steps} steps and plain calls on streams")
+    rng = np.random.default_rng(steps)
+    w, h, n = 96, 72, 12
+    K = np.array([84.0, 85.0, w / 2 - 0.3, h / 2 + 0.2], np.float32)
+    T = [np.array([[1.0, 0.0, 0.0, 1.0 + 0.02 * i], [0.0, 1.0, 0.0, 1.0], [0.0, 0.0, 1.0, -0.3]]) for i in range(n)]
+    frames = [t(_random_depth(rng, w, h, 1.0, 1.4)) for _ in range(n)]
+    torch.cuda.synchronize()
+
+    def run(streams):
+        with mvf.Context() as ctx:
+            gid = ctx.grid((0.0, 0.0, 0.0), 0.01, 4.0, 128)
+            ids = [ctx.volume(gid, o, (100, 100, 128)) for o in ((0, 0, 0), (99, 0, 0), (0, 99, 0), (99, 99, 0))]
+            outs = [[{k: torch.zeros((h, w) + tail, dtype=dt, device="cuda") for k, tail, dt in
+                      (("depth", (), torch.float32), ("vertex", (3,), torch.float32), ("normal", (3,), torch.float32),
+                       ("hit", (), torch.int32))} for _ in range(steps + 1)] for _ in range(n)]
+            torch.cuda.synchronize()
+            call = iter(range(1 << 20))
+            for i in range(n):
+                s = streams[next(call) % len(streams)]
+                for j in range(steps):
+                    ctx.step([(0, frames[(i + j) % n], None, T[i], K)], [outs[i][j]], stream=s)
+                ctx.integrate(frames[i], None, T[i], K, stream=streams[next(call) % len(streams)])
+                ctx.raycast(T[i], K, w, h, out=outs[i][steps], stream=streams[next(call) % len(streams)])
+                if i % 3 == 2:
+                    next(call)   # the streams take other turns
+            torch.cuda.synchronize()
+            return [ctx.read_volume(i) for i in ids], [{k: v.cpu().numpy() for k, v in o.items()} for r in outs for o in r]
+
+    (va, oa), (vb, ob) = run([torch.cuda.Stream() for _ in range(3)]), run([None])
+    assert all((v[1] > 0).any() for v in vb) and (ob[-1]["hit"] >= 0).any()
+    for a, b in zip(va, vb):
+        for x, y in zip(a, b):
+            np.testing.assert_array_equal(x, y)
+    for a, b in zip(oa, ob):
+        for k in b:
+            np.testing.assert_array_equal(a[k], b[k])
+
+
+@pytest.mark.parametrize("n", [16, 17, 33])
+def test_step_streams_of_different_sizes(mvf, n):
+    """As many streams as the preparation takes as arguments, one more, and many
+    more, each with frames and maps of its own size: a batched step's volumes and
+    maps equal the plain calls' bit for bit, and every stream observes voxels and
+    hits a surface."""
+    log(f"step {n} streams of different sizes")
+    rng = np.random.default_rng(100 + n)
+    size = [(24 + 5 * (i % 7), 18 + 3 * (i % 11)) for i in range(n)]
+    out_size = [(w + 3 - i % 5, h + i % 4) for i, (w, h) in enumerate(size)]
+    Ks = [np.array([0.9 * w, 0.92 * w, w / 2 - 0.3, h / 2 + 0.2], np.float32) for w, h in size]
+    T = np.array([[1.0, 0.0, 0.0, 0.5], [0.0, 1.0, 0.0, 0.5], [0.0, 0.0, 1.0, -0.3]])
+    frames = [(t(rng.uniform(0.8, 0.85, (h, w)).astype(np.float32)), t(rng.integers(0, 256, (h, w, 3), dtype=np.uint8)))
+              for w, h in size]
+
+    def run(step):
+        with mvf.Context() as ctx:
+            gid = ctx.grid((0.0, 0.0, 0.0), 0.025, 4.0, 128)
+            ids = [ctx.volume(gid, (0, 0, 0), (40, 40, 40), stream_id=i) for i in range(n)]
+            outs = [ctx.raycast(T, Ks[i], *out_size[i], stream_id=i) for i in range(n)]
+            for _ in range(2):
+                if step:
+                    ctx.step([(i, d, c, T, Ks[i]) for i, (d, c) in enumerate(frames)], outs)
+                else:
+                    for i, (d, c) in enumerate(frames):
+                        ctx.integrate(d, c, T, Ks[i], stream_id=i)
+                        ctx.raycast(T, Ks[i], *out_size[i], stream_id=i, out=outs[i])
+            vols = [ctx.read_volume(i) for i in ids]
+            return vols, [{k: v.cpu().numpy() for k, v in o.items()} for o in outs]
+
+    (va, oa), (vb, ob) = run(True), run(False)
+    for i in range(n):
+        assert (va[i][1] > 0).any() and (oa[i]["hit"] >= 0).any(), i
+        for a, b in zip(va[i], vb[i]):
+            np.testing.assert_array_equal(a, b)
+        for k in oa[i]:
+            np.testing.assert_array_equal(oa[i][k], ob[i][k])
+
+
+def test_integrate_grids_together(mvf):
+    """Volumes on grids of different voxel sizes, truncations, weight caps and
+    origins share the launches of a plain integration: each volume and its brick
+    summary the same bit for bit as when it is alone in a context."""
+    log("integrate grids together")
+    rng = np.random.default_rng(8)
+    w, h = 160, 120
+    K = np.array([140.0, 141.0, w / 2 - 0.3, h / 2 + 0.2], np.float32)
+    T = np.array([[1.0, 0.0, 0.0, 0.5], [0.0, 1.0, 0.0, 0.5], [0.0, 0.0, 1.0, -0.4]])
+    frames = [(t(_random_depth(rng, w, h, 0.6, 1.3)), t(rng.integers(0, 256, (h, w, 3), dtype=np.uint8))) for _ in range(4)]
+    grids = [((0.0, 0.0, 0.0), 0.01, 4.0, 128), ((0.1, -0.2, 0.05), 0.025, 3.0, 2), ((-0.3, 0.0, 0.2), 0.004, 7.5, 3)]
+    vols = [(0, (0, 0, 0), (100, 100, 90)), (1, (0, 8, -3), (41, 33, 40)), (2, (90, 20, 0), (130, 121, 128)),
+            (1, (3, 40, 1), (20, 9, 50)), (0, (20, 30, 40), (64, 64, 8))]
+
+    def fuse(ctx, which):
+        gids = [ctx.grid(*g) for g in grids]
+        ids = [ctx.volume(gids[g], off, dims) for g, off, dims in which]
+        for d, c in frames:
+            ctx.integrate(d, c, T, K)
+        return [ctx.read_volume(i) + ctx.brick_summary(i) for i in ids]
+
+    with mvf.Context() as ctx:
+        got = fuse(ctx, vols)
+    for v, g in zip(vols, got):
+        with mvf.Context() as ctx:
+            (alone,) = fuse(ctx, [v])
+        assert (alone[1] > 0).any()
+        for a, b in zip(g, alone):
+            np.testing.assert_array_equal(a, b)

@@ -160,3 +160,22 @@ def test_step_buffers_are_kept(lib):
         assert counts[0] == counts[1], (width, height)
     for x in (m, plain):
         x.close()
+
+
+@pytest.mark.parametrize("steps", [1, 2, 3, 4, 5])
+def test_calls_run_in_order_on_any_stream(lib, steps):
+    """Batched steps, whose table slots are released in fours, between the other
+    calls, dealt over three streams and the null stream, over more calls than
+    there are slots: everything launched runs after everything before it."""
+    m = Map(lib, volumes=3)
+    streams = [lib.t_stream() for _ in range(3)] + [None]
+    lib.t_watch()
+    for i in range(16):
+        m.stream = streams[i % 3]
+        for _ in range(steps):
+            m.step()
+        for j, call in enumerate(("integrate", "raycast", "extract", "raycast", "step", "integrate")):
+            m.stream = streams[(2 * i + j) % 4]
+            CALLS[call](m)
+    assert lib.t_unordered().decode() == ""
+    m.close()
