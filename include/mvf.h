@@ -266,8 +266,9 @@ typedef struct {
 
 /* Integrate frames[i] into the active volumes of frames[i].stream_id, then
  * raycast every stream at its frame's pose into outs[i], for all n streams
- * at once: one persistent integration launch and one persistent raycast
- * launch over a device volume table.  Results equal the plain calls bit for bit.  When the active
+ * at once: one launch of each kernel over a device volume table (frame
+ * preparation, integration and its visit pass, distance transform, range
+ * bounds, raycast).  Results equal the plain calls bit for bit.  When the active
  * in-view volumes of the streams do not fit the budget together they are
  * processed in waves that do (swapping volumes in and out, Memory Passing
  * section), one chain of launches per wave, the raycast of each wave merged

@@ -184,15 +184,6 @@ struct PrepArgs {
     PrepItem item[kPrepInline];
 };
 
-// Integration work item: a brick column (8x8 voxel columns) of one volume
-// over a chunk of zchunk bricks along z.  Items of table entry v are
-// [item_base[v], item_base[v+1]).
-//
-// z table: for volume v and local z in [0, 8 * bd[2]), entry
-// vols[v].zt_base + z holds 3 floats: T[8], T[9], T[10] times
-// (x_w(z) - T[11]), the camera-frame offset of the voxel plane z (binary32,
-// the same operations as the voxel test).  Written by launch_ztable before
-// the integration kernel runs; ztab holds >= hdr->total_z entries.
 // The raycast's work: pixel tiles of 8x8 (one range-bound cell each), each
 // marched by 2^level one-wavefront blocks of 64 >> level pixels, 2^level lanes
 // per ray.  More lanes per ray make a tile's longest chain of rounds shorter
@@ -233,6 +224,15 @@ struct TileOrder {
     int32_t fresh;      // ignore the durations (of another image size)
 };
 
+// Integration work item: a brick column (8x8 voxel columns) of one volume
+// over a chunk of zchunk bricks along z.  Items of table entry v are
+// [item_base[v], item_base[v+1]).
+//
+// z table: for volume v and local z in [0, 8 * bd[2]), entry
+// vols[v].zt_base + z holds 3 floats: T[8], T[9], T[10] times
+// (x_w(z) - T[11]), the camera-frame offset of the voxel plane z (binary32,
+// the same operations as the voxel test).  Written by launch_ztable before
+// the integration kernel runs; ztab holds >= hdr->total_z entries.
 struct IntegrateLaunch {
     const LaunchHeader* hdr;
     const DevVolume* vols;

@@ -505,7 +505,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void m
             const size_t base = colbase + (size_t)bz * kBrickVox;
             GPTR(float) const pF = vF + base;
             GPTR(uint16_t) const pW = vW + base;
-            // a deep brick has a wavefront of its own (integrate_deep_brick)
+            // a deep brick has a wavefront of its own (integrate_deep_bricks)
             if ((vis >> (8 * (bz - bz0) + 1)) & 1ull) continue;
             // the brick's 8 z-table entries, one scalar block
             struct ZRow { float v[3 * kBrick]; };
@@ -1681,8 +1681,8 @@ int launch_column_flags(DevVolume v, void* stream)
 // bounds, the brick's footprint.
 // ---------------------------------------------------------------------------
 constexpr int kDistSide = 2 * kDistCap + 1;
-// Wavefronts of the distance lines (1.3 us a line): one a line up to half of
-// what the device holds.  With 256 for any number of volumes, each of which
+// Wavefronts of the distance lines (1.3 us a line): one a line up to 2048
+// (2 to a SIMD, of the 5 that fit).  With 256 for any number of volumes, each of which
 // walked the whole volume table for its lines, 48 volumes of up to 384^3 took
 // 42 us, now 30; eight of 257^3 12.5 and 8.5.
 constexpr int kDistWavesMax = 2048;
@@ -2747,13 +2747,13 @@ int launch_extract(DevVolume v, const ExtractBuffers& B, float* V, float* N, int
 
 // ---------------------------------------------------------------------------
 // Differentiable raycast on one dense x-fastest volume (F, W).  The forward
-// is the same march (binary32 contract; validity from W), skipping bricks by
-// a summary computed for the call; it records k of the crossing's second
-// sample.  The backward
-// recomputes the two bracketing samples from k, and with the structure held
-// fixed scatters dL/dF (16 voxels per pixel, float atomics) and reduces
-// dL/dxi per block into binary64 partials, summed by a second kernel in a
-// fixed order (deterministic).
+// is the same march (binary32 contract; validity from W), in a
+// mirror of the TSDF in bricks with their summaries; it records k of the
+// crossing's second sample.  The backward recomputes the two bracketing samples
+// from k, and with the structure held fixed gathers dL/dF of a block's pixels
+// (8 voxels a sample) in LDS before the float atomics, and reduces dL/dxi per
+// block into binary64 partials, summed by a second kernel in a fixed order
+// (deterministic).
 // ---------------------------------------------------------------------------
 static __device__ __forceinline__ double lerp64(double a, double b, double t)
 {

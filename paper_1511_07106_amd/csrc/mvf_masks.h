@@ -71,10 +71,11 @@ MVF_HD uint32_t occupancy_z(uint64_t m)
            ((m >> 48) ? 8u : 0u);
 }
 
-// Grow the clear box [lo, hi] (sub-blocks; (cm & box) == 0 on entry) along
-// x, then y, then z, each as far as it stays clear, towards the sign of
-// dir[a] (no growth along an axis with dir 0).  The same box as growing one
-// sub-block at a time.
+// The clear box of a sample axis by axis: grow [lo, hi] (sub-blocks; (cm & box)
+// == 0 on entry) along x, then y, then z, each as far as it stays clear, towards
+// the sign of dir[a] (no growth along an axis with dir 0).  The same box as
+// growing one sub-block at a time.  No kernel uses it, nor subblock_box: it is the
+// reference that the tests hold clear_ahead to.
 template <class F>
 MVF_HD void grow_clear_box(uint64_t cm, int lo[3], int hi[3], const F dir[3])
 {

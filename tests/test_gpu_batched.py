@@ -1,6 +1,5 @@
-"""The batched form (one persistent integration launch and one persistent
-raycast launch over a device volume table, captured once in a HIP graph and
-replayed) gives the same bits as the plain per-volume calls."""
+"""The batched form (one launch of each kernel over a device volume table)
+gives the same bits as the plain per-volume calls."""
 import numpy as np
 import pytest
 

@@ -1,7 +1,7 @@
 """Oracle parity at the shapes the benchmark times (Comparison to
 KinectFusion; Memory Passing):
 
-- the captured step (mvf_step, one graph replay per frame) on one 512^3
+- the batched step (mvf_step, one call per frame) on one 512^3
   volume over the 3 m large room, 640x480, under several launch schedules
   and under the schedule the autotuner picks;
 - the 8 x 257^3 tiling at offsets {0, 255}^3 through the plain calls and
