@@ -127,6 +127,7 @@ struct Scratch {
     int32_t* list = nullptr;   // integration: visited bricks, then deep bricks (8 per item each)
     unsigned long long* list_count = nullptr;  // two count words, zeroed at allocation
     int list_parity = 0;
+    bool unfinished = false;    // the last call did not make all its launches
     uint32_t* tile_cost = nullptr;  // raycast tiles: last duration, then launch order
     int32_t* tile_order = nullptr;
     int tiles_cap = 0;
@@ -787,6 +788,28 @@ mvf_status clear_new(mvf_ctx* c, void* p, int words, hipStream_t stream)
     return mark_tail(c, stream);
 }
 
+// A call's launches leave the counts that the next call appends to at zero, and
+// the tiles in an order, only if all of them are made: after a call that was
+// refused or failed on the way, the next one clears the counts and orders anew.
+mvf_status begin_launches(mvf_ctx* c, Scratch* s, hipStream_t stream)
+{
+    if (s->unfinished) {
+        if (s->list_count) CHECK_ST(clear_new(c, s->list_count, 2, stream));
+        if (s->rb_counts) CHECK_ST(clear_new(c, s->rb_counts, s->rb_counts_cap, stream));
+        s->last_tiles = s->order_ready_tiles = 0;
+    }
+    s->unfinished = true;
+    return MVF_OK;
+}
+
+// The end of a call that may have launched part of its work: later calls run
+// after it.
+mvf_status settle(mvf_ctx* c, mvf_status st, hipStream_t stream)
+{
+    if (st != MVF_OK) (void)mark_tail(c, stream);
+    return st;
+}
+
 // Raycast duration per tile (zero: not known) and launch order, for n tiles.
 mvf_status alloc_tile_buffers(mvf_ctx* c, int n, uint32_t** cost, int32_t** order, hipStream_t stream)
 {
@@ -1049,6 +1072,7 @@ mvf_status integrate_plain(mvf_ctx* c, int sid, const mvf_frame* f, const float*
         CHECK_HIP(hipMalloc((void**)&sc->list_count, 2 * sizeof(unsigned long long)));
         CHECK_ST(clear_new(c, sc->list_count, 2, stream));
     }
+    CHECK_ST(begin_launches(c, sc, stream));
     // once per raycast (the ordering uses the durations up)
     bool order_pending = sc->tile_cost && sc->last_tiles > 0 && sc->order_ready_tiles == 0;
     hipEvent_t tail = nullptr;   // there is a wave, if an empty one
@@ -1127,6 +1151,7 @@ mvf_status integrate_plain(mvf_ctx* c, int sid, const mvf_frame* f, const float*
         CHECK_ST(arena_release(c, slot2, stream));
         tail = c->arena.ev[slot2];
     }
+    sc->unfinished = false;
     return mark_tail_at(c, tail, stream);
 }
 
@@ -1148,6 +1173,7 @@ mvf_status raycast_plain(mvf_ctx* c, int sid, const float* T, const mvf_intrinsi
     const int tiles = ray_tiles(out->width, out->height);
     CHECK_ST(get_tile_buffers(c, sc, tiles, stream));
     CHECK_ST(get_bound_buffers(sc, out->width, out->height));
+    CHECK_ST(begin_launches(c, sc, stream));
     // an order the integration computed holds for this many tiles only (else the merge computes one)
     const bool ordered = sc->order_ready_tiles == tiles && sc->last_tiles == tiles;
     const bool fresh = sc->last_tiles != tiles;
@@ -1231,6 +1257,7 @@ mvf_status raycast_plain(mvf_ctx* c, int sid, const float* T, const mvf_intrinsi
         c->stats.raycast_launches += 1;
     }
     c->stats.pixels_raycast += (uint64_t)out->width * out->height;
+    sc->unfinished = false;
     return mark_tail_at(c, tail, stream);
 }
 
@@ -2034,7 +2061,7 @@ mvf_status mvf_integrate(mvf_ctx* c, int32_t sid, const mvf_frame* f, const floa
     hipStream_t s = (hipStream_t)stream;
     CHECK_ST(order_after_previous(c, s));
     std::vector<int> ids = stream_volumes(c, sid, T_wc, *K, f->width, f->height);
-    return integrate_plain(c, sid, f, T_wc, *K, ids, s);
+    return settle(c, integrate_plain(c, sid, f, T_wc, *K, ids, s), s);
 }
 
 mvf_status mvf_raycast(mvf_ctx* c, int32_t sid, const float T_wc[12], const mvf_intrinsics* K,
@@ -2054,10 +2081,13 @@ mvf_status mvf_raycast(mvf_ctx* c, int32_t sid, const float T_wc[12], const mvf_
     for (int id : ids)
         if (c->vols[id].d.grid_id != c->vols[ids[0]].d.grid_id)
             return set_error(MVF_ERR_UNSUPPORTED, "volumes of stream %d lie on different grids", sid);
-    return raycast_plain(c, sid, T_wc, *K, out, ids, s);
+    return settle(c, raycast_plain(c, sid, T_wc, *K, out, ids, s), s);
 }
 
 // ---- batched step -------------------------------------------------------------
+
+static mvf_status step_launches(mvf_ctx* c, int32_t n, const mvf_stream_frame* frames, const mvf_raycast_out* outs,
+                                hipStream_t s);
 
 mvf_status mvf_step(mvf_ctx* c, int32_t n, const mvf_stream_frame* frames, const mvf_raycast_out* outs, void* stream)
 {
@@ -2078,7 +2108,12 @@ mvf_status mvf_step(mvf_ctx* c, int32_t n, const mvf_stream_frame* frames, const
     CHECK_HIP(hipSetDevice(c->device));
     hipStream_t s = (hipStream_t)stream;
     CHECK_ST(order_after_previous(c, s));
+    return settle(c, step_launches(c, n, frames, outs, s), s);
+}
 
+static mvf_status step_launches(mvf_ctx* c, int32_t n, const mvf_stream_frame* frames, const mvf_raycast_out* outs,
+                                hipStream_t s)
+{
     // volumes per stream (integration set == raycast set: active and in view)
     std::vector<std::vector<int>> per(n);
     std::vector<int> all;
@@ -2180,8 +2215,10 @@ mvf_status mvf_step(mvf_ctx* c, int32_t n, const mvf_stream_frame* frames, const
         for (int i = 0; i < n; ++i) tiles += ray_tiles(outs[i].width, outs[i].height);
         G.ray_tiles = tiles;
         CHECK_ST(alloc_tile_buffers(c, tiles, &G.tile_cost, &G.tile_order, s));
-        G.valid = true;
     }
+    // made anew if this call does not make all its launches (its counts would
+    // not be zero)
+    G.valid = false;
     // scratch per stream (with the running best of a multi-wave raycast)
     std::vector<Scratch*> sc(n);
     for (int i = 0; i < n; ++i)
@@ -2344,6 +2381,7 @@ mvf_status mvf_step(mvf_ctx* c, int32_t n, const mvf_stream_frame* frames, const
         }
         CHECK_ST(arena_release_step(c, slot, s));  // reused once the launch that reads it is done
     }
+    G.valid = true;
     CHECK_ST(timing_end(c, s, t0, 2));
     c->last_sched = sch;
     if (tuning) CHECK_ST(finish_tuning(c));
@@ -3105,12 +3143,12 @@ mvf_status mvf_diffray_forward(mvf_ctx* c, const mvf_dense_tsdf* v, const float 
     CHECK_HIP(hipSetDevice(c->device));
     hipStream_t s = (hipStream_t)stream;
     CHECK_ST(order_after_previous(c, s));
-    CHECK_ST(build_diff_mirror(c, v, s));
+    CHECK_ST(settle(c, build_diff_mirror(c, v, s), s));
     mvf_raycast_out out{};
     out.depth = depth;
     out.width = width;
     out.height = height;
-    return raycast_plain(c, kDiffStream, T_wc, *K, &out, std::vector<int>{c->diff_mirror.vol}, s, record);
+    return settle(c, raycast_plain(c, kDiffStream, T_wc, *K, &out, std::vector<int>{c->diff_mirror.vol}, s, record), s);
 }
 
 // Argument checks shared by the two backward entry points.

@@ -5,7 +5,9 @@
 // stream that nothing orders after all the earlier work on the others is noted
 // too: streams, events and the host carry vector clocks; no stream waits for the
 // null stream (a caller's are non-blocking), and hipMemset does not wait for
-// its clear.
+// its clear.  The launchers keep the kernels' books: the counts that a kernel
+// appends to must be zero when it starts, and a raycast must find an order that
+// no other raycast has used.  A launch can be made to fail.
 #include <hip/hip_runtime.h>
 #include <stdlib.h>
 #include <string.h>
@@ -38,8 +40,16 @@ int work(const char* name)
     return 0;
 }
 
+std::string g_fail;         // the launch of that name fails, once
+std::string g_stale;        // counts that were not zero, orders that were not made
+std::map<const void*, bool> g_ordered;
+
 int work(const char* name, void* stream)
 {
+    if (g_fail == name) {
+        g_fail.clear();
+        return (int)hipErrorLaunchFailure;
+    }
     Clock& seen = g_stream[stream];
     join(seen, g_host);
     bool after_all = true;
@@ -61,7 +71,10 @@ void* t_stream()
     hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
     return s;
 }
-void t_watch() { g_unordered.clear(); }
+void t_watch() { g_unordered.clear(); g_stale.clear(); }
+const char* t_stale() { return g_stale.c_str(); }
+void t_fail(const char* name) { g_fail = name; }
+int t_failed() { return g_fail.empty(); }
 const char* t_unordered() { return g_unordered.c_str(); }
 
 hipError_t hipGetDeviceCount(int* n) { *n = 2; return hipSuccess; }
@@ -114,18 +127,73 @@ hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) { join(g_st
 }
 
 namespace mvf {
-int launch_frame_prep(const PrepItem*, int, int, int, void* s, const void*, void*, size_t) { return work("frame_prep", s); }
+int launch_frame_prep(const PrepItem*, int, int, int, void* s, const void* tsrc, void* tdst, size_t tbytes)
+{
+    const int e = work("frame_prep", s);
+    if (!e && tsrc) memcpy(tdst, tsrc, tbytes);
+    return e;
+}
 int launch_volume_init(DevVolume, void* s) { return work("volume_init", s); }
-int launch_ztable(const IntegrateLaunch&, int, void* s) { return work("ztable", s); }
-int launch_integrate(const IntegrateLaunch&, int, void* s, void*, void*) { return work("integrate", s); }
-int launch_raycast(const RaycastLaunch&, int, void* s, void*, void*) { return work("raycast", s); }
+int launch_ztable(const IntegrateLaunch& L, int, void* s)
+{
+    const int e = work("ztable", s);
+    if (e || !L.list_count) return e;
+    const int par = L.hdr->list_parity;
+    if (L.list_count[par]) g_stale += "list ";
+    L.list_count[par] = 1;
+    L.list_count[par ^ 1] = 0;
+    return 0;
+}
+void ordered(const TileOrder& o)
+{
+    if (o.tiles > 0) g_ordered[o.order] = true;
+}
+void collect(const LaunchHeader* hdr, const RayBounds& rb)
+{
+    for (int v = 0; v < hdr->nvol; ++v) {
+        uint32_t& n = rb.counts[(size_t)hdr->rb_parity * rb.cap + v];
+        if (n) g_stale += "footprints ";
+        n = 1;
+    }
+}
+int launch_integrate(const IntegrateLaunch& L, int, void* s, void*, void*)
+{
+    const int e = work("integrate", s);
+    if (!e) ordered(L.order);
+    return e;
+}
+int launch_raycast(const RaycastLaunch& L, int, void* s, void*, void*)
+{
+    const int e = work("raycast", s);
+    if (!e && !g_ordered[L.tile_order]) g_stale += "order ";
+    g_ordered[L.tile_order] = false;
+    return e;
+}
 int launch_column_flags(DevVolume, void* s) { return work("column_flags", s); }
-int launch_brick_distance(const LaunchHeader*, const DevVolume*, const int32_t*, int, int, void* s, const DevFrame*,
-                          RayBounds) { return work("brick_distance", s); }
-int launch_ray_bounds_collect(const LaunchHeader*, const DevVolume*, const int32_t*, const DevFrame*, RayBounds, int,
-                              void* s) { return work("ray_bounds_collect", s); }
-int launch_ray_bounds_merge(const LaunchHeader*, const DevFrame*, const int32_t*, const int32_t*, const int32_t*,
-                            RayBounds, int, int, int, void* s, TileOrder) { return work("ray_bounds_merge", s); }
+int launch_brick_distance(const LaunchHeader* hdr, const DevVolume*, const int32_t*, int, int bricks, void* s,
+                          const DevFrame* frames, RayBounds rb)
+{
+    if (bricks <= 0) return 0;
+    const int e = work("brick_distance", s);
+    if (!e && frames && rb.entries) collect(hdr, rb);
+    return e;
+}
+int launch_ray_bounds_collect(const LaunchHeader* hdr, const DevVolume*, const int32_t*, const DevFrame*, RayBounds rb, int,
+                              void* s)
+{
+    const int e = work("ray_bounds_collect", s);
+    if (!e) collect(hdr, rb);
+    return e;
+}
+int launch_ray_bounds_merge(const LaunchHeader* hdr, const DevFrame*, const int32_t*, const int32_t*, const int32_t*,
+                            RayBounds rb, int, int, int, void* s, TileOrder order)
+{
+    const int e = work("ray_bounds_merge", s);
+    if (e) return e;
+    std::fill_n(rb.counts + (size_t)(1 - hdr->rb_parity) * rb.cap, rb.cap, 0u);
+    ordered(order);
+    return 0;
+}
 int launch_swap_copy(const void* src, void* dst, size_t bytes, void* s)
 {
     memcpy(dst, src, bytes);
@@ -147,8 +215,9 @@ ExtractBuffers extract_buffers(void*, size_t, long long* total)
 int launch_extract(DevVolume, const ExtractBuffers&, float*, float*, int32_t*, long long, void* s) { return work("extract", s); }
 int launch_fill_u64(unsigned long long* p, int n, unsigned long long value, void* s)
 {
-    std::fill(p, p + n, value);
-    return work("fill", s);
+    const int e = work("fill", s);
+    if (!e) std::fill(p, p + n, value);
+    return e;
 }
 int launch_placement_clear(unsigned long long*, int, int*, void* s) { return work("placement_clear", s); }
 int launch_placement_count(const PlacementCount&, PlacementCells* out, void* s)

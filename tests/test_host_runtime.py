@@ -30,7 +30,8 @@ def lib():
         getattr(lib, name).argtypes = args
         getattr(lib, name).restype = C.c_int32
     lib.mvf_last_error.restype = C.c_char_p
-    lib.t_elsewhere.restype = lib.t_unordered.restype = C.c_char_p
+    lib.t_elsewhere.restype = lib.t_unordered.restype = lib.t_stale.restype = C.c_char_p
+    lib.t_fail.argtypes = [C.c_char_p]
     lib.t_stream.restype = C.c_void_p
     return lib
 
@@ -178,4 +179,66 @@ def test_calls_run_in_order_on_any_stream(lib, steps):
             m.stream = streams[(2 * i + j) % 4]
             CALLS[call](m)
     assert lib.t_unordered().decode() == ""
+    m.close()
+
+
+LAUNCHES = {"integrate": ["frame_prep", "ztable", "integrate", "brick_distance", "volume_init", "fill"],
+            "raycast": ["hipMemcpyAsync", "ray_bounds_collect", "ray_bounds_merge", "raycast"],
+            "step": ["frame_prep", "ztable", "integrate", "brick_distance", "ray_bounds_merge", "raycast"]}
+
+
+@pytest.mark.parametrize("call,launch", [(c, n) for c, ns in LAUNCHES.items() for n in ns])
+def test_after_a_call_that_fails(lib, call, launch):
+    """A call of which one launch fails, in a new context and in one in use: the
+    next ones, on another stream, run after what it launched, append to counts
+    that are zero, and raycast in an order that has been made."""
+    a, b = lib.t_stream(), lib.t_stream()
+    for before in ((), ("integrate", "raycast", "step"), ("raycast", "integrate")):
+        m = Map(lib, volumes=3)
+        for m.stream in (a, b):
+            for c in before:
+                CALLS[c](m)
+        m.stream = a
+        lib.t_watch()
+        lib.t_fail(launch.encode())
+        try:
+            CALLS[call](m)
+            assert not lib.t_failed()   # nothing of that name was launched (an initialised volume, no new memory)
+            lib.t_fail(b"")
+        except AssertionError:
+            assert lib.t_failed()
+        m.stream = b
+        for c in ("raycast", "integrate", "step", "integrate", "raycast", "raycast", "step"):
+            CALLS[c](m)
+        assert (lib.t_stale().decode(), lib.t_unordered().decode()) == ("", ""), before
+        m.close()
+
+
+def test_after_launch_tables_overflow(lib):
+    """An integration into more volumes than a table slot holds is refused; the
+    next one, with fewer, appends to lists whose counts are zero."""
+    m = Map(lib, volumes=0)
+    gid = C.c_int32()
+    m.ok("mvf_grid_create", C.byref(L.mvf_grid_desc((C.c_float * 3)(-2.048, -2.048, 1.0), 0.002, 4.0, 128, 0)), C.byref(gid))
+
+    def volume(offset, dims):
+        vid = C.c_int32()
+        d = L.mvf_volume_desc(gid.value, (C.c_int32 * 3)(*offset), (C.c_int32 * 3)(*dims), 0)
+        m.ok("mvf_volume_create", C.byref(d), C.byref(vid))
+        m.ok("mvf_volume_place", vid)
+        return vid.value
+
+    volume((0, 0, 0), (2048, 2048, 100))   # a launch's work items alone
+    small = [volume((1000 + i % 64, 1000 + i // 64, 120), (2, 2, 2)) for i in range(6000)]
+    for _ in range(2):
+        lib.t_watch()
+        with pytest.raises(AssertionError):
+            CALLS["integrate"](m)
+        for v in small:
+            m.ok("mvf_volume_evict", v, 0)
+        for _ in range(3):
+            CALLS["integrate"](m)
+        assert lib.t_stale().decode() == ""
+        for v in small:
+            m.ok("mvf_volume_place", v)
     m.close()
