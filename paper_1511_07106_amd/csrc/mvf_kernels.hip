@@ -1306,9 +1306,11 @@ static __device__ bool march_volume_group(const DevVolume& V, const Ray& r, floa
         if (t0 > best_t || (t0 == best_t && V.id > best_id)) return false;
     }
     // a crossing is not nearer than its first sample: the last far end is the
-    // last k with (k - 1) delta <= best_t (from an estimate above it)
+    // last k with (k - 1) delta <= best_t (from an estimate above it: its
+    // reciprocal, product and the sample's own product are within 2^-21 together)
     if ((float)(k1 - 1) * delta > best_t) {
-        k1 = min(k1, (int)(best_t * r.inv_delta) + 4);
+        const int q = (int)(best_t * r.inv_delta);
+        k1 = min(k1, q + 4 + (q >> 20));
         while ((float)(k1 - 1) * delta > best_t) --k1;
     }
     const SkipDir dir = skip_dir(V, r, delta);

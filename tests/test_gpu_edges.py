@@ -664,3 +664,37 @@ def test_integrate_grids_together(mvf):
         assert (alone[1] > 0).any()
         for a, b in zip(g, alone):
             np.testing.assert_array_equal(a, b)
+
+
+def test_raycast_of_far_fine_samples(mvf):
+    """Samples far beyond 2^24 along the rays (a ten-thousandth of a voxel apart,
+    400 m away): the crossings of two overlapping volumes lie within a few
+    samples of each other, and the nearer one is taken as in the oracle."""
+    log("raycast of far fine samples")
+    rng = np.random.default_rng(21)
+    dims, s, step, z0 = (48, 40, 24), 0.05, 1e-4, 400.0
+    origin = (-1.2, -1.0, z0)
+    og = O.OGrid(origin, s, 4.0, 128)
+    z, y, x = np.meshgrid(*[np.arange(n) for n in dims[::-1]], indexing="ij")
+    vols = []
+    for i in range(3):
+        surface = 11.3 + 0.002 * rng.standard_normal(z.shape[1:])[None] + 1e-4 * i
+        F = np.clip((surface - z) / 4.0, -1.0, 1.0).astype(np.float32)
+        W = np.full(F.shape, 5, np.uint16)
+        vols.append(O.OVolume(dims, (0, 0, 0), F.astype(np.float64), W, np.zeros(W.shape + (4,), np.uint8)))
+    w, h = 24, 18
+    K = np.array([4400.0, 4400.0, w / 2 - 0.3, h / 2 + 0.2], np.float32)
+    T = np.concatenate([np.eye(3), np.zeros((3, 1))], 1)
+    with mvf.Context(ray_step=step, t_far=450.0) as ctx:
+        gid = ctx.grid(origin, s, 4.0, 128)
+        ids = []
+        for v in vols:
+            ids.append(ctx.volume(gid, (0, 0, 0), dims))
+            ctx.write_volume(ids[-1], v.F32(), v.W, v.Cc)
+        out = {k: v.cpu().numpy() for k, v in ctx.raycast(T, K, w, h).items()}
+    rc = O.raycast(vols, og, K, T, w, h, step=step, t_far=450.0)
+    assert (rc["hit"] >= 0).mean() > 0.9 and len(np.unique(rc["hit"])) >= 3
+    assert rc["k"].max() > 1 << 26
+    np.testing.assert_array_equal(out["hit"], np.where(rc["hit"] >= 0, np.asarray(ids)[np.maximum(rc["hit"], 0)], -1))
+    # binary32 world coordinates are 3e-5 m apart there
+    assert np.abs(out["depth"].astype(np.float64) - rc["depth"])[rc["hit"] >= 0].max() <= 1e-3
